@@ -160,7 +160,7 @@ hhlb_status hhlb_init_equilibrium(hhlb_solver *s, double n0, double u0, double T
 
 /* Advance every channel by n_steps TVD RK-3 steps (Eq. rk3).  Asynchronous:
  * ordered after the work already on the solver's stream and before work
- * enqueued there later.  By default every stage kernel is launched directly
+ * enqueued there later.  By default every kernel is launched directly
  * on the solver's stream; hhlb_set_graph_steps switches to HIP graph replay.
  * Returns HHLB_E_NUMERIC without stepping when the last hhlb_diagnostics
  * found non-finite populations (it waits for that diagnostics to finish). */
@@ -179,18 +179,15 @@ hhlb_status hhlb_step(hhlb_solver *s, int64_t n_steps);
  *  xcd_map:       1 = consecutive windows of a channel go to the same XCD
  *                 (the hardware deals blocks round-robin over the 8 XCDs);
  *                 0 = block b handles window b.
- *  waves_per_window: 2 = one wave per momentum half holds both f and chi of
- *                 a 64-cell window; 4 = one wave per half and function (FP64
- *                 half-range channels with chi; other classes keep 2).
- *  step_fusion:   1 = the three stages of a step (Eq. rk3) in one launch per
- *                 class, y^n and the stage state kept in registers over
- *                 windows with 9-cell halos (FP64 half-range Gauss-Hermite
- *                 classes; others keep one launch per stage); 0 = one launch
- *                 per stage.  The stages' arithmetic is the same; results
- *                 agree to rounding (the equilibrium's correction count is
- *                 chosen per window of cells).
- *  merge_classes: 0 = one launch per stage for each model class; 1 = one
- *                 launch per stage for all FP64 half-range classes that share
+ *  waves_per_window, step_fusion: kept for callers that set them.  FP64
+ *                 classes with Q <= 16 run whole steps (Eq. rk3) per launch
+ *                 whatever the value -- windows of 128 cells with 9-cell
+ *                 halos, one wave per momentum half and function, y^n and the
+ *                 stage state in registers; classes whose channels fit one
+ *                 window each (Nx <= 124) up to 64 steps per launch -- and the
+ *                 other classes one launch per stage.
+ *  merge_classes: 0 = launches of their own for each model class; 1 = one
+ *                 launch per step for all FP64 half-range classes that share
  *                 the functions (f, or f and chi) and the scheme, each block
  *                 taking one window of any of them; 2 = the same launch with
  *                 as many blocks as the GPU holds at once, each taking
@@ -254,7 +251,8 @@ hhlb_status hhlb_moments(const hhlb_solver *s, double *n_dev, double *u_dev, dou
 hhlb_status hhlb_diagnostics(hhlb_solver *s, double *n_wall_dev, double *mass_dev, double *residual_dev,
                              int32_t *nonfinite_dev);
 
-/* Kernel launches one hhlb_step of one RK stage issues (for profiling). */
+/* Kernel launches of one RK stage (for profiling); where a launch takes a
+ * whole step it counts as one. */
 hhlb_status hhlb_launch_info(const hhlb_solver *s, int32_t *launches_per_stage,
                              int64_t *windows_total);
 

@@ -1,332 +1,686 @@
-// gfx950 kernel for one whole TVD RK-3 step (the three stages of Eq. rk3)
-// of the half-range model per launch, FP64: step fusion with a 9-cell halo.
+// gfx950 kernel for whole TVD RK-3 steps (the three stages of Eq. rk3) of one
+// model class per launch, FP64, half-range (HHLB) and full-range (HLB) models
+// with at most 16 nodes per half.
 //
-// The per-stage kernels read the stage state and y^n and write the next
-// stage: 8 array passes per function and step.  Here a window keeps y^n and
-// the stage state of its 64 cells in registers through the three stages and
-// touches memory twice per function: y^n in, y^{n+1} out.
+// A stage per launch moves 8 array passes per function and step and ran at
+// 88 % of a device copy's rate on 256 channels of 16384 cells (Q = 16, 1.57 ms
+// a launch): nothing but fewer bytes could speed it up.  Here a window keeps
+// y^n and the stage state in registers through the three stages and touches
+// memory twice per function and step: y^n in, y^{n+1} out.
 //
-// Window geometry.  Lane l holds cell c0 + l.  Each stage's WENO-5 stencil
-// reaches 3 cells, so a lane's value stays exact for one stage less per 3
-// lanes from an edge of the window that is not a wall: a window whose edges
-// are interior keeps 9 halo lanes on each side and writes at most the 46
-// cells of lanes 9..54.  At a wall the closure (Sec. IV.C.3) rebuilds the
-// ghosts from the current stage every stage, exactly as the per-stage kernel
-// does, so nothing is lost there.  The faces the method needs read the first
-// two ghosts only, so a wall may sit where just two ghost lanes fit (cell 0
-// at lane 2 or 3; cell Nx-1 at lane 61 or below).  The host builds each
-// channel's windows (fused_windows) so that every window edge is either such
-// a wall or lies inside the channel with its whole halo.
+// Mapping: a block of one wave per momentum half and function (f, chi) holds
+// 128 consecutive cells, two neighbouring cells per lane.  Two cells per lane
+// halve the lane shifts of the WENO-5 stencil (10 moves per two faces instead
+// of 20) and the share of halo lanes (110 of 128 cells are written, where a
+// window of 64 would write 46 of 64), and give every wave two independent
+// chains.  The waves of a half share the equilibrium: each evaluates it for
+// one of the two cells of its lanes.  The halves meet in LDS: moment sums,
+// wall densities, the equilibrium populations (and, full range, the
+// populations the dense force matrix couples), two barriers per stage.
 //
-// Per stage the arithmetic is that of stage_kernel_half: the same closure,
-// moments, equilibrium, force block, BGK, face values and combination
-// y_{s+1} = a_s y^n + b_s (y_s + dt L[y_s]), with y^n from registers.  Lanes
-// outside the stage's exact range compute values that are never used; they
-// are kept out of the wave-wide decisions (the equilibrium ladder and the
-// WENO rescaling branch).
+// Window geometry.  Position q holds cell c0 + q.  Each stage's stencil reaches
+// 3 cells, so the cells next to a window edge that is not a wall go stale at 3
+// per stage: a window writes the cells at least 9 from such an edge.  At a
+// wall the closure (Sec. IV.C.3) rebuilds the ghosts from the current stage
+// every stage, so nothing is lost there; the faces read the first two ghosts
+// only, and a wall sits where those two fit (cell 0 at position 2, cell Nx-1
+// at position 125 or below).  The host builds each channel's windows
+// (step_windows).  A channel that fits one window (Nx <= 124) needs no
+// neighbour at all: such classes take many steps in one launch.
+//
+// Lanes run down the wind of their half (see weno5_down): wind position 2 l + s
+// of slot s of lane l is position 2 l + s for p > 0 and 127 - (2 l + s) for
+// p < 0.
 #pragma once
 #include "step_kernels.hpp"
 
-// occupancy target: three waves per SIMD while y^n and the stage state of
-// both functions fit beside the working set (Q <= 4), two above
-#ifndef HHLB_FUSED_WAVES_SMALL
-#define HHLB_FUSED_WAVES_SMALL 3
-#endif
-#ifndef HHLB_FUSED_WAVES_LARGE
-#define HHLB_FUSED_WAVES_LARGE 2
-#endif
-
 namespace hhlb {
 
-constexpr int kFusedHalo = 3 * kHalo;   // halo lanes of an interior window edge
-// largest per-half order with a fused-step kernel: y^n and the stage state of
-// both functions stay in registers, 4Q doubles per lane
-#ifndef HHLB_FUSED_QMAX
-#define HHLB_FUSED_QMAX 16
-#endif
-constexpr int kQmaxFused = HHLB_FUSED_QMAX;
+constexpr int kStepCells = 128;         // cells a window holds
+constexpr int kStepHalo = 3 * kHalo;    // stale cells at an edge that is not a wall
+constexpr int kStepGhosts = 2;          // ghosts kept beyond a wall
+// output cells: both walls in the window, one, none
+constexpr int kStepSingle = kStepCells - 2 * kStepGhosts;
+constexpr int kStepWall = kStepCells - kStepGhosts - kStepHalo;
+constexpr int kStepInner = kStepCells - 2 * kStepHalo;
 
-// One window of the fused kernel: channel, first output cell, cell of lane
-// 0 and the number of output cells (lanes i0 - c0 .. i0 - c0 + nout - 1).
+// waves per SIMD the registers are fitted to: y^n, the stage state and the
+// sources take 6 H doubles per lane
+constexpr int step_waves(int H) { return H <= 4 ? 4 : (H <= 8 ? 3 : 2); }
+
+// One window: channel, first output cell, cell of position 0 and the number
+// of output cells.
 struct DevFusedWindow {
   int32_t ch, i0, c0, nout;
 };
+struct DevFusedClassWindow {
+  int32_t ch, i0, c0, nout;
+  int32_t cls, Q;   // model class (index of its tables) and its order
+  int32_t pad[2];
+};
 
-template <int Q, int NFUN, int ADV>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(
-    Q <= 4 ? HHLB_FUSED_WAVES_SMALL : HHLB_FUSED_WAVES_LARGE))) void fused_kernel_half(
-    StageArgs A, const DevTables *__restrict__ tb, const DevChannel *__restrict__ chans,
-    const DevFusedWindow *__restrict__ wins, const double *__restrict__ inv_dx,
-    const double *__restrict__ gw, const double *__restrict__ in_f,
-    const double *__restrict__ in_c) {
-  constexpr int H = Q;
-  constexpr int NC = NFUN;
-  __shared__ double s_nw[2];
-  constexpr bool kMfma = HHLB_MFMA && (H == 16);
-  constexpr int kLds = (kMfma ? 2 * 64 * 17 : 1) > 2 * 6 * 64 ? 2 * 64 * 17 : 2 * 6 * 64;
-  __shared__ double s_lds[kLds];
-  double (*s_part)[6][64] = reinterpret_cast<double (*)[6][64]>(s_lds);
-  double *s_T = s_lds;
-  const int hw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// Orders whose H x H contractions (equilibrium table, force block) run on the
+// matrix cores.
+#ifndef HHLB_STEP_MFMA
+#define HHLB_STEP_MFMA 16
+#endif
+template <int QUAD, int Q>
+constexpr bool step_mfma() { return QUAD == 0 && Q >= HHLB_STEP_MFMA && Q % 4 == 0; }
+
+// LDS of a window (doubles)
+template <int QUAD, int Q, int NFUN>
+constexpr int step_lds_doubles() {
+  constexpr int H = QUAD == 0 ? Q : Q / 2;
+  constexpr int part = 2 * 6 * kStepCells;            // moment partials of the halves
+  constexpr int geq = 2 * 2 * H * 64;                 // equilibrium populations
+  constexpr int y = QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells;   // dense force matrix: every node's population
+  // matrix cores: a tile per wave, in the memory of the partials (dead by then)
+  constexpr int tile = step_mfma<QUAD, Q>() ? 2 * NFUN * H * 64 : 0;
+  return (tile > part ? tile : part) + geq + y + 2;
+}
+
+// Register layout of v_mfma_f64_16x16x4f64 (checked on the GPU):
+//   A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
+//   D[i][j] in lane j + 16 (i % 4), accumulator register i / 4.
+// X[i][cell] <- sum_k M[i][k] X[k][cell] for the H x H table M (A operands
+// aM[kc] = M[lane % 16][4 kc + lane / 16], zero outside) and the H rows of 64
+// cells of a tile in LDS, in place.  Node-major rows serve all four accesses
+// (a lane's own cell, B operand, D result, own cell again) without padding:
+// every 16 lanes touch one run of 128 bytes.
+template <int H>
+__device__ __forceinline__ void mfma_tile(const double *aM, double *T, int lane) {
+  constexpr int KC = H / 4;
+  __builtin_amdgcn_wave_barrier();
+  dbl4 acc[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) {
+    acc[cb] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+      acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aM[kc], T[(4 * kc + (lane >> 4)) * 64 + 16 * cb + (lane & 15)],
+                                                     acc[cb], 0, 0, 0);
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int r = 0; r < KC; ++r) T[(4 * r + (lane >> 4)) * 64 + 16 * cb + (lane & 15)] = acc[cb][r];
+  __builtin_amdgcn_wave_barrier();
+}
+template <int H>
+__device__ __forceinline__ void mfma_operand(const double *M, int lane, double *aM) {
+  const int i = lane & 15;
+#pragma unroll
+  for (int kc = 0; kc < H / 4; ++kc) aM[kc] = i < H ? M[(i < H ? i : 0) * H + 4 * kc + (lane >> 4)] : 0.0;
+}
+
+// exp(a) for -1/2 <= a <= 0 (the correction rule within its calibrated
+// range): the Taylor polynomial of degree 14, remainder below 3e-17, as
+// four interleaved polynomials in a^4 (a chain of 6 instead of 14).
+__device__ __forceinline__ double exp_small(double a) {
+  const double a2 = a * a, a4 = a2 * a2;
+  const double p0 = fma(a4, fma(a4, fma(a4, 1.0 / 479001600, 1.0 / 40320), 1.0 / 24), 1.0);
+  const double p1 = fma(a4, fma(a4, fma(a4, 1.0 / 6227020800.0, 1.0 / 362880), 1.0 / 120), 1.0);
+  const double p2 = fma(a4, fma(a4, fma(a4, 1.0 / 87178291200.0, 1.0 / 3628800), 1.0 / 720), 0.5);
+  const double p3 = fma(a4, fma(a4, 1.0 / 39916800, 1.0 / 5040), 1.0 / 6);
+  return fma(a2, fma(a, p3, p2), fma(a, p1, p0));
+}
+
+// 1/sqrt(x) for normal, finite x > 0: the hardware estimate refined by two
+// Newton-Raphson steps.
+__device__ __forceinline__ double rsqrt_full(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  double e = fma(-x * r, r, 1.0);
+  r = fma(0.5 * r, e, r);
+  e = fma(-x * r, r, 1.0);
+  return fma(0.5 * r, e, r);
+}
+
+// Sum over the first 16 lanes (lanes 16.. hold zero), returned as a scalar.
+__device__ __forceinline__ double row_sum16(double x) {
+#define HHLB_ROW_ADD(ctrl)                                                                              \
+  x += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), ctrl, 0xf, 0xf, true),        \
+                        __builtin_amdgcn_update_dpp(0, __double2loint(x), ctrl, 0xf, 0xf, true))
+  HHLB_ROW_ADD(0x111);   // row_shr:1, 2, 4, 8
+  HHLB_ROW_ADD(0x112);
+  HHLB_ROW_ADD(0x114);
+  HHLB_ROW_ADD(0x118);
+#undef HHLB_ROW_ADD
+  return readlane_d(x, 15);
+}
+
+// Largest of the wave's non-negative values, rounded up to FP32.
+__device__ __forceinline__ float wave_max_up(double x) {
+  float m = (float)x * 1.0000002f;
+#define HHLB_ROW_MAX(ctrl, rows)                                                                          \
+  m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), ctrl, rows, 0xf, false)))
+  HHLB_ROW_MAX(0x111, 0xf);
+  HHLB_ROW_MAX(0x112, 0xf);
+  HHLB_ROW_MAX(0x114, 0xf);
+  HHLB_ROW_MAX(0x118, 0xf);
+  HHLB_ROW_MAX(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+  HHLB_ROW_MAX(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef HHLB_ROW_MAX
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 63));
+}
+
+// WENO-5 values at the downwind faces of a lane's two cells (wind positions
+// 2 l and 2 l + 1): weno5_down with the differences the two faces share
+// formed once, and one branch for the rare rescaling of either.
+struct WenoWeights {
+  double sL, sC, sR, pL, pC, pR, dd;
+  __device__ __forceinline__ void products(double a, double b, double c) {
+    const double q1 = a * a, q2 = b * b, q3 = c * c;
+    pL = q2 * q3; pC = q1 * q3; pR = q1 * q2;
+    dd = fma(0.5, pR, fma(1.0 / 6.0, pL, pC));
+  }
+  __device__ __forceinline__ WenoWeights(double dm, double dp, double DL, double D, double DR, double qL, double qD,
+                                         double qR) {
+    constexpr double h = 0.5 / kSq1312;
+    const double tL = fma(h, DL, dm), tC = fma(h, D, dm), tR = fma(-h, DR, dp);
+    sL = fma(tL, tL, qL); sC = fma(tC, tC, qD); sR = fma(tR, tR, qR);
+    products(sL, sC, sR);
+  }
+  __device__ __forceinline__ bool regular() const { return dd > 1e-260 && dd < 1e260; }
+  __device__ __forceinline__ void rescale() {
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(sL, fmax(sC, sR)));
+    const double rL = ldexp(sL, -ex), rC = ldexp(sC, -ex), rR = ldexp(sR, -ex);
+    products(rL, rC, rR);
+    if (!(dd > 1e-250)) {
+      const double tiny = 1e-125;
+      pL = rL * rL < tiny ? 1.0 : 0.0;
+      pC = rC * rC < tiny ? 1.0 : 0.0;
+      pR = rR * rR < tiny ? 1.0 : 0.0;
+      dd = fma(0.5, pR, fma(1.0 / 6.0, pL, pC));
+    }
+  }
+  __device__ __forceinline__ double face(double dm, double dp, double dLD, double dDR, double y) const {
+    const double r = __builtin_amdgcn_rcp(dd), e = fma(-dd, r, 1.0), e2 = fma(e, e, e);
+    double m = fma(1.5, pR * dDR, pL * dLD) * r;
+    m = fma(m, e2, m);
+    return fma(1.0 / (18.0 * kSq1312), m, fma(1.0 / 3.0, dp, fma(1.0 / 6.0, dm, y)));
+  }
+};
+
+template <int ADV>
+__device__ __forceinline__ void faces_down2(double ya, double yb, bool usedA, bool usedB, double &fa, double &fb) {
+  const double da = yb - ya, db = dpp_shl1(ya) - yb, dm = dpp_shr1(db);
+  if constexpr (ADV == 0) {
+    const double Da = kSq1312 * (da - dm), Db = kSq1312 * (db - da);
+    const double Dl = dpp_shr1(Db), Dr = dpp_shl1(Da);
+    const double qa = Da * Da, qb = Db * Db, dab = Da - Db;
+    WenoWeights wa(dm, da, Dl, Da, Db, Dl * Dl, qa, qb), wb(da, db, Da, Db, Dr, qa, qb, Dr * Dr);
+    if ((!wa.regular() && usedA) || (!wb.regular() && usedB)) {
+      wa.rescale();
+      wb.rescale();
+    }
+    fa = wa.face(dm, da, Dl - Da, dab, ya);
+    fb = wb.face(da, db, dab, Db - Dr, yb);
+  } else {
+    fa = fma(1.0 / 3.0, da, fma(1.0 / 6.0, dm, ya));
+    fb = fma(1.0 / 3.0, db, fma(1.0 / 6.0, da, yb));
+  }
+}
+
+// nsteps steps of nst stages (3; or 1: one forward-Euler stage, for the
+// residual) of one window, run by a block of 2 NFUN waves.
+template <int QUAD, int Q, int NFUN, int ADV>
+__device__ __forceinline__ void step_window(const StageArgs &A, const DevTables *tb, const DevChannel *chans,
+                                            const DevFusedWindow win, const double *__restrict__ inv_dx,
+                                            const double *__restrict__ gw, const double *__restrict__ in_f,
+                                            const double *__restrict__ in_c, double *s_lds) {
+  constexpr int H = QUAD == 0 ? Q : Q / 2;
+  constexpr int SLOTS = 2;
+  ConstTables tp = (ConstTables)tb;
+  ConstChannel cp = (ConstChannel)(chans + win.ch);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hw = wv & 1, fn = NFUN > 1 ? wv >> 1 : 0;
   const int lane = threadIdx.x & 63;
-  const int w = A.xcd_map ? xcd_window(blockIdx.x, A.nwin) : (int)blockIdx.x;
-  const DevFusedWindow win = wins[w];
-  const DevChannel C = chans[win.ch];
-  const int Nx = C.Nx;
-  const int c0 = win.c0;                             // cell of lane 0
-  const int hl = win.i0 - c0, nout = win.nout;       // output lanes hl .. hl + nout - 1
-  const bool needL = c0 < 0;                         // the walls inside the window
-  const bool needR = Nx - 1 - c0 <= 61;
-  const int i = c0 + lane;
-  const bool inside = i >= 0 && i < Nx;
-  const int ic = inside ? i : 0;                     // clamped cell index: loads stay in bounds
-  const int kb0 = hw * H;
+  const int pl = hw ? 63 - lane : lane;                 // index of the lane's cells in the shared arrays
+  const int Nx = cp->Nx, c0 = win.c0;
   const double sg = hw ? -1.0 : 1.0;
-  const int64_t obase = C.off + (int64_t)kb0 * Nx;
+  constexpr bool kMfma = step_mfma<QUAD, Q>();
+  double *s_part = s_lds, *s_tile = s_lds + wv * H * 64;   // the tile: matrix cores only
+  double *s_geq = s_lds + (step_lds_doubles<QUAD, Q, NFUN>() - 2 - 2 * 2 * H * 64 - (QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells));
+  double *s_y = s_geq + 2 * 2 * H * 64;
+  double *s_nw = s_lds + step_lds_doubles<QUAD, Q, NFUN>() - 2;
+  // plane (parity of the position) and cell of each slot
+  const int plane[SLOTS] = {hw, 1 - hw};
+  const int i[SLOTS] = {hw ? c0 + 127 - 2 * lane : c0 + 2 * lane, hw ? c0 + 126 - 2 * lane : c0 + 2 * lane + 1};
+  const int first = win.i0 - c0, last = first + win.nout - 1;   // output positions
+  const bool needL = c0 < 0, needR = Nx - 1 - c0 <= kStepCells - 1 - kStepGhosts;
+  const bool down = hw ? needL : needR, up = hw ? needR : needL;
 
-  double yf[H], yc[NC > 1 ? H : 1], nf[H], nc[NC > 1 ? H : 1];
+  const int w0 = c0 < 0 ? 0 : c0, w1 = c0 + kStepCells < Nx ? c0 + kStepCells : Nx;
+  const uint32_t wbytes = (uint32_t)(w1 - w0) * 8u;
+  uint32_t off[SLOTS];
+  bool inside[SLOTS];
+  double dxi[SLOTS];
+  const int64_t obase = cp->off + (int64_t)(hw * H) * Nx + w0;
+  const int64_t stride = (int64_t)Nx * 8;
 #pragma unroll
-  for (int j = 0; j < H; ++j) nf[j] = inside ? in_f[obase + (int64_t)j * Nx + ic] : 0.0;
-  if constexpr (NC > 1) {
-#pragma unroll
-    for (int j = 0; j < H; ++j) nc[j] = inside ? in_c[obase + (int64_t)j * Nx + ic] : 0.0;
+  for (int s = 0; s < SLOTS; ++s) {
+    inside[s] = i[s] >= 0 && i[s] < Nx;
+    off[s] = (uint32_t)(i[s] - w0) * 8u;
+    dxi[s] = row_load(row_rsrc(inv_dx + cp->cell_off + w0, wbytes), off[s]);
   }
+  double lad = 0.0;   // reach of the correction rule `lane`
+  if constexpr (QUAD == 0) lad = tb->lad_y[lane < kLadderAll ? lane : kLadderAll - 1];
+
+  double yn[H][SLOTS], y[H][SLOTS];
+  {
+    RowWalk w(fn == 0 ? in_f : in_c, obase);
 #pragma unroll
-  for (int j = 0; j < H; ++j) {
-    yf[j] = nf[j];
-    if constexpr (NC > 1) yc[j] = nc[j];
+    for (int j = 0; j < H; ++j) {
+      const __amdgpu_buffer_rsrc_t r = w.take(stride, wbytes);
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) y[j][s] = yn[j][s] = row_load(r, off[s]);
+    }
   }
 
-  const double dx_inv = inv_dx[C.cell_off + ic];
-  const double gforce = C.g, dt = C.dt;
-  const FaceCoef fcoef = face_coef(hw);
-  const bool wall_face_l = hw == 0 ? (i == -1) : (i == Nx);
-  const double sdx = hw == 0 ? -dx_inv : dx_inv;   // L = sdx (F - F_other) + source
-  const double *gwL = gw + C.gw_off, *gwR = gw + C.gw_off + 2 * H + H;
-
+  int wide = 0;   // evaluations whose correction lay beyond the calibrated ladder
 #pragma unroll 1
-  for (int st = 0; st < 3; ++st) {
+  for (int it = 0; it < A.nsteps * A.nst; ++it) {
+    const int st = A.nst == 1 ? 0 : it % 3;
     // Eq. (rk3): y_{s+1} = a_s y^n + b_s (y_s + dt L[y_s])
     const double a_s = st == 0 ? 0.0 : (st == 1 ? 0.75 : 1.0 / 3.0);
     const double b_s = st == 0 ? 1.0 : (st == 1 ? 0.25 : 2.0 / 3.0);
-    // lanes whose stage result is still exact: 3 fewer per stage at each
-    // window edge that is not a wall
-    const int lo = needL ? 0 : kHalo * (st + 1);
-    const int hi = needR ? 63 : 60 - kHalo * st;
-    const bool live = lane >= lo && lane <= hi;
-    if (st > 0) __syncthreads();   // the previous stage's tiles are read before the partials overwrite them
+    // positions whose result is still exact after this stage
+    const int left = 3 * (A.nst - 1 - st);
+    const int lo = needL ? 0 : first - left, hi = needR ? kStepCells - 1 : last + left;
 
-    // ---- closure, part 1: incoming ghosts extrapolated from the three
-    // nearest cells, and the wall density from their wall-face fluxes ----
+    // ---- closure, part 1: ghosts of the nodes flowing into a wall are
+    // extrapolated quadratically from the three nearest cells (Sec. IV.C.3)
+    // and their wall-face fluxes give the wall density (Eq. nplus_def) ----
     double nw_mine = 0.0;
-    if ((hw == 1 && needL) || (hw == 0 && needR)) {
-      const bool left = hw == 1;
-      const int l0 = left ? -c0 : Nx - 1 - c0;     // lane of the wall cell
-      const int dl = left ? 1 : -1;
-      const int gi = left ? -i : i - Nx + 1;       // ghost order 1..3 (else <= 0)
-      const double e0 = gi == 1 ? 3.0 : (gi == 2 ? 6.0 : 10.0);
-      const double e1 = gi == 1 ? -3.0 : (gi == 2 ? -8.0 : -15.0);
-      const double e2 = gi == 1 ? 1.0 : (gi == 2 ? 3.0 : 6.0);
-      const bool is_ghost = gi >= 1 && gi <= 3;
+    if (down) {
+      int ln = lane;   // what the closure needs of the lane is formed anew, not kept through the steps
+      asm volatile("" : "+v"(ln));
+      const int pd = hw ? kStepCells - 1 + c0 : Nx - 1 - c0;   // wind position of the wall cell
+      const int lp = pd >> 1;
+      const bool odd = pd & 1;
+      double c_[3][SLOTS];
+      bool ghost[SLOTS];
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) {
+        const int gi = 2 * ln + s - pd;   // ghost order 1, 2 (else <= 0)
+        ghost[s] = gi == 1 || gi == 2;
+        c_[0][s] = gi == 1 ? 3.0 : 6.0;
+        c_[1][s] = gi == 1 ? -3.0 : -8.0;
+        c_[2][s] = gi == 1 ? 1.0 : 3.0;
+      }
+      // lane j gathers node j's three wall-adjacent values; ghost lanes
+      // extrapolate every node of this half
       double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        const double y0 = readlane_d(yf[j], l0), y1 = readlane_d(yf[j], l0 + dl),
-                     y2 = readlane_d(yf[j], l0 + 2 * dl);
-        if (lane == j) { a0 = y0; a1 = y1; a2 = y2; }
-        if (is_ghost) yf[j] = e0 * y0 + e1 * y1 + e2 * y2;
-        if constexpr (NC > 1) {
-          const double x0 = readlane_d(yc[j], l0), x1 = readlane_d(yc[j], l0 + dl),
-                       x2 = readlane_d(yc[j], l0 + 2 * dl);
-          if (is_ghost) yc[j] = e0 * x0 + e1 * x1 + e2 * x2;
-        }
+        const double e0 = readlane_d(y[j][0], lp), o0 = readlane_d(y[j][1], odd ? lp : lp - 1),
+                     e1 = readlane_d(y[j][0], lp - 1), o1 = readlane_d(y[j][1], lp - 1);
+        const double y0 = odd ? o0 : e0, y1 = odd ? e0 : o0, y2 = odd ? o1 : e1;
+        if (ln == j) { a0 = y0; a1 = y1; a2 = y2; }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+          if (ghost[s]) y[j][s] = fma(c_[2][s], y2, fma(c_[1][s], y1, c_[0][s] * y0));
       }
-      const double g1 = 3.0 * a0 - 3.0 * a1 + a2, g2 = 6.0 * a0 - 8.0 * a1 + 3.0 * a2;
-      const double fv = face_value<ADV>(a2, a1, a0, g1, g2);
-      const double acc = wave_sum(lane < H ? tb->p[kb0 + (lane < H ? lane : 0)] * fv : 0.0);
-      nw_mine = -acc * (left ? C.inv_DL : C.inv_DR);
+      if (fn == 0) {
+        // incoming wall-face flux of node `lane`, all nodes in parallel
+        const double g1 = fma(3.0, a0 - a1, a2), g2 = fma(6.0, a0, fma(-8.0, a1, 3.0 * a2));
+        const double fv = face_value<ADV>(a2, a1, a0, g1, g2);
+        const double acc = row_sum16(ln < H ? tb->p[ln < H ? ln : 0] * fv : 0.0);
+        nw_mine = -sg * acc * (hw ? cp->inv_DL : cp->inv_DR);
+      }
     }
 
     // ---- partial moments of this half and the rank-1 force projections ----
-    double pn = 0.0, pm = 0.0, ps = 0.0, pc = 0.0, pbf = 0.0, pbc = 0.0;
+    asm volatile("" : "+s"(tp), "+s"(cp));
+    auto part = [&](int h, int q, int s) -> double & {
+      return s_part[((h * 6 + q) * 2 + plane[s]) * 64 + pl];
+    };
+    {
+      double m0[SLOTS] = {0.0, 0.0}, mb[SLOTS] = {0.0, 0.0};
+      if (fn == 0) {   // uniform over the wave
+        double m1[SLOTS] = {0.0, 0.0}, m2[SLOTS] = {0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < H; ++j) {
-      const double v = tb->p[kb0 + j];
-      pn += yf[j];
-      pm += v * yf[j];
-      ps += v * v * yf[j];
-      pbf += tb->kb[j] * yf[j];
-      if constexpr (NC > 1) { pc += yc[j]; pbc += tb->kb[j] * yc[j]; }
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) {
+            m0[s] += y[j][s];
+            m1[s] = fma(tp->p[j], y[j][s], m1[s]);
+            m2[s] = fma(tp->vv[j], y[j][s], m2[s]);
+            if constexpr (QUAD == 0) mb[s] = fma(tp->kb[j], y[j][s], mb[s]);
+          }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          part(hw, 0, s) = m0[s];
+          part(hw, 1, s) = sg * m1[s];
+          part(hw, 2, s) = m2[s];
+          part(hw, 4, s) = mb[s];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) {
+            m0[s] += y[j][s];
+            if constexpr (QUAD == 0) mb[s] = fma(tp->kb[j], y[j][s], mb[s]);
+          }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          part(hw, 3, s) = m0[s];
+          part(hw, 5, s) = mb[s];
+        }
+      }
     }
-    s_part[hw][0][lane] = pn;
-    s_part[hw][1][lane] = pm;
-    s_part[hw][2][lane] = ps;
-    s_part[hw][3][lane] = pc;
-    s_part[hw][4][lane] = pbf;
-    s_part[hw][5][lane] = pbc;
-    if (lane == 0) s_nw[hw] = nw_mine;
+    if constexpr (QUAD == 1) {
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) s_y[((fn * 2 * H + hw * H + j) * 2 + plane[s]) * 64 + pl] = y[j][s];
+    }
+    if (fn == 0 && lane == 0) s_nw[hw] = nw_mine;
     __syncthreads();
-    double n = s_part[0][0][lane] + s_part[1][0][lane];
-    double mom = s_part[0][1][lane] + s_part[1][1][lane];
-    const double s2 = s_part[0][2][lane] + s_part[1][2][lane];
-    const double ech = s_part[0][3][lane] + s_part[1][3][lane];
-    const double bf = s_part[0][4][lane] + s_part[1][4][lane];
-    const double bc = s_part[0][5][lane] + s_part[1][5][lane];
-    const double nL = s_nw[1], nR = s_nw[0];
-    __syncthreads();   // the tiles below overwrite the partials
 
-    // ---- closure, part 2: emergent ghosts n_w g^w_k in all three cells ----
-    if (hw == 0 && i < 0) {
+    // ---- closure, part 2: emergent ghosts n_w g^w_k ----
+    if (up) {
+      const double nw = s_nw[1 - hw];
+      const double sc = fn == 0 ? nw : nw * (cp->half_Dt * (hw ? cp->TR : cp->TL));
+      typedef const __attribute__((address_space(4))) double *ConstDoubles;
+      ConstDoubles gww = (ConstDoubles)gw + cp->gw_off + (hw ? 3 * H : 0);
+      asm volatile("" : "+s"(gww));
+      const bool gh[SLOTS] = {hw ? i[0] >= Nx : i[0] < 0, hw ? i[1] >= Nx : i[1] < 0};
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        yf[j] = nL * gwL[j];
-        if constexpr (NC > 1) yc[j] = C.half_Dt * C.TL * yf[j];
-      }
-    }
-    if (hw == 1 && i >= Nx && i <= Nx + 2) {
+        const double ghost = sc * gww[j];
 #pragma unroll
-      for (int j = 0; j < H; ++j) {
-        yf[j] = nR * gwR[j];
-        if constexpr (NC > 1) yc[j] = C.half_Dt * C.TR * yf[j];
+        for (int s = 0; s < SLOTS; ++s) y[j][s] = gh[s] ? ghost : y[j][s];
       }
     }
-    if (A.nwall && st == 2 && lane == 0) {
-      if (hw == 1 && needL) A.nwall[2 * win.ch] = nL;
-      if (hw == 0 && needR) A.nwall[2 * win.ch + 1] = nR;
+    if (A.nwall && it == A.nsteps * A.nst - 1 && A.nst == 3 && fn == 0 && lane == 0) {
+      if (hw == 1 && needL) A.nwall[2 * win.ch] = nw_mine;
+      if (hw == 0 && needR) A.nwall[2 * win.ch + 1] = nw_mine;
     }
 
     // ---- moments (Eq. fmoms) ----
-    if (!inside) n = 1.0, mom = 0.0;
-    const double u = mom / n;
-    double T = (s2 - u * mom + 2.0 * ech) * C.inv_1pDt / n;
-    if (!inside) T = 1.0;
-    const double inv_tau = n * C.inv_Kn;
+    double n[SLOTS], u[SLOTS], T[SLOTS], bp[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      const double ns = part(0, 0, s) + part(1, 0, s), mom = part(0, 1, s) + part(1, 1, s);
+      const double s2 = part(0, 2, s) + part(1, 2, s);
+      double ech = 0.0;
+      if constexpr (NFUN > 1) ech = part(0, 3, s) + part(1, 3, s);
+      bp[s] = QUAD == 0 ? part(0, 4 + fn, s) + part(1, 4 + fn, s) : 0.0;
+      const double rn = recip(ns);
+      n[s] = inside[s] ? ns : 1.0;
+      u[s] = inside[s] ? mom * rn : 0.0;
+      T[s] = inside[s] ? fma(2.0, ech, fma(-u[s], mom, s2)) * (cp->inv_1pDt * rn) : 1.0;
+    }
 
-    // ---- equilibrium coefficients of this half ----
-    double G[Q];
-#pragma unroll
-    for (int l = 0; l < Q; ++l) G[l] = 0.0;
-    if (C.inv_Kn != 0.0) {
-      const double sT = sqrt(T);
-      const double ub = sg * u * tb->inv_p0, s = sT * tb->inv_p0, y0 = -u / sT;
-      auto accum = [&](double x, double wt) {
-        double qm = 1.0, q = x - tb->a[0];
-        G[0] += wt;
-        if (Q > 1) G[1] += wt * q;
-#pragma unroll
-        for (int l = 1; l + 1 < Q; ++l) {
-          const double qn = (x - tb->a[l]) * q - tb->mb[l] * qm;
-          qm = q; q = qn;
-          G[l + 1] += wt * q;
-        }
-      };
+    // ---- equilibrium populations g_k of this half: with f and chi, each of
+    // the half's two waves takes one slot ----
+    asm volatile("" : "+s"(tp), "+s"(cp));
+    const bool collide = cp->inv_Kn != 0.0;
+    if (collide) {
 #pragma unroll 1
-      for (int j = 0; j < tb->nm; ++j) accum(ub + s * tb->zm[j], tb->wm[j]);
-      const double ymax = wave_max(inside && live ? fabs(y0) : 0.0);
-      if (ymax > 0.0) {
-        const int li = ladder_entry(tb, ymax);
-        const int ncor = tb->lad_n[li], o = tb->lad_off[li];
-        if (ncor > tb->lad_n[kLadder - 1] && lane == 0 && A.wide) atomicAdd(A.wide, 1ull);
-        for (int j = 0; j < ncor; ++j) {
-          const double t = tb->ltau[o + j];
-          const double yt = y0 * t;
-          const double e = y0 * tb->llamw[o + j] * exp(-0.5 * yt * yt);
-          accum(ub * (1.0 - t), -sg * e);
+      for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 ? fn + 1 : SLOTS); ++e) {
+        const double ue = e == 0 ? u[0] : u[1], Te = e == 0 ? T[0] : T[1];
+        double G[Q];
+        if constexpr (QUAD == 0) {
+          // exact change of variables: main rule over [0, inf) and a
+          // correction over [y0, 0] (monic recurrence; the normalisation is
+          // folded into HWs)
+#pragma unroll
+          for (int l = 0; l < Q; ++l) G[l] = 0.0;
+          const double rT = rsqrt_full(Te);
+          const double ub = sg * ue * tp->inv_p0, sc = Te * rT * tp->inv_p0, y0 = -ue * rT;
+          auto accum = [&](double x, double wt) {
+            double qm = 1.0, q = x - tp->a[0];
+            G[0] += wt;
+            if (Q > 1) G[1] = fma(wt, q, G[1]);
+#pragma unroll
+            for (int l = 1; l + 1 < Q; ++l) {
+              const double qn = fma(x - tp->a[l], q, -(tp->mb[l] * qm));
+              qm = q; q = qn;
+              G[l + 1] = fma(wt, q, G[l + 1]);
+            }
+          };
+          const int nm = tp->nm;
+#pragma unroll 2
+          for (int j = 0; j < nm; ++j) accum(fma(sc, tp->zm[j], ub), tp->wm[j]);
+          // correction: the smallest ladder entry that covers the wave's
+          // largest |y0| (the last when none does, also for a non-finite one)
+          const int qp = (e == 0 ? plane[0] : plane[1]) + 2 * pl;   // position
+          const bool cin = (e == 0 ? inside[0] : inside[1]) && qp >= lo && qp <= hi;
+          const float ymax = wave_max_up(cin ? fabs(y0) : 0.0);
+          if (ymax != 0.0f) {
+            const unsigned long long reach =
+                __ballot(lane >= 1 && (lane == kLadderAll - 1 || (lane < kLadderAll && lad >= (double)ymax)));
+            const int li = __ffsll(reach) - 1;
+            const int nc = tp->lad_n[li], o = tp->lad_off[li];
+            const bool wd = nc > tp->lad_n[kLadder - 1];
+            if (wd) ++wide;
+            const bool far = ymax > 1.000001f;
+            const double sy = -sg * y0, hy = -0.5 * y0 * y0;
+            if (!far) {
+#pragma unroll 2
+              for (int j = 0; j < nc; ++j) {
+                const double t = tp->ltau[o + j];
+                accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp_small(hy * (t * t)));
+              }
+            } else {
+#pragma unroll 1
+              for (int j = 0; j < nc; ++j) {
+                const double t = tp->ltau[o + j];
+                accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp(hy * (t * t)));
+              }
+            }
+          }
+        } else {
+          // closed form (Sec. IV.A.3): G_{l+1} = ub G_l + l a G_{l-1}
+          const double aa = fma(Te * tp->inv_p0, tp->inv_p0, -1.0), bb = ue * tp->inv_p0;
+          G[0] = 1.0;
+          if (Q > 1) G[1] = bb;
+#pragma unroll
+          for (int l = 1; l + 1 < Q; ++l) G[l + 1] = fma(bb, G[l], ((double)l * aa) * G[l - 1]);
+        }
+        asm volatile("" : "+s"(tp));
+        double *ge = s_geq + (hw * 2 + e) * H * 64;
+        if constexpr (kMfma) {
+          double aH[H / 4];
+          mfma_operand<H>(tb->HWs, lane, aH);
+#pragma unroll
+          for (int l = 0; l < Q; ++l) ge[l * 64 + lane] = G[l];
+          mfma_tile<H>(aH, ge, lane);
+        } else {
+          const __attribute__((address_space(4))) double *hw_t = QUAD == 0 ? tp->HWs : tp->HW + hw * H * Q;
+#pragma unroll
+          for (int k = 0; k < H; ++k) {
+            double acc = 0.0;
+#pragma unroll
+            for (int l = 0; l < Q; ++l) acc = fma(hw_t[k * Q + l], G[l], acc);
+            ge[k * 64 + lane] = acc;
+          }
         }
       }
     }
+    __syncthreads();
 
-    // pass 1: local source -F (K y)_k - (y_k - y^eq_k)/tau for f and chi
-    double srcf[H], srcc[(NC > 1 && !kMfma) ? H : 1];
-    const double eqc = C.half_Dt * T;
+    // ---- pass 1: b y + b dt (-F (K y)_k - (y_k - y^eq_k)/tau) ----
+    asm volatile("" : "+s"(tp), "+s"(cp));
+    const double bdt = b_s * cp->dt;
+    const double cF = -cp->g * (QUAD == 0 ? sg : 1.0) * bdt;
+    double cT[SLOTS], nT[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      cT[s] = n[s] * cp->inv_Kn * bdt;
+      nT[s] = n[s] * cT[s];
+      if (fn == 1) nT[s] *= cp->half_Dt * T[s];
+    }
+    // matrix cores: the second slot's force block stays in the tile until
+    // pass 2 reads it, which keeps H values out of the register file
+    constexpr int SREG = kMfma ? 1 : SLOTS;
+    double src[H][SREG];
     if constexpr (kMfma) {
-      double *Tw = s_T + hw * 64 * 17;
-      double aK[4], aH[4];
+      double aK[H / 4];
+      mfma_operand<H>(tb->Kin, lane, aK);
 #pragma unroll
-      for (int kc = 0; kc < 4; ++kc) {
-        aK[kc] = tb->Kin[(lane & 15) * H + 4 * kc + (lane >> 4)];
-        aH[kc] = tb->HWs[(lane & 15) * Q + 4 * kc + (lane >> 4)];
-      }
-      double geq[H], ky[H];
-      mfma_contract16(aH, G, geq, Tw, lane);
-      mfma_contract16(aK, yf, ky, Tw, lane);
+      for (int j = 0; j < H; ++j) s_tile[j * 64 + lane] = y[j][0];
+      mfma_tile<H>(aK, s_tile, lane);
 #pragma unroll
-      for (int j = 0; j < H; ++j) {
-        srcf[j] = -gforce * sg * (ky[j] + tb->ka[j] * bf) - (yf[j] - n * geq[j]) * inv_tau;
-        asm volatile("" : "+v"(srcf[j]));
-      }
-      if constexpr (NC > 1) {
-        mfma_contract16_keep(aK, yc, Tw, lane);
+      for (int j = 0; j < H; ++j) src[j][0] = fma(tp->ka[j], bp[0], s_tile[j * 64 + lane]);
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int j = 0; j < H; ++j)
-          Tw[lane * 17 + j] = -gforce * sg * (Tw[lane * 17 + j] + tb->ka[j] * bc) - (yc[j] - eqc * n * geq[j]) * inv_tau;
-      }
-    } else {
-      double geq[H];
+      for (int j = 0; j < H; ++j) s_tile[j * 64 + lane] = y[j][1];
+      mfma_tile<H>(aK, s_tile, lane);
+    } else if constexpr (QUAD == 0) {
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        double acc = 0.0;
-#pragma unroll
-        for (int l = 0; l < Q; ++l) acc += tb->HWs[j * Q + l] * G[l];
-        geq[j] = acc;
-      }
-#pragma unroll
-      for (int j = 0; j < H; ++j) {
-        double kf = 0.0, kcc = 0.0;
+        double k0 = tp->ka[j] * bp[0], k1 = tp->ka[j] * bp[1];
 #pragma unroll
         for (int jj = 0; jj < H; ++jj) {
-          const double kv = tb->Kin[j * H + jj];
-          kf += kv * yf[jj];
-          if constexpr (NC > 1) kcc += kv * yc[jj];
+          k0 = fma(tp->Kin[j * H + jj], y[jj][0], k0);
+          k1 = fma(tp->Kin[j * H + jj], y[jj][1], k1);
         }
-        kf = sg * (kf + tb->ka[j] * bf);
-        const double feq = n * geq[j];
-        srcf[j] = -gforce * kf - (yf[j] - feq) * inv_tau;
-        if constexpr (NC > 1) {
-          kcc = sg * (kcc + tb->ka[j] * bc);
-          srcc[j] = -gforce * kcc - (yc[j] - eqc * feq) * inv_tau;
+        src[j][0] = k0;
+        src[j][1] = k1;
+      }
+    } else {
+      double yo[H][SLOTS];   // the other half
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+          yo[j][s] = s_y[((fn * 2 * H + (1 - hw) * H + j) * 2 + plane[s]) * 64 + pl];
+      const __attribute__((address_space(4))) double *Kr = tp->Kin + hw * H * Q;
+#pragma unroll
+      for (int j = 0; j < H; ++j) {
+        double k0 = 0.0, k1 = 0.0;
+#pragma unroll
+        for (int jj = 0; jj < H; ++jj) {
+          const double ks = Kr[j * Q + hw * H + jj], ko = Kr[j * Q + (1 - hw) * H + jj];
+          k0 = fma(ko, yo[jj][0], fma(ks, y[jj][0], k0));
+          k1 = fma(ko, yo[jj][1], fma(ks, y[jj][1], k1));
         }
+        src[j][0] = k0;
+        src[j][1] = k1;
+      }
+    }
+    if (collide) {
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SREG; ++s) {
+          const double geq = s_geq[((hw * 2 + s) * H + j) * 64 + lane];
+          const double v = fma(nT[s], geq, fma(-cT[s], y[j][s], cF * src[j][s]));
+          src[j][s] = fma(b_s, y[j][s], v);
+        }
+    } else {
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SREG; ++s) src[j][s] = fma(cF, src[j][s], b_s * y[j][s]);
+      if constexpr (kMfma) {   // pass 2 reads the second slot's equilibrium
+#pragma unroll
+        for (int j = 0; j < H; ++j) s_geq[((hw * 2 + 1) * H + j) * 64 + lane] = 0.0;
       }
     }
 
-    // pass 2: advection and the RK-3 combination into the registers; the
-    // face values of node j read only node j's values, so y[j] is replaced
-    // once its flux difference is formed
-    // faces the exact lanes need: lane i forms the face at i+1/2 (hw = 0) or
-    // i-1/2 (hw = 1), and L of lane i also takes its neighbour's
-    const bool face_used = inside && lane >= lo - 1 + hw && lane <= hi + hw;
+    // ---- pass 2: advection (WENO-5 / upwind-3 face fluxes, Sec. IV.C.2) and
+    // the RK-3 combination into the registers; the faces of node j read only
+    // node j's values, so y[j] is replaced once its fluxes are formed ----
+    const int q0 = plane[0] + 2 * pl, q1 = plane[1] + 2 * pl;
+    const bool use0 = inside[0] && q0 >= lo - 1 && q0 <= hi + 1, use1 = inside[1] && q1 >= lo - 1 && q1 <= hi + 1;
+    const bool wf0 = hw ? i[0] == Nx : i[0] == -1, wf1 = hw ? i[1] == Nx : i[1] == -1;
+    const double sdx0 = -dxi[0] * bdt, sdx1 = -dxi[1] * bdt;
+    asm volatile("" : "+s"(tp));
 #pragma unroll
     for (int j = 0; j < H; ++j) {
-      const double v = tb->p[kb0 + j];
-#pragma unroll
-      for (int fn = 0; fn < NC; ++fn) {
-        const double y0v = fn == 0 ? yf[j] : yc[j];
-        double src;
-        if constexpr (kMfma && NC > 1) src = fn == 0 ? srcf[j] : s_T[hw * 64 * 17 + lane * 17 + j];
-        else src = fn == 0 ? srcf[j] : srcc[j];
-        double fv = face_value_lanes<ADV>(y0v, fcoef, face_used);
-        if (wall_face_l) fv = y0v;
-        const double F = v * fv;
-        const double Fo = hw == 0 ? dpp_shr1(F) : dpp_shl1(F);
-        const double L = fma(sdx, F - Fo, src);
-        const double yb = fn == 0 ? nf[j] : nc[j];
-        const double yn = a_s * yb + b_s * (y0v + dt * L);
-        if (fn == 0) yf[j] = yn;
-        else if constexpr (NC > 1) yc[j] = yn;
-        if ((j * NC + fn + 1) % HHLB_SCHED_GROUP == 0) __builtin_amdgcn_sched_barrier(0);
+      const double v = tp->p[j];
+      double fa, fb;
+      faces_down2<ADV>(y[j][0], y[j][1], use0, use1, fa, fb);
+      if (up) {   // the emergent flux at the wall is the wall's own
+        asm volatile("");
+        if (wf0) fa = y[j][0];
+        if (wf1) fb = y[j][1];
       }
+      const double fu = dpp_shr1(fb);
+      y[j][0] = fma(a_s, yn[j][0], fma(sdx0 * v, fa - fu, src[j][0]));
+      double src1;
+      if constexpr (kMfma) {
+        const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
+        const double geq = s_geq[((hw * 2 + 1) * H + j) * 64 + lane];
+        src1 = fma(b_s, y[j][1], fma(nT[1], geq, fma(-cT[1], y[j][1], cF * k1)));
+      } else {
+        src1 = src[j][1];
+      }
+      y[j][1] = fma(a_s, yn[j][1], fma(sdx1 * v, fb - fa, src1));
+      // keep the update here: sunk below the later nodes it would hold their
+      // faces and y^n at once
+      asm volatile("" : "+v"(y[j][0]), "+v"(y[j][1]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kMfma) __syncthreads();   // the next partials overwrite the tiles
+    if (st == 2 && it + 1 < A.nsteps * A.nst) {
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) yn[j][s] = y[j][s];
     }
   }
 
-  // ---- y^{n+1} of the window's output cells ----
-  const bool out_lane = lane >= hl && lane < hl + nout;
+  // ---- the window's output cells ----
+  uint32_t oo[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) oo[s] = i[s] >= win.i0 && i[s] < win.i0 + win.nout ? off[s] : 0xffffffffu;
+  RowWalk w(fn == 0 ? A.out_f : A.out_c, obase);
 #pragma unroll
   for (int j = 0; j < H; ++j) {
-    const int64_t o = obase + (int64_t)j * Nx + ic;
-    if (out_lane) {
-      ((double *)A.out_f)[o] = yf[j];
-      if constexpr (NC > 1) ((double *)A.out_c)[o] = yc[j];
+    const __amdgpu_buffer_rsrc_t r = w.take(stride, wbytes);
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) row_store(r, oo[s], y[j][s]);
+  }
+  if (wide && lane == 0 && A.wide) atomicAdd(A.wide, (unsigned long long)wide);
+}
+
+template <int QUAD, int Q, int NFUN, int ADV>
+__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(step_waves(QUAD == 0 ? Q : Q / 2)))) void
+step_kernel(StageArgs A, const DevTables *__restrict__ tb, const DevChannel *__restrict__ chans,
+            const DevFusedWindow *__restrict__ wins, const double *__restrict__ inv_dx,
+            const double *__restrict__ gw, const double *__restrict__ in_f, const double *__restrict__ in_c) {
+  __shared__ double s_lds[step_lds_doubles<QUAD, Q, NFUN>()];
+  const int w = A.xcd_map ? xcd_window(blockIdx.x, A.nwin) : (int)blockIdx.x;
+  step_window<QUAD, Q, NFUN, ADV>(A, tb, chans, wins[w], inv_dx, gw, in_f, in_c, s_lds);
+}
+
+// One launch for the windows of several half-range model classes that share
+// the functions and the scheme.  Record b names the window and its class; the
+// class's order Q, the same for the whole block, selects the per-order code
+// (orders up to QTOP).  Persistent form: with fewer blocks than windows each
+// block takes windows b, b + gridDim.x, .. in turn.
+template <int QTOP, int NFUN, int ADV, bool PERSIST>
+__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(step_waves(QTOP)))) void
+step_kernel_classes(StageArgs A, const DevTables *__restrict__ tbs, const DevChannel *__restrict__ chans,
+                    const DevFusedClassWindow *__restrict__ wins, const double *__restrict__ inv_dx,
+                    const double *__restrict__ gw, const double *__restrict__ in_f,
+                    const double *__restrict__ in_c) {
+  __shared__ double s_lds[step_lds_doubles<0, QTOP, NFUN>()];
+  for (int b = blockIdx.x; b < A.nwin; b += gridDim.x) {
+    if (PERSIST && b != (int)blockIdx.x) __syncthreads();   // the last window's LDS reads are done
+    const int w = A.xcd_map ? xcd_window(b, A.nwin) : b;
+    const DevFusedClassWindow cw = wins[w];
+    const DevFusedWindow win{cw.ch, cw.i0, cw.c0, cw.nout};
+    const DevTables *tb = tbs + __builtin_amdgcn_readfirstlane(cw.cls);
+    switch (__builtin_amdgcn_readfirstlane(cw.Q)) {
+#define HHLB_CLASS_CASE(q)                                                            \
+  case q:                                                                             \
+    if constexpr (q <= QTOP)                                                          \
+      step_window<0, q, NFUN, ADV>(A, tb, chans, win, inv_dx, gw, in_f, in_c, s_lds); \
+    break;
+      HHLB_CLASS_CASE(1) HHLB_CLASS_CASE(2) HHLB_CLASS_CASE(3) HHLB_CLASS_CASE(4)
+      HHLB_CLASS_CASE(6) HHLB_CLASS_CASE(8) HHLB_CLASS_CASE(12) HHLB_CLASS_CASE(16)
+#undef HHLB_CLASS_CASE
+      default: break;
     }
+    if constexpr (!PERSIST) break;   // one window per block
   }
 }
 

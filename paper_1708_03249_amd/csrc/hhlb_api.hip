@@ -45,7 +45,6 @@ const hhlb::LaunchMap &launchers() {
   static hhlb::LaunchMap m = [] {
     hhlb::LaunchMap t;
     hhlb::register_fp64(t);
-    hhlb::register_fp64_q16(t);
     hhlb::register_mixed_f32(t);
     hhlb::register_mixed_bf16(t);
     hhlb::register_mixed_f16(t);
@@ -255,13 +254,13 @@ struct ModelClass {
   double p0;
   hhlb::Rule rule;
   hhlb::DevTables dev;
-  Launcher launch = nullptr;    // two waves per window
-  Launcher launch4 = nullptr;   // four waves per window (FP64, f and chi), if built
-  Launcher fused = nullptr;     // one launch per RK-3 step (FP64 half range), if built
+  Launcher launch = nullptr;    // mixed forms: one RK stage per launch
+  Launcher step = nullptr;      // FP64, Q <= 16: whole RK-3 steps per launch
   std::vector<hhlb::DevWindow> windows;
   size_t win_off = 0;  // byte offset in workspace
-  std::vector<hhlb::DevFusedWindow> fwindows;   // the fused kernel's windows (9-cell halos)
+  std::vector<hhlb::DevFusedWindow> fwindows;   // the step kernel's windows (9-cell halos)
   size_t fwin_off = 0;
+  bool whole = true;   // every channel fits one window of the step kernel
   // Q > 16 (half-range Hermite, FP64): the node-parallel stage, whose tables
   // (DevLarge, then KinT and HWs) live in their own workspace block
   bool large = false;
@@ -316,7 +315,7 @@ struct hhlb_solver {
     Launcher launch = nullptr;
     int qtop = 0;
     std::vector<size_t> members;
-    std::vector<hhlb::DevClassWindow> wins;
+    std::vector<hhlb::DevFusedClassWindow> wins;
     size_t win_off = 0;
   };
   std::vector<MergeGroup> groups;
@@ -425,36 +424,31 @@ float round_bf16(float x) {
 }
 float round_f16(float x) { return (float)(_Float16)x; }
 
-// Windows of the fused-step kernel for one channel of Nx cells.  A window's
-// edge is a wall whose first two ghosts fit in the 64 lanes, or lies inside
-// the channel with its whole 9-lane halo (lane 63 at a cell).
-//  - Nx <= 58: one window, both walls, three ghosts each (c0 = -3);
-//    Nx = 59, 60: one window with two ghosts per wall (c0 = -2);
-//  - else a left-wall window (c0 = -3, 52 cells on lanes 3..54), interior
-//    windows of 46 cells (c0 = first cell - 9), and a right-wall window
-//    once at most 53 cells remain (cell Nx-1 at lane <= 61).
-//  An interior edge needs at least 55 remaining cells after the window's
-//  first output; a window takes one cell less whenever the remainder would
-//  be exactly 54, which neither kind of window can start from.
-void fused_windows(int ch, int Nx, std::vector<hhlb::DevFusedWindow> &w) {
-  if (Nx <= 60) {
-    w.push_back({ch, 0, Nx <= 58 ? -3 : -2, Nx});
+// Windows of the step kernel for one channel of Nx cells.  A window's edge is
+// a wall whose first two ghosts fit among its 128 positions, or lies 9 cells
+// beyond its outputs inside the channel.  As few windows as hold the channel
+// (one up to 124 cells, two up to 234, 110 more each), of nearly equal
+// length: with two or more windows each writes 62 cells at least, so every
+// halo finds its cells.
+void step_windows(int ch, int Nx, std::vector<hhlb::DevFusedWindow> &w) {
+  using namespace hhlb;
+  if (Nx <= kStepSingle) {
+    w.push_back({ch, 0, -kStepGhosts, Nx});
     return;
   }
+  const int extra = Nx - 2 * kStepWall;
+  int left = 2 + (extra > 0 ? (extra + kStepInner - 1) / kStepInner : 0);
   int o = 0;
   bool first = true;
-  for (;;) {
-    const int R = Nx - o;
-    if (!first && R <= 53) {
-      w.push_back({ch, o, o - 9, R});
-      return;
-    }
-    int m = first ? 52 : 46;
-    if (R - m == 54) --m;
-    w.push_back({ch, o, first ? -3 : o - 9, m});
+  for (; left > 1; --left) {
+    // an equal share, or more where the windows after this one could not hold the rest
+    const int rest = kStepInner * (left - 2) + kStepWall;
+    const int m = std::min(first ? kStepWall : kStepInner, std::max((Nx - o + left - 1) / left, Nx - o - rest));
+    w.push_back({ch, o, first ? -kStepGhosts : o - kStepHalo, m});
     o += m;
     first = false;
   }
+  w.push_back({ch, o, o - kStepHalo, Nx - o});
 }
 
 // Device tables of one model class (quadrature, Q, N, p0).
@@ -492,7 +486,7 @@ void add_composite_entries(T &d, int o, double ytop, long double inv_s2pi) {
 hhlb_status make_tables(const hhlb_channel &h, int N, int precision, const hhlb::Rule &r, hhlb::DevTables &d) {
   std::memset(&d, 0, sizeof(d));
   for (int k = 0; k < r.V; ++k) d.p[k] = r.p[k];
-  for (int k = 0; k < r.H; ++k) { d.z[k] = (double)r.z[k]; d.w[k] = (double)r.w[k]; }
+  for (int k = 0; k < r.H; ++k) { d.z[k] = (double)r.z[k]; d.w[k] = (double)r.w[k]; d.vv[k] = r.p[k] * r.p[k]; }
   for (int l = 0; l < h.Q + 1 && l < (int)r.a.size(); ++l) d.a[l] = (double)r.a[l];
   for (int l = 0; l < h.Q + 2 && l < (int)r.b.size(); ++l) {
     d.sb[l] = (double)sqrtl(r.b[l]);
@@ -858,15 +852,11 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         } else {
           // both half-range kinds run the half-range kernels (tables differ)
           const int kq = hhlb::half_range(h.quad) ? HHLB_HALF_HERMITE : HHLB_FULL_HERMITE;
-          auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, 2});
+          auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, precision == HHLB_FP64 ? 1 : 2});
           if (lk == launchers().end())
             return fail(HHLB_E_UNSUPPORTED, "channel " + std::to_string(c) + ": no kernel for quad=" +
                                                 std::to_string(h.quad) + " Q=" + std::to_string(h.Q));
-          mc.launch = lk->second;
-          auto lk4 = launchers().find({kq, h.Q, nf, h.adv, precision, 4});
-          if (lk4 != launchers().end()) mc.launch4 = lk4->second;
-          auto lkf = launchers().find({kq, h.Q, nf, h.adv, precision, 1});
-          if (lkf != launchers().end() && kq == HHLB_HALF_HERMITE) mc.fused = lkf->second;
+          (precision == HHLB_FP64 ? mc.step : mc.launch) = lk->second;
           st = cached_tables(h, N, precision, mc.rule, mc.dev);
           if (st) return st;
         }
@@ -936,16 +926,20 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       d.inv_1pDt = 1.0 / (1.0 + h.transverse_dof);
       s->dch.push_back(d);
       for (int i0 = 0; i0 < h.Nx; i0 += hhlb::kWin) mc.windows.push_back({c, i0});
-      if (mc.fused) fused_windows(c, h.Nx, mc.fwindows);
+      if (mc.step) {
+        const size_t had = mc.fwindows.size();
+        step_windows(c, h.Nx, mc.fwindows);
+        mc.whole = mc.whole && mc.fwindows.size() == had + 1;
+      }
     }
-    // classes that can share a launch per stage: FP64 half-range classes of
-    // the per-stage window kernels, grouped by functions and scheme
+    // classes that can share a launch: FP64 half-range classes of the step
+    // kernel, grouped by functions and scheme
     s->class_group.assign(s->classes.size(), -1);
     if (precision == HHLB_FP64) {
       std::map<std::pair<int, int>, std::vector<size_t>> by;
       for (size_t ci = 0; ci < s->classes.size(); ++ci) {
         const ModelClass &mc = s->classes[ci];
-        if (!mc.large && hhlb::half_range(mc.quad) && mc.launch) by[{mc.Dt > 0 ? 2 : 1, mc.adv}].push_back(ci);
+        if (mc.step && hhlb::half_range(mc.quad)) by[{mc.Dt > 0 ? 2 : 1, mc.adv}].push_back(ci);
       }
       for (auto &kv : by) {
         if (kv.second.size() < 2) continue;
@@ -960,7 +954,8 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         g.members = kv.second;
         for (size_t ci : kv.second) {
           const ModelClass &mc = s->classes[ci];
-          for (const auto &w : mc.windows) g.wins.push_back({w.ch, w.i0, (int32_t)ci, (int32_t)mc.Q});
+          for (const auto &w : mc.fwindows)
+            g.wins.push_back({w.ch, w.i0, w.c0, w.nout, (int32_t)ci, (int32_t)mc.Q, {0, 0}});
           s->class_group[ci] = (int)s->groups.size();
         }
         s->groups.push_back(std::move(g));
@@ -977,7 +972,7 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       mc.win_off = take(sizeof(hhlb::DevWindow) * mc.windows.size());
       mc.fwin_off = take(sizeof(hhlb::DevFusedWindow) * mc.fwindows.size());
     }
-    for (auto &g : s->groups) g.win_off = take(sizeof(hhlb::DevClassWindow) * g.wins.size());
+    for (auto &g : s->groups) g.win_off = take(sizeof(hhlb::DevFusedClassWindow) * g.wins.size());
     s->o_dx = take(sizeof(double) * s->total_cells);
     s->o_invdx = take(sizeof(double) * s->total_cells);
     s->o_gw = take(sizeof(double) * s->gw.size());
@@ -1044,7 +1039,7 @@ hhlb_status hhlb_bind_workspace(hhlb_solver *s, void *dev_ptr) {
       HIP_TRY(hipMemcpyAsync(ws + mc.lbl_off, mc.lblob.data(), mc.lblob.size(), hipMemcpyHostToDevice, s->stream));
   }
   for (auto &g : s->groups)
-    HIP_TRY(hipMemcpyAsync(ws + g.win_off, g.wins.data(), sizeof(hhlb::DevClassWindow) * g.wins.size(),
+    HIP_TRY(hipMemcpyAsync(ws + g.win_off, g.wins.data(), sizeof(hhlb::DevFusedClassWindow) * g.wins.size(),
                            hipMemcpyHostToDevice, s->stream));
   HIP_TRY(hipMemcpyAsync(ws + s->o_dx, s->dx.data(), sizeof(double) * s->total_cells,
                          hipMemcpyHostToDevice, s->stream));
@@ -1220,21 +1215,20 @@ void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, const void *inf, 
   a.wide = (unsigned long long *)(s->ws + s->o_wide);
   a.lo_in_f = lo_in_f; a.lo_in_c = lo_in_c;
   a.lo_out_f = lo_out_f; a.lo_out_c = lo_out_c;
-  (s->tuning.waves_per_window == 4 && mc.launch4 ? mc.launch4 : mc.launch)(a, stream);
+  mc.launch(a, stream);
 }
 
-// One whole RK-3 step of model class ci in one launch (FP64 half-range
-// classes with a fused-step kernel): y^n from (inf, inc), y^{n+1} to (outf, outc).
-void enqueue_class_fused(hhlb_solver *s, size_t ci, const void *inf, const void *inc, void *outf, void *outc,
-                         hipStream_t stream) {
-  ModelClass &mc = s->classes[ci];
+// nsteps RK-3 steps (nst = 3), or one forward-Euler stage (nsteps = nst = 1),
+// of model class ci in one launch of the step kernel: y^n from (inf, inc), the
+// result to (outf, outc).  nsteps > 1 needs a class whose every channel is one
+// window.  With gi >= 0: of the classes of merge group gi.
+void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, const void *inf, const void *inc,
+                        void *outf, void *outc, hipStream_t stream) {
   hhlb::StageArgs a;
   std::memset(&a, 0, sizeof a);
-  a.tb = (const hhlb::DevTables *)(s->ws + s->o_tables) + ci;
   a.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
-  a.wins = (const hhlb::DevWindow *)(s->ws + mc.fwin_off);   // DevFusedWindow records
-  a.nwin = (int32_t)mc.fwindows.size();
-  a.stage = 2;
+  a.nsteps = nsteps;
+  a.nst = nst;
   a.xcd_map = s->tuning.xcd_map;
   a.inv_dx = (const double *)(s->ws + s->o_invdx);
   a.gw = (const double *)(s->ws + s->o_gw);
@@ -1242,78 +1236,72 @@ void enqueue_class_fused(hhlb_solver *s, size_t ci, const void *inf, const void 
   a.out_f = outf; a.out_c = outc;
   a.nwall = (double *)(s->ws + s->o_nwall);
   a.wide = (unsigned long long *)(s->ws + s->o_wide);
-  mc.fused(a, stream);
+  a.tb = (const hhlb::DevTables *)(s->ws + s->o_tables);
+  if (gi >= 0) {
+    const auto &g = s->groups[gi];
+    a.wins = (const hhlb::DevWindow *)(s->ws + g.win_off);   // DevFusedClassWindow records; the tables by class
+    a.nwin = (int32_t)g.wins.size();
+    a.nblocks = s->tuning.merge_classes == 2 ? -1 : 0;
+    g.launch(a, stream);
+  } else {
+    ModelClass &mc = s->classes[ci];
+    a.tb += ci;
+    a.wins = (const hhlb::DevWindow *)(s->ws + mc.fwin_off);   // DevFusedWindow records
+    a.nwin = (int32_t)mc.fwindows.size();
+    mc.step(a, stream);
+  }
 }
 
-// One RK stage of the classes of merge group gi in one launch (FP64).
-void enqueue_group_stage(hhlb_solver *s, size_t gi, int stage, const void *inf, const void *inc, void *outf,
-                         void *outc, double a_base, double b_stage, hipStream_t stream) {
-  const auto &g = s->groups[gi];
-  hhlb::StageArgs a;
-  std::memset(&a, 0, sizeof a);
-  a.tb = (const hhlb::DevTables *)(s->ws + s->o_tables);   // the classes' tables, indexed by class
-  a.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
-  a.wins = (const hhlb::DevWindow *)(s->ws + g.win_off);    // DevClassWindow records
-  a.nwin = (int32_t)g.wins.size();
-  a.nblocks = s->tuning.merge_classes == 2 ? -1 : 0;
-  a.stage = stage;
-  a.xcd_map = s->tuning.xcd_map;
-  a.inv_dx = (const double *)(s->ws + s->o_invdx);
-  a.gw = (const double *)(s->ws + s->o_gw);
-  a.in_f = inf; a.in_c = inc;
-  a.base_f = s->fA(); a.base_c = s->cA();
-  a.out_f = outf; a.out_c = outc;
-  a.a_base = a_base;
-  a.b_stage = b_stage;
-  a.nwall = (double *)(s->ws + s->o_nwall);
-  a.wide = (unsigned long long *)(s->ws + s->o_wide);
-  g.launch(a, stream);
-}
-
-// One RK-3 step of merge group gi (FP64, the per-stage buffers of
-// enqueue_class_steps) from the solver's current parity (left unchanged).
+// One RK-3 step of merge group gi from the solver's current parity (left
+// unchanged).
 void enqueue_group_step(hhlb_solver *s, size_t gi, hipStream_t stream) {
   const int p = s->par, q = p ^ 1;
-  enqueue_group_stage(s, gi, 0, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
-  enqueue_group_stage(s, gi, 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
-  enqueue_group_stage(s, gi, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
+  enqueue_class_step(s, 0, (int)gi, 1, 3, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], stream);
 }
 
-// One RK stage of every class on one stream.
+// The first RK stage (a forward-Euler stage) of every class on one stream.
 void enqueue_stage(hhlb_solver *s, int stage, const void *inf, const void *inc, void *outf, void *outc,
                    double a_base, double b_stage, hipStream_t stream) {
-  for (size_t ci = 0; ci < s->classes.size(); ++ci)
-    enqueue_class_stage(s, ci, stage, inf, inc, outf, outc, a_base, b_stage, stream);
+  for (size_t ci = 0; ci < s->classes.size(); ++ci) {
+    if (s->classes[ci].step) enqueue_class_step(s, ci, -1, 1, 1, inf, inc, outf, outc, stream);
+    else enqueue_class_stage(s, ci, stage, inf, inc, outf, outc, a_base, b_stage, stream);
+  }
 }
 
 // n_steps RK-3 steps (Eq. rk3) of class ci on one stream, starting from the
 // solver's current state parity (left unchanged).
-//  FP64, y^n in copy p of the pair (A, B), q = 1 - p: stage 1 p -> q,
-//        stage 2 (q, p) -> C, stage 3 (C, p) -> q (y1 in q is dead by then);
-//        or, with step fusion, one launch p -> q.
+//  FP64, Q <= 16, y^n in copy p of the pair (A, B), q = 1 - p: one launch p -> q
+//        per step; channels of one window each keep their state in registers
+//        through up to kStepsPerLaunch steps of a launch.
+//  FP64, Q > 16: stage 1 p -> q, stage 2 (q, p) -> C, stage 3 (C, p) -> q (y1
+//        in q is dead by then).
 //  Mixed: stage 1 hi -> d1 (B), stage 2 (hi, d1) -> d2 (C), stage 3
 //        (hi, lo, d2) -> the other (hi, lo) copy.
 // Every step moves y^n to the other copy: the parity flips.
+constexpr int64_t kStepsPerLaunch = 64;   // about half a millisecond of a small channel
+
 void enqueue_class_steps(hhlb_solver *s, size_t ci, int64_t n_steps, hipStream_t stream) {
   const int par0 = s->par;
-  for (int64_t step = 0; step < n_steps; ++step) {
-    const int p = s->par, q = p ^ 1;
-    if (!s->mixed()) {
-      if (s->tuning.step_fusion && s->classes[ci].fused) {
-        enqueue_class_fused(s, ci, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], stream);
-      } else {
-        enqueue_class_stage(s, ci, 0, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
-        enqueue_class_stage(s, ci, 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
-        enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
-      }
-      s->par = q;
+  const ModelClass &mc = s->classes[ci];
+  for (int64_t step = 0; step < n_steps;) {
+    const int p = s->par;
+    int64_t k = 1;
+    if (mc.step && mc.whole) k = std::min(n_steps - step, kStepsPerLaunch);
+    const int q = p ^ (int)(k & 1);
+    if (mc.step) {
+      enqueue_class_step(s, ci, -1, (int)k, 3, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], stream);
+    } else if (!s->mixed()) {
+      enqueue_class_stage(s, ci, 0, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
+      enqueue_class_stage(s, ci, 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
+      enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
     } else {
       enqueue_class_stage(s, ci, 0, nullptr, nullptr, s->fB, s->cB, 0.0, 1.0, stream);
       enqueue_class_stage(s, ci, 1, s->fB, s->cB, s->fC, s->cC, 0.75, 0.25, stream);
       enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream,
                           s->loF[p], s->loC[p], s->loF[q], s->loC[q]);
-      s->par = q;
     }
+    s->par = q;
+    step += k;
   }
   s->par = par0;
 }
@@ -1328,16 +1316,20 @@ void enqueue_class_steps(hhlb_solver *s, size_t ci, int64_t n_steps, hipStream_t
 hhlb_status enqueue_steps(hhlb_solver *s, int64_t n_steps, hipStream_t stream, bool capturing = false) {
   const size_t nc = s->classes.size();
   if (capturing || !s->tuning.class_streams || nc < 2) {
-    const int par0 = s->par;
     const bool merge = s->tuning.merge_classes != 0;
+    // a single class, or one whose channels are single windows, takes its
+    // steps in a run of its own (classes touch disjoint channels, so nothing
+    // orders them)
+    auto alone = [&](size_t ci) { return nc == 1 || (s->classes[ci].step && s->classes[ci].whole); };
+    for (size_t ci = 0; ci < nc; ++ci)
+      if ((!merge || s->class_group[ci] < 0) && alone(ci)) enqueue_class_steps(s, ci, n_steps, stream);
     for (int64_t step = 0; step < n_steps; ++step) {
       if (merge)
         for (size_t gi = 0; gi < s->groups.size(); ++gi) enqueue_group_step(s, gi, stream);
       for (size_t ci = 0; ci < nc; ++ci)
-        if (!merge || s->class_group[ci] < 0) enqueue_class_steps(s, ci, 1, stream);
+        if ((!merge || s->class_group[ci] < 0) && !alone(ci)) enqueue_class_steps(s, ci, 1, stream);
       s->par ^= 1;
     }
-    (void)par0;
     return HHLB_OK;
   }
   // one stream and one join event per class, created and kept in pairs
@@ -1488,8 +1480,9 @@ extern "C" hhlb_status hhlb_autotune(hhlb_solver *s, int32_t trial_steps, hhlb_t
   const bool multi = s->classes.size() > 1;
   bool has4 = false, hasf = false;
   for (auto &mc : s->classes) {
-    has4 = has4 || mc.launch4 != nullptr;
-    hasf = hasf || mc.fused != nullptr;
+    const bool half = mc.step && hhlb::half_range(mc.quad);
+    has4 = has4 || (half && mc.Dt > 0);
+    hasf = hasf || half;
   }
   std::vector<hhlb_tuning> cands;
   for (int sf : {0, 1})

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void large_cell_kernel(LargeArgs A) {
 // table) and the B operand (the rows of f or chi for the window's 64 cells)
 // load straight from memory in the MFMA layout, and the four partial tiles
 // are summed through LDS.  After that wave w owns nodes kt0 + 4w .. kt0 + 4w
-// + 3, lane = cell i0 - kHalo + lane as in stage_kernel_half.
+// + 3, its lanes the window's cells in the half's wind order.
 #ifndef HHLB_LARGE_WAVES
 #define HHLB_LARGE_WAVES 4   // waves per node-phase block (the rows split over them)
 #endif
@@ -294,7 +294,8 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
   const int hw = ty / gph;                               // 0: p > 0, 1: p < 0
   const int kt0 = (ty % gph) * kTileNodes;               // first node of the tile
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = win.i0 - kHalo + lane;
+  const int pos = hw ? 63 - lane : lane;                 // lanes run down the wind (see weno5_down)
+  const int i = win.i0 - kHalo + pos;
   const bool inside = i >= 0 && i < Nx;
   const int ic = inside ? i : (i < 0 ? 0 : Nx - 1);      // clamped: loads stay in bounds
   const bool nfc = A.nfun > 1;
@@ -364,7 +365,7 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
     for (int q = 0; q < NG; ++q) {
       double v = 0.0;
 #pragma unroll
-      for (int w = 0; w < kNodeWaves; ++w) v += s_red[(w * kTileNodes + wave * NG + q) * S + lane];
+      for (int w = 0; w < kNodeWaves; ++w) v += s_red[(w * kTileNodes + wave * NG + q) * S + pos];
       out[q] = v;
     }
     __syncthreads();
@@ -397,18 +398,16 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
   // from the three nearest cells, emergent nodes n_w g^w_k in all three
   const bool needL = win.i0 < kHalo, needR = win.i0 - kHalo + 63 >= Nx;
   if ((hw == 1 && needL) || (hw == 0 && needR)) {
-    const bool lw = hw == 1;
-    const int l0 = lw ? kHalo : Nx - 1 - (win.i0 - kHalo);
-    const int dl = lw ? 1 : -1;
-    const int gi = lw ? -i : i - Nx + 1;
+    const int l0 = hw == 1 ? 63 - kHalo + win.i0 : Nx - 1 - (win.i0 - kHalo);   // lane of the wall cell
+    const int gi = lane - l0;
     const double c0 = gi == 1 ? 3.0 : (gi == 2 ? 6.0 : 10.0);
     const double c1 = gi == 1 ? -3.0 : (gi == 2 ? -8.0 : -15.0);
     const double c2 = gi == 1 ? 1.0 : (gi == 2 ? 3.0 : 6.0);
     const bool ghost = gi >= 1 && gi <= 3;
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
-      const double y0 = readlane_d(yf[q], l0), y1 = readlane_d(yf[q], l0 + dl), y2 = readlane_d(yf[q], l0 + 2 * dl);
-      const double x0 = readlane_d(yc[q], l0), x1 = readlane_d(yc[q], l0 + dl), x2 = readlane_d(yc[q], l0 + 2 * dl);
+      const double y0 = readlane_d(yf[q], l0), y1 = readlane_d(yf[q], l0 - 1), y2 = readlane_d(yf[q], l0 - 2);
+      const double x0 = readlane_d(yc[q], l0), x1 = readlane_d(yc[q], l0 - 1), x2 = readlane_d(yc[q], l0 - 2);
       if (ghost) {
         yf[q] = c0 * y0 + c1 * y1 + c2 * y2;
         yc[q] = c0 * x0 + c1 * x1 + c2 * x2;
@@ -455,28 +454,25 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
   }
 
   // advection (lane-parallel face values) and the RK-3 combination
-  const FaceCoef fcoef = face_coef(hw);
-  const bool face_used = inside && lane >= kHalo - 1 + hw && lane < kHalo + kWin + hw;
+  const bool face_used = inside && lane >= kHalo - 1 && lane < kHalo + kWin;
   const bool wall_face = hw == 0 ? (i == -1) : (i == Nx);
   const bool out_lane = lane >= kHalo && lane < kHalo + kWin && inside;
   const double dx_inv = A.inv_dx[C.cell_off + ic];
-  const double sdx = hw == 0 ? -dx_inv : dx_inv;
-  const bool need_base = A.a_base != 0.0;
+    const bool need_base = A.a_base != 0.0;
 #pragma unroll
   for (int q = 0; q < NG; ++q) {
     if (q >= ng) break;
     const int k = k0 + q;
-    const double v = A.p[hw * H + k];
+    const double v = A.p[k];
     const int64_t o = rowh + (int64_t)k * Nx + ic;
 #pragma unroll
     for (int fn = 0; fn < 2; ++fn) {
       if (fn == 1 && !nfc) break;
       const double y0v = fn == 0 ? yf[q] : yc[q];
-      double fv = face_value_lanes<ADV>(y0v, fcoef, face_used);
+      double fv = face_value_down<ADV>(y0v, face_used);
       if (wall_face) fv = y0v;
-      const double F = v * fv;
-      const double Fo = hw == 0 ? dpp_shr1(F) : dpp_shl1(F);
-      const double L = fma(sdx, F - Fo, fn == 0 ? srcf[q] : srcc[q]);
+      const double fo = dpp_shr1(fv);
+      const double L = fma(-dx_inv * v, fv - fo, fn == 0 ? srcf[q] : srcc[q]);
       const double base = need_base ? (fn == 0 ? A.base_f : A.base_c)[o] : 0.0;
       const double yn = A.a_base * base + A.b_stage * (y0v + C.dt * L);
       if (out_lane) (fn == 0 ? A.out_f : A.out_c)[o] = yn;

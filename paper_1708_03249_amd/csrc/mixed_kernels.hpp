@@ -118,10 +118,13 @@ __device__ __forceinline__ void add_to_state(float hi, int16_t lo, float delta, 
 struct FaceCoefF {
   float dl, dc, dr, el, gl, ec, er, gr;
 };
+constexpr double kKappa = 0.9607689228305228;         // sqrt(12/13)
+constexpr double kHalfKappa = 0.4803844614152614;     // sqrt(12/13) / 2
 __device__ __forceinline__ FaceCoefF face_coef_f(int hw) {
-  const FaceCoef c = face_coef(hw);
-  return FaceCoefF{(float)c.dl, (float)c.dc, (float)c.dr, (float)c.el, (float)c.gl,
-                   (float)c.ec, (float)c.er, (float)c.gr};
+  constexpr double h = 1.0 / (2.0 * kKappa);   // a = 1/4 in units of E
+  if (hw == 0)
+    return FaceCoefF{0.1f, 0.6f, 0.3f, (float)(3.0 * h), (float)(13.0 / 12.0), (float)h, (float)-h, (float)(1.0 / 12.0)};
+  return FaceCoefF{0.3f, 0.6f, 0.1f, (float)h, (float)(1.0 / 12.0), (float)-h, (float)(-3.0 * h), (float)(13.0 / 12.0)};
 }
 __device__ __forceinline__ float weno5f_lanes(float y, const FaceCoefF &c, bool used) {
   const float ym = dpp_shr1f(y), yp = dpp_shl1f(y);
