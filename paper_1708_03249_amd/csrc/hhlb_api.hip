@@ -1672,6 +1672,7 @@ struct MultiSet {
   int d = 0, V = 0;
   int kdoubles = 0;   // sum of V_a multi_kcols(V_a): the padded K_a tables the kernel stages in LDS
   int nmax = 0;       // the largest equilibrium order of the axes
+  hhlb::MultiShape shape = {};
 };
 
 std::mutex g_multi_mu;
@@ -1749,11 +1750,13 @@ hhlb_status multi_set(const hhlb_axis *axes, int32_t d, std::shared_ptr<const Mu
     std::memcpy(ms->blob.data(), &hdr, sizeof hdr);
     std::memcpy(ms->blob.data() + sizeof hdr, tail.data(), sizeof(double) * tail.size());
     std::memcpy(ms->blob.data() + sizeof hdr + sizeof(double) * tail.size(), idx.data(), sizeof(int32_t) * V);
-    ms->d = d;
-    ms->V = V;
+    ms->d = ms->shape.d = d;
+    ms->V = ms->shape.V = V;
     for (int a = 0; a < d; ++a) {
       ms->kdoubles += hdr.Va[a] * hhlb::multi_kcols(hdr.Va[a]);
       ms->nmax = std::max(ms->nmax, (int)axes[a].N);
+      ms->shape.Va[a] = hdr.Va[a];
+      ms->shape.N[a] = axes[a].N;
     }
     std::lock_guard<std::mutex> lk(g_multi_mu);
     out = g_multi_cache.emplace(key, ms).first->second;
@@ -1774,6 +1777,21 @@ hhlb_status multi_launch_checks(const MultiSet &ms, const void *f, int64_t npts,
     if (!std::isfinite(F[a])) return fail(HHLB_E_ARG, "F must be finite");
   if (work_bytes < need) return fail(HHLB_E_ARG, "workspace too small");
   return HHLB_OK;
+}
+
+// Launch the whole-step kernel if the set has one: the y and z velocities of a
+// point fit the lanes of a wave, V_x has an instance, and the block's LDS stays
+// within 64 KB.  The others run one launch per stage.
+bool multi_whole(const MultiSet &ms, const hhlb::MultiArgs &a, hipStream_t s) {
+  const int P = ms.V / ms.shape.Va[0];
+  if (P > 64) return false;
+  if (a.npts <= 0) return true;
+  size_t lds = 0;   // tables of the lane axes, then the populations
+  for (int k = 1; k < ms.d; ++k) lds += (size_t)ms.shape.Va[k] * ms.shape.Va[k] + (size_t)ms.shape.Va[k] * 21 / 2;
+  lds += (size_t)hhlb::kMultiWaves * 64 * ms.shape.Va[0];
+  if (lds * sizeof(double) > 65536) return false;
+  return ms.nmax <= 3 ? hhlb::launch_multi_n3(a, ms.shape, s)
+                      : (ms.nmax <= 7 ? hhlb::launch_multi_n7(a, ms.shape, s) : hhlb::launch_multi_n20(a, ms.shape, s));
 }
 
 hhlb::MultiArgs multi_args(const MultiSet &ms, void *work, int64_t npts, const double *F, double Kn) {
@@ -1877,7 +1895,7 @@ hhlb_status hhlb_multi_rhs(const hhlb_axis *axes, int32_t d, const double *f_dev
   a.in = f_dev;
   a.out = L_dev;
   a.rhs_only = 1;
-  hhlb::launch_multi(a, s, ms->V, ms->kdoubles, ms->nmax);
+  if (!multi_whole(*ms, a, s)) hhlb::launch_multi(a, s, ms->V, ms->kdoubles, ms->nmax);
   HIP_TRY(hipGetLastError());
   return HHLB_OK;
 }
@@ -1927,7 +1945,14 @@ hhlb_status multi_steps(const MultiSet &msr, double *f_dev, int64_t npts, const 
   double *y1 = (double *)((char *)work_dev + tb), *y2 = (double *)((char *)work_dev + tb + sb);
   hhlb::MultiArgs a = multi_args(*ms, work_dev, npts, F, Kn);
   a.dt = dt;
-  for (int k = 0; k < n_steps; ++k) {
+  constexpr int kStepsPerLaunch = 64;   // bounds a launch's time (about 0.1 s for 1e6 points of 128 velocities)
+  a.in = f_dev; a.out = f_dev;
+  int done = 0;
+  for (; done < n_steps; done += a.nsteps) {
+    a.nsteps = std::min(n_steps - done, kStepsPerLaunch);
+    if (!multi_whole(*ms, a, s)) break;
+  }
+  for (int k = done; k < n_steps; ++k) {
     // Eq. (rk3): y1 = y + dt L[y]; y2 = 3/4 y + 1/4 (y1 + dt L[y1]);
     // y+ = 1/3 y + 2/3 (y2 + dt L[y2])
     a.in = f_dev; a.base = nullptr; a.out = y1; a.a_base = 0.0; a.b_stage = 1.0;

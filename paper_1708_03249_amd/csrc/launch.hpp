@@ -30,6 +30,12 @@ void launch_large(const LargeArgs &a, int adv, int H, hipStream_t s);
 
 // The mixed-quadrature (App. A) velocity-space stage: kernels_multi.hip.
 struct MultiArgs;
+struct MultiShape;
+// Whole-step kernels by the largest equilibrium order of the axes: false if
+// there is no instance for the set's V_x.
+bool launch_multi_n3(const MultiArgs &a, const MultiShape &m, hipStream_t s);
+bool launch_multi_n7(const MultiArgs &a, const MultiShape &m, hipStream_t s);
+bool launch_multi_n20(const MultiArgs &a, const MultiShape &m, hipStream_t s);
 void launch_multi(const MultiArgs &a, hipStream_t s, int V, int k_doubles, int n_max);
 
 }  // namespace hhlb

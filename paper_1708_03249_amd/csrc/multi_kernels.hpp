@@ -66,6 +66,13 @@ struct MultiArgs {
   double F[kMultiAxes];            // acceleration (m = 1)
   double inv_Kn, dt, a_base, b_stage;
   int32_t rhs_only;                // 1: out = L[in]
+  int32_t nsteps;                  // whole-step kernel: steps of the launch (in: y^n, out: y^{n + nsteps})
+};
+
+// What the host needs of a product set to choose and launch a kernel.
+struct MultiShape {
+  int d, V;
+  int Va[kMultiAxes], N[kMultiAxes];
 };
 
 }  // namespace hhlb
