@@ -149,19 +149,24 @@ __device__ __forceinline__ double row_sum16(double x) {
   return readlane_d(x, 15);
 }
 
-// Largest of the wave's non-negative values, rounded up to FP32.
+// Largest of the wave's non-negative values, rounded up to FP32 (compared as
+// integers: the bits of non-negative floats order like them).
 __device__ __forceinline__ float wave_max_up(double x) {
-  float m = (float)x * 1.0000002f;
-#define HHLB_ROW_MAX(ctrl, rows)                                                                          \
-  m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), ctrl, rows, 0xf, false)))
-  HHLB_ROW_MAX(0x111, 0xf);
-  HHLB_ROW_MAX(0x112, 0xf);
-  HHLB_ROW_MAX(0x114, 0xf);
-  HHLB_ROW_MAX(0x118, 0xf);
-  HHLB_ROW_MAX(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
-  HHLB_ROW_MAX(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+  const float up = (float)x * 1.0000002f;
+  unsigned m = up > 0.0f ? __float_as_uint(up) : 0u;   // NaN counts as zero
+#define HHLB_ROW_MAX(ctrl, rows)                                                                  \
+  {                                                                                               \
+    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, ctrl, rows, 0xf, false);  \
+    m = o > m ? o : m;                                                                            \
+  }
+  HHLB_ROW_MAX(0x111, 0xf)
+  HHLB_ROW_MAX(0x112, 0xf)
+  HHLB_ROW_MAX(0x114, 0xf)
+  HHLB_ROW_MAX(0x118, 0xf)
+  HHLB_ROW_MAX(0x142, 0xa)   // row_bcast:15 into rows 1 and 3
+  HHLB_ROW_MAX(0x143, 0xc)   // row_bcast:31 into rows 2 and 3
 #undef HHLB_ROW_MAX
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 63));
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)m, 63));
 }
 
 // WENO-5 values at the downwind faces of a lane's two cells (wind positions

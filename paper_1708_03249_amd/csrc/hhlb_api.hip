@@ -1786,10 +1786,6 @@ bool multi_whole(const MultiSet &ms, const hhlb::MultiArgs &a, hipStream_t s) {
   const int P = ms.V / ms.shape.Va[0];
   if (P > 64) return false;
   if (a.npts <= 0) return true;
-  size_t lds = 0;   // tables of the lane axes, then the populations
-  for (int k = 1; k < ms.d; ++k) lds += (size_t)ms.shape.Va[k] * ms.shape.Va[k] + (size_t)ms.shape.Va[k] * 21 / 2;
-  lds += (size_t)hhlb::kMultiWaves * 64 * ms.shape.Va[0];
-  if (lds * sizeof(double) > 65536) return false;
   return ms.nmax <= 3 ? hhlb::launch_multi_n3(a, ms.shape, s)
                       : (ms.nmax <= 7 ? hhlb::launch_multi_n7(a, ms.shape, s) : hhlb::launch_multi_n20(a, ms.shape, s));
 }

@@ -54,13 +54,14 @@ __device__ __forceinline__ double group_sum(double x, int P) {
 }
 
 // Equilibrium coefficients G_l, l <= NM, of the half sg of a half-range axis
-// at (u, T): the quadrature points q0, q0 + dq, .. of the main rule and of the
-// correction (Sec. IV.B.3 by the change of variables of the step kernel), the
-// correction's point count one for the wave (the smallest that covers its
-// largest |y0|).  `lad` is lane j's reach of entry j.
-template <int NM>
-__device__ __forceinline__ void half_coeffs(ConstLarge tl, double sg, double u, double T, double lad, int lane, int q0,
-                                            int dq, double (&G)[NM + 1]) {
+// at (u, T): the main rule and the correction (Sec. IV.B.3 by the change of
+// variables of the step kernel), the correction's point count one for the wave
+// (the smallest that covers its largest |y0|).  SPLIT: the lane takes the even
+// (second = false) or the odd quadrature points only.  `lad` is lane j's reach
+// of entry j.
+template <int NM, bool SPLIT>
+__device__ __forceinline__ void half_coeffs(ConstLarge tl, double sg, double u, double T, double lad, int lane,
+                                            bool second, double (&G)[NM + 1]) {
 #pragma unroll
   for (int l = 0; l <= NM; ++l) G[l] = 0.0;
   const double rT = rsqrt_full(T), ub = sg * u * tl->inv_p0, sc = T * rT * tl->inv_p0, y0 = -u * rT;
@@ -75,34 +76,45 @@ __device__ __forceinline__ void half_coeffs(ConstLarge tl, double sg, double u, 
       G[l + 1] = fma(wt, q, G[l + 1]);
     }
   };
+  // point j of a rule of cnt points, or with SPLIT the lane's of j and j + 1
+  // (weight zero past the end)
+  auto point = [&](ConstDoubles x, ConstDoubles w, int j, int cnt, double &xj, double &wj) {
+    if constexpr (SPLIT) {
+      const bool more = j + 1 < cnt;
+      const int j1 = more ? j + 1 : j;
+      const double x0 = x[j], x1 = x[j1], w0 = w[j], w1 = w[j1];
+      xj = second ? x1 : x0;
+      wj = second ? (more ? w1 : 0.0) : w0;
+    } else {
+      xj = x[j];
+      wj = w[j];
+    }
+  };
+  constexpr int dq = SPLIT ? 2 : 1;
   const float ymax = wave_max_up(fabs(y0));
   const unsigned long long reach =
       __ballot(lane >= 1 && (lane == kLadderAll - 1 || (lane < kLadderAll && lad >= (double)ymax)));
   const int li = __ffsll(reach) - 1;
   const int nm = tl->nm, nc = ymax != 0.0f ? tl->lad_n[li] : 0, o = tl->lad_off[li];
-  // the loops are uniform; a lane without a point of its own adds weight zero
-  // (its table entries are those of a point another lane has)
+  double xj, wj;
+#pragma unroll 1
   for (int j = 0; j < nm; j += dq) {
-    double z = tl->zm[j], w = tl->wm[j];
-    if (dq > 1) {
-      const bool hi = q0 != 0;
-      z = hi && j + 1 < nm ? tl->zm[j + 1 < nm ? j + 1 : j] : z;
-      w = hi ? (j + 1 < nm ? tl->wm[j + 1 < nm ? j + 1 : j] : 0.0) : w;
-    }
-    accum(fma(sc, z, ub), w);
+    point(tl->zm, tl->wm, j, nm, xj, wj);
+    accum(fma(sc, xj, ub), wj);
   }
   const double sy = -sg * y0, hy = -0.5 * y0 * y0;
-  const bool far = ymax > 1.000001f;
-  for (int j = 0; j < nc; j += dq) {
-    double t = tl->ltau[o + j], w = tl->llamw[o + j];
-    if (dq > 1) {
-      const bool hi = q0 != 0;
-      const int j1 = j + 1 < nc ? j + 1 : j;
-      t = hi ? tl->ltau[o + j1] : t;
-      w = hi ? (j + 1 < nc ? tl->llamw[o + j1] : 0.0) : w;
+  if (!(ymax > 1.000001f)) {
+#pragma unroll 1
+    for (int j = 0; j < nc; j += dq) {
+      point(tl->ltau + o, tl->llamw + o, j, nc, xj, wj);
+      accum(fma(-ub, xj, ub), sy * wj * exp_small(hy * (xj * xj)));
     }
-    const double a = hy * (t * t), ex = far ? exp(a) : exp_small(a);
-    accum(fma(-ub, t, ub), sy * w * ex);
+  } else {
+#pragma unroll 1
+    for (int j = 0; j < nc; j += dq) {
+      point(tl->ltau + o, tl->llamw + o, j, nc, xj, wj);
+      accum(fma(-ub, xj, ub), sy * wj * exp(hy * (xj * xj)));
+    }
   }
 }
 // Full range: G_l / sqrt(l!) by the closed-form recurrence (Sec. IV.A.3); the
@@ -116,10 +128,14 @@ __device__ __forceinline__ void full_coeffs(ConstLarge tl, double sg, double u, 
   for (int l = 1; l < NM; ++l) G[l + 1] = fma(ub, G[l], tl->sq[l] * (aa * G[l - 1])) * kInvSqrt[l + 1];
 }
 
+#ifndef HHLB_MULTI_STEPS_OCC
+#define HHLB_MULTI_STEPS_OCC 3
+#endif
 template <int NX, int NM, bool QZ>
-__global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs A) {
+__global__ __launch_bounds__(64 * kMultiWaves)
+__attribute__((amdgpu_waves_per_eu(NX <= 8 && NM <= 7 ? HHLB_MULTI_STEPS_OCC : 1))) void multi_steps_kernel(MultiArgs A) {
   extern __shared__ double s_mem[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6, lane0 = threadIdx.x & 63;
   ConstMulti tm = (ConstMulti)A.tm;
   ConstDoubles tab = (ConstDoubles)A.tab;
   constexpr int H0 = NX / 2;
@@ -129,42 +145,48 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
   const bool pow2 = (P & (P - 1)) == 0;
   // the lane's point and its y and z velocity; lanes past the last whole
   // point of the wave repeat the first one's and store nothing
-  int seg = lane / P;
-  const int sub = lane - seg * P;
-  const bool spare = seg >= ppw;
-  if (spare) seg = 0;
-  const int j = d == 3 ? sub / Vz : 0, k = sub - j * Vz;
-  const int64_t pt0 = ((int64_t)blockIdx.x * kMultiWaves + wave) * ppw + seg;
+  int seg0 = lane0 / P;
+  const int sub = lane0 - seg0 * P;
+  const bool spare = seg0 >= ppw;
+  if (spare) seg0 = 0;
+  const int j0 = d == 3 ? sub / Vz : 0, k0 = sub - j0 * Vz;
+  const int64_t pt0 = ((int64_t)blockIdx.x * kMultiWaves + wave) * ppw + seg0;
   const bool valid = !spare && pt0 < A.npts;
   const int64_t pt = pt0 < A.npts ? pt0 : A.npts - 1;
 
   // block tables: F_a K_a of the lane axes, their equilibrium tables
-  double *s_Ky = s_mem, *s_Kz = s_Ky + Vy * Vy, *s_hy = s_Kz + Vz * Vz;
-  const int Ny = d == 3 ? tm->ax[1].N : 0, Nz = tm->ax[az].N;
-  double *s_hz = s_hy + (d == 3 ? (Vy / 2) * (Ny + 1) : 0);
-  double *s_f = s_hz + (Vz / 2) * (Nz + 1) + wave * NX * 64;
+  constexpr int NG = NM + 1;   // row of the equilibrium tables, zero beyond the axis' order
+  double *s_Ky = s_mem, *s_Kz = s_Ky + Vy * Vy, *s_hx = s_Kz + Vz * Vz, *s_hy = s_hx + H0 * NG;
+  double *s_hz = s_hy + (Vy / 2) * NG;
+  double *s_f = s_hz + (Vz / 2) * NG + wave * NX * 64;
   {
     const double Fy = d == 3 ? A.F[1] : 0.0, Fz = d == 3 ? A.F[2] : A.F[1];
+    auto stage_rows = [&](double *to, int a, int rows) {
+      const int N = tm->ax[a].N, from = tm->hw_off[a];
+      for (int t = threadIdx.x; t < rows * NG; t += 64 * kMultiWaves) {
+        const int r = t / NG, l = t - r * NG;
+        to[t] = l <= N ? A.tab[from + r * (N + 1) + (l <= N ? l : 0)] : 0.0;
+      }
+    };
     if (d == 3) {
       for (int t = threadIdx.x; t < Vy * Vy; t += 64 * kMultiWaves) s_Ky[t] = Fy * A.tab[tm->k_off[1] + t];
-      for (int t = threadIdx.x; t < (Vy / 2) * (Ny + 1); t += 64 * kMultiWaves) s_hy[t] = A.tab[tm->hw_off[1] + t];
+      stage_rows(s_hy, 1, Vy / 2);
     }
     for (int t = threadIdx.x; t < Vz * Vz; t += 64 * kMultiWaves) s_Kz[t] = Fz * A.tab[tm->k_off[az] + t];
-    for (int t = threadIdx.x; t < (Vz / 2) * (Nz + 1); t += 64 * kMultiWaves) s_hz[t] = A.tab[tm->hw_off[az] + t];
+    stage_rows(s_hz, az, Vz / 2);
+    stage_rows(s_hx, 0, H0);
   }
   __syncthreads();
-  const double py = d == 3 ? A.tab[tm->p_off[1] + j] : 0.0, pz = A.tab[tm->p_off[az] + k];
+  const double py = d == 3 ? A.tab[tm->p_off[1] + j0] : 0.0, pz = A.tab[tm->p_off[az] + k0];
   double kq[4];   // z matrix entries of the quad's lanes
   if constexpr (QZ) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) kq[m] = s_Kz[k * 4 + (k ^ m)];
+    for (int m = 0; m < 4; ++m) kq[m] = s_Kz[k0 * 4 + (k0 ^ m)];
   }
-  const int ll = lane < kLadderAll ? lane : kLadderAll - 1;
+  const int ll = lane0 < kLadderAll ? lane0 : kLadderAll - 1;
   const bool fx = tm->ax[0].full != 0, fy = d == 3 && tm->ax[1].full != 0, fz = tm->ax[az].full != 0;
   const double ladx = A.tm->ax[0].lad_y[ll], lady = A.tm->ax[1].lad_y[ll], ladz = A.tm->ax[az].lad_y[ll];
   const bool collide = A.inv_Kn != 0.0;
-  const double sgy = j < Vy / 2 || d == 2 ? 1.0 : -1.0, sgz = k < Vz / 2 ? 1.0 : -1.0;
-  const int hy = d == 3 ? (j < Vy / 2 ? j : j - Vy / 2) : 0, hz = k < Vz / 2 ? k : k - Vz / 2;
 
   double f[NX], fn[NX];
   const double *src = A.in + pt * V + sub;
@@ -177,6 +199,12 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
     const int st = it % 3;
     const double a_s = st == 0 ? 0.0 : (st == 1 ? 0.75 : 1.0 / 3.0);
     const double b_s = st == 0 ? 1.0 : (st == 1 ? 0.25 : 2.0 / 3.0);
+    // addresses and lane selections are formed anew in each stage: kept
+    // through the stages they would take the registers of the state
+    int lane = lane0, seg = seg0, j = j0, k = k0;
+    asm volatile("" : "+v"(lane), "+v"(seg), "+v"(j), "+v"(k));
+    const double sgy = j < Vy / 2 || d == 2 ? 1.0 : -1.0, sgz = k < Vz / 2 ? 1.0 : -1.0;
+    const int hy = d == 3 ? (j < Vy / 2 ? j : j - Vy / 2) : 0, hz = k < Vz / 2 ? k : k - Vz / 2;
     asm volatile("" : "+s"(tm), "+s"(tab));
     // ---- moments: n, u, then T from the spread about u ----
     ConstDoubles px = tab + tm->p_off[0];
@@ -273,27 +301,25 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
       const double rate = n * A.inv_Kn;
       double gyz = n * rate;
       {
-        double G[NM + 1];
+        double G[NG];
         if (d == 3) {
           if (fy) full_coeffs<NM>(&tm->ax[1], sgy, uy, T, G);
-          else half_coeffs<NM>(&tm->ax[1], sgy, uy, T, lady, lane, 0, 1, G);
+          else half_coeffs<NM, false>(&tm->ax[1], sgy, uy, T, lady, lane, false, G);
           double g = 0.0;
 #pragma unroll
-          for (int l = 0; l <= NM; ++l)
-            if (l <= Ny) g = fma(s_hy[hy * (Ny + 1) + l], G[l], g);
+          for (int l = 0; l <= NM; ++l) g = fma(s_hy[hy * NG + l], G[l], g);
           gyz *= g;
         }
         if (fz) full_coeffs<NM>(&tm->ax[az], sgz, uz, T, G);
-        else half_coeffs<NM>(&tm->ax[az], sgz, uz, T, ladz, lane, 0, 1, G);
+        else half_coeffs<NM, false>(&tm->ax[az], sgz, uz, T, ladz, lane, false, G);
         double g = 0.0;
 #pragma unroll
-        for (int l = 0; l <= NM; ++l)
-          if (l <= Nz) g = fma(s_hz[hz * (Nz + 1) + l], G[l], g);
+        for (int l = 0; l <= NM; ++l) g = fma(s_hz[hz * NG + l], G[l], g);
         gyz *= g;
       }
       // x: even lanes take the half p > 0, odd ones p < 0; in whole quads the
       // two pairs take every other quadrature point
-      double Gp[NM + 1], Gm[NM + 1];
+      double Gp[NG], Gm[NG];
       asm volatile("" : "+s"(tm), "+s"(tab));
       if (fx) {
         full_coeffs<NM>(&tm->ax[0], 1.0, ux, T, Gp);
@@ -301,13 +327,13 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
         for (int l = 0; l <= NM; ++l) Gm[l] = l & 1 ? -Gp[l] : Gp[l];
       } else {
         const double sx = lane & 1 ? -1.0 : 1.0;
-        double G[NM + 1];
+        double G[NG];
         if (P % 4 == 0) {
-          half_coeffs<NM>(&tm->ax[0], sx, ux, T, ladx, lane, (lane >> 1) & 1, 2, G);
+          half_coeffs<NM, true>(&tm->ax[0], sx, ux, T, ladx, lane, (lane & 2) != 0, G);
 #pragma unroll
           for (int l = 0; l <= NM; ++l) G[l] += dpp_d<kQuadXor2>(G[l]);
         } else {
-          half_coeffs<NM>(&tm->ax[0], sx, ux, T, ladx, lane, 0, 1, G);
+          half_coeffs<NM, false>(&tm->ax[0], sx, ux, T, ladx, lane, false, G);
         }
 #pragma unroll
         for (int l = 0; l <= NM; ++l) {
@@ -315,18 +341,15 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
           Gm[l] = dpp_d<kQuadOdd>(G[l]);
         }
       }
-      const int N0 = tm->ax[0].N;
-      ConstDoubles hx = tab + tm->hw_off[0];
 #pragma unroll
       for (int x = 0; x < H0; ++x) {
         double gp = 0.0, gm = 0.0;
 #pragma unroll
-        for (int l = 0; l <= NM; ++l)
-          if (l <= N0) {
-            const double h = hx[x * (N0 + 1) + l];
-            gp = fma(h, Gp[l], gp);
-            gm = fma(h, Gm[l], gm);
-          }
+        for (int l = 0; l <= NM; ++l) {
+          const double h = s_hx[x * NG + l];
+          gp = fma(h, Gp[l], gp);
+          gm = fma(h, Gm[l], gm);
+        }
         acc[x] = fma(gyz, gp, -fma(rate, f[x], acc[x]));
         acc[H0 + x] = fma(gyz, gm, -fma(rate, f[H0 + x], acc[H0 + x]));
       }
@@ -356,10 +379,10 @@ __global__ __launch_bounds__(64 * kMultiWaves) void multi_steps_kernel(MultiArgs
 }
 
 // Dynamic LDS of a block (doubles).
-inline size_t multi_steps_lds(const MultiShape &m) {
-  const int z = m.d - 1, Vy = m.d == 3 ? m.Va[1] : 1;
-  return (size_t)Vy * Vy + (size_t)m.Va[z] * m.Va[z] + (m.d == 3 ? (Vy / 2) * (m.N[1] + 1) : 0) +
-         (size_t)(m.Va[z] / 2) * (m.N[z] + 1) + (size_t)kMultiWaves * m.Va[0] * 64;
+inline size_t multi_steps_lds(const MultiShape &m, int NM) {
+  const int Vz = m.Va[m.d - 1], Vy = m.d == 3 ? m.Va[1] : 1;
+  return (size_t)Vy * Vy + (size_t)Vz * Vz + (size_t)(m.Va[0] / 2 + Vy / 2 + Vz / 2) * (NM + 1) +
+         (size_t)kMultiWaves * m.Va[0] * 64;
 }
 
 template <int NX, int NM>
@@ -367,14 +390,15 @@ void launch_multi_nx(const MultiArgs &a, const MultiShape &m, hipStream_t s) {
   const int P = (m.d == 3 ? m.Va[1] : 1) * m.Va[m.d - 1];
   const int64_t per_block = (int64_t)(64 / P) * kMultiWaves;
   const dim3 grid((unsigned)((a.npts + per_block - 1) / per_block));
-  const size_t shm = sizeof(double) * multi_steps_lds(m);
+  const size_t shm = sizeof(double) * multi_steps_lds(m, NM);
   if (m.Va[m.d - 1] == 4) hipLaunchKernelGGL((multi_steps_kernel<NX, NM, true>), grid, dim3(64 * kMultiWaves), shm, s, a);
   else hipLaunchKernelGGL((multi_steps_kernel<NX, NM, false>), grid, dim3(64 * kMultiWaves), shm, s, a);
 }
 
-// Runs it if there is an instance for the set's V_x.
+// Runs it if there is an instance for the set's V_x whose LDS fits.
 template <int NM>
 bool launch_multi_nm(const MultiArgs &a, const MultiShape &m, hipStream_t s) {
+  if (sizeof(double) * multi_steps_lds(m, NM) > 65536) return false;
   switch (m.Va[0]) {
     case 4: launch_multi_nx<4, NM>(a, m, s); return true;
     case 6: launch_multi_nx<6, NM>(a, m, s); return true;
