@@ -179,13 +179,13 @@ hhlb_status hhlb_step(hhlb_solver *s, int64_t n_steps);
  *  xcd_map:       1 = consecutive windows of a channel go to the same XCD
  *                 (the hardware deals blocks round-robin over the 8 XCDs);
  *                 0 = block b handles window b.
- *  waves_per_window, step_fusion: kept for callers that set them.  FP64
- *                 classes with Q <= 16 run whole steps (Eq. rk3) per launch
- *                 whatever the value -- windows of 128 cells with 9-cell
- *                 halos, one wave per momentum half and function, y^n and the
- *                 stage state in registers; classes whose channels fit one
- *                 window each (Nx <= 124) up to 64 steps per launch -- and the
- *                 other classes one launch per stage.
+ *  waves_per_window, step_fusion: kept for callers that set them.  Classes
+ *                 with Q <= 16 run whole steps (Eq. rk3) per launch whatever
+ *                 the value -- windows of 128 cells with 9-cell halos, one
+ *                 wave per momentum half and function, y^n and the stage state
+ *                 in registers; classes whose channels fit one window each
+ *                 (Nx <= 124) up to 64 steps per launch -- and larger ones
+ *                 launch their stages.
  *  merge_classes: 0 = launches of their own for each model class; 1 = one
  *                 launch per step for all FP64 half-range classes that share
  *                 the functions (f, or f and chi) and the scheme, each block

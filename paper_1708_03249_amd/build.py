@@ -35,7 +35,8 @@ SOURCES = ("tables.cpp", "hhlb_api.hip", "kernels_fp64.hip", "kernels_mixed_f32.
 # register file holding the state, and constants moved ahead of that loop
 # would only spill (Q = 8: 47 registers spilled instead of 99)
 SOURCE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"] for f in (
-    "kernels_fp64.hip", "kernels_classes.hip", "kernels_multi_n3.hip", "kernels_multi_n7.hip", "kernels_multi_n20.hip")}
+    "kernels_fp64.hip", "kernels_classes.hip", "kernels_mixed_f32.hip", "kernels_mixed_bf16.hip", "kernels_mixed_f16.hip",
+    "kernels_multi_n3.hip", "kernels_multi_n7.hip", "kernels_multi_n20.hip")}
 
 
 def build(verbose: bool = True, out: str | None = None, defines=()) -> str:

@@ -169,6 +169,58 @@ __device__ __forceinline__ float wave_max_up(double x) {
   return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)m, 63));
 }
 
+// Equilibrium coefficients G_l (l < Q) of one half at a lane's (u, T) by the
+// exact change of variables (Sec. IV.B.3): main rule over [0, inf) and a
+// correction over [y0, 0] (monic recurrence; the normalisation is folded into
+// the table the coefficients meet).  sg is the half's sign, lad the reach of
+// ladder entry `lane`, `used` marks the lanes whose result counts; an
+// evaluation beyond the calibrated ladder is counted in `wide`.
+template <int Q>
+__device__ __forceinline__ void half_range_coeffs(ConstTables tp, double ue, double Te, double sg, int lane, double lad,
+                                                  bool used, int &wide, double (&G)[Q]) {
+#pragma unroll
+  for (int l = 0; l < Q; ++l) G[l] = 0.0;
+  const double rT = rsqrt_full(Te);
+  const double ub = sg * ue * tp->inv_p0, sc = Te * rT * tp->inv_p0, y0 = -ue * rT;
+  auto accum = [&](double x, double wt) {
+    double qm = 1.0, q = x - tp->a[0];
+    G[0] += wt;
+    if (Q > 1) G[1] = fma(wt, q, G[1]);
+#pragma unroll
+    for (int l = 1; l + 1 < Q; ++l) {
+      const double qn = fma(x - tp->a[l], q, -(tp->mb[l] * qm));
+      qm = q; q = qn;
+      G[l + 1] = fma(wt, q, G[l + 1]);
+    }
+  };
+  const int nm = tp->nm;
+#pragma unroll 2
+  for (int j = 0; j < nm; ++j) accum(fma(sc, tp->zm[j], ub), tp->wm[j]);
+  // correction: the smallest ladder entry that covers the wave's
+  // largest |y0| (the last when none does, also for a non-finite one)
+  const float ymax = wave_max_up(used ? fabs(y0) : 0.0);
+  if (ymax == 0.0f) return;
+  const unsigned long long reach =
+      __ballot(lane >= 1 && (lane == kLadderAll - 1 || (lane < kLadderAll && lad >= (double)ymax)));
+  const int li = __ffsll(reach) - 1;
+  const int nc = tp->lad_n[li], o = tp->lad_off[li];
+  if (nc > tp->lad_n[kLadder - 1]) ++wide;
+  const double sy = -sg * y0, hy = -0.5 * y0 * y0;
+  if (ymax <= 1.000001f) {
+#pragma unroll 2
+    for (int j = 0; j < nc; ++j) {
+      const double t = tp->ltau[o + j];
+      accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp_small(hy * (t * t)));
+    }
+  } else {
+#pragma unroll 1
+    for (int j = 0; j < nc; ++j) {
+      const double t = tp->ltau[o + j];
+      accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp(hy * (t * t)));
+    }
+  }
+}
+
 // WENO-5 values at the downwind faces of a lane's two cells (wind positions
 // 2 l and 2 l + 1): weno5_down with the differences the two faces share
 // formed once, and one branch for the rare rescaling of either.
@@ -430,55 +482,9 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
         const double ue = e == 0 ? u[0] : u[1], Te = e == 0 ? T[0] : T[1];
         double G[Q];
         if constexpr (QUAD == 0) {
-          // exact change of variables: main rule over [0, inf) and a
-          // correction over [y0, 0] (monic recurrence; the normalisation is
-          // folded into HWs)
-#pragma unroll
-          for (int l = 0; l < Q; ++l) G[l] = 0.0;
-          const double rT = rsqrt_full(Te);
-          const double ub = sg * ue * tp->inv_p0, sc = Te * rT * tp->inv_p0, y0 = -ue * rT;
-          auto accum = [&](double x, double wt) {
-            double qm = 1.0, q = x - tp->a[0];
-            G[0] += wt;
-            if (Q > 1) G[1] = fma(wt, q, G[1]);
-#pragma unroll
-            for (int l = 1; l + 1 < Q; ++l) {
-              const double qn = fma(x - tp->a[l], q, -(tp->mb[l] * qm));
-              qm = q; q = qn;
-              G[l + 1] = fma(wt, q, G[l + 1]);
-            }
-          };
-          const int nm = tp->nm;
-#pragma unroll 2
-          for (int j = 0; j < nm; ++j) accum(fma(sc, tp->zm[j], ub), tp->wm[j]);
-          // correction: the smallest ladder entry that covers the wave's
-          // largest |y0| (the last when none does, also for a non-finite one)
           const int qp = (e == 0 ? plane[0] : plane[1]) + 2 * pl;   // position
-          const bool cin = (e == 0 ? inside[0] : inside[1]) && qp >= lo && qp <= hi;
-          const float ymax = wave_max_up(cin ? fabs(y0) : 0.0);
-          if (ymax != 0.0f) {
-            const unsigned long long reach =
-                __ballot(lane >= 1 && (lane == kLadderAll - 1 || (lane < kLadderAll && lad >= (double)ymax)));
-            const int li = __ffsll(reach) - 1;
-            const int nc = tp->lad_n[li], o = tp->lad_off[li];
-            const bool wd = nc > tp->lad_n[kLadder - 1];
-            if (wd) ++wide;
-            const bool far = ymax > 1.000001f;
-            const double sy = -sg * y0, hy = -0.5 * y0 * y0;
-            if (!far) {
-#pragma unroll 2
-              for (int j = 0; j < nc; ++j) {
-                const double t = tp->ltau[o + j];
-                accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp_small(hy * (t * t)));
-              }
-            } else {
-#pragma unroll 1
-              for (int j = 0; j < nc; ++j) {
-                const double t = tp->ltau[o + j];
-                accum(fma(-ub, t, ub), sy * tp->llamw[o + j] * exp(hy * (t * t)));
-              }
-            }
-          }
+          half_range_coeffs<Q>(tp, ue, Te, sg, lane, lad, (e == 0 ? inside[0] : inside[1]) && qp >= lo && qp <= hi,
+                               wide, G);
         } else {
           // closed form (Sec. IV.A.3): G_{l+1} = ub G_l + l a G_{l-1}
           const double aa = fma(Te * tp->inv_p0, tp->inv_p0, -1.0), bb = ue * tp->inv_p0;

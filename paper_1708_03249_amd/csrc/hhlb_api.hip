@@ -254,8 +254,7 @@ struct ModelClass {
   double p0;
   hhlb::Rule rule;
   hhlb::DevTables dev;
-  Launcher launch = nullptr;    // mixed forms: one RK stage per launch
-  Launcher step = nullptr;      // FP64, Q <= 16: whole RK-3 steps per launch
+  Launcher step = nullptr;      // Q <= 16: whole RK-3 steps per launch
   std::vector<hhlb::DevWindow> windows;
   size_t win_off = 0;  // byte offset in workspace
   std::vector<hhlb::DevFusedWindow> fwindows;   // the step kernel's windows (9-cell halos)
@@ -290,13 +289,13 @@ struct hhlb_solver {
   size_t o_cell = 0, o_lnw = 0;
   bool any_large = false;
   char *ws = nullptr;
-  // stored state.  FP64 form: hi[0] = y^n (the last stage updates it in
-  // place), B and C = RK stage values.  Mixed form: hi[par] + lo[par] = y^n
-  // as FP32 value and 16-bit correction word (a ping-pong pair, par flips
-  // every step), B and C = stage increments y_s - y^n in FP32.
+  // stored state: hi[par] = y^n, a ping-pong pair (par flips every step), C a
+  // stage value or the residual's Euler stage.  Mixed form: hi[par] + lo[par] =
+  // y^n as FP32 value and 16-bit correction word, C = the Euler stage's
+  // increment in FP32.
   void *hiF[2] = {nullptr, nullptr}, *hiC[2] = {nullptr, nullptr};
   int16_t *loF[2] = {nullptr, nullptr}, *loC[2] = {nullptr, nullptr};
-  void *fB = nullptr, *fC = nullptr, *cB = nullptr, *cC = nullptr;
+  void *fC = nullptr, *cC = nullptr;
   int par = 0;
   void *fA() const { return hiF[par]; }
   void *cA() const { return hiC[par]; }
@@ -413,15 +412,6 @@ void make_grid(const hhlb_channel &c, std::vector<double> &dx) {
 
 // Round-to-nearest-even conversions of FP32 values, as the matrix-core
 // operands see them (finite values of normal range).
-float round_bf16(float x) {
-  uint32_t u;
-  std::memcpy(&u, &x, 4);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  u &= 0xFFFF0000u;
-  float y;
-  std::memcpy(&y, &u, 4);
-  return y;
-}
 float round_f16(float x) { return (float)(_Float16)x; }
 
 // Windows of the step kernel for one channel of Nx cells.  A window's edge is
@@ -548,8 +538,8 @@ hhlb_status make_tables(const hhlb_channel &h, int N, int precision, const hhlb:
       d.wp2q[k] = (double)(wk * pk * pk);
       d.pf[k] = (float)r.p[k];
     }
-    // reduced-precision operands: FP16 row scales, and the weighted column
-    // sums of the block exactly as the matrix cores round it
+    // FP16 operands: row scales, and the weighted column sums of the block
+    // exactly as the matrix cores round it
     long double wsum = 0;
     for (int k = 0; k < r.H; ++k) wsum += r.w[k];
     d.iwh = (float)(1.0L / wsum);
@@ -568,10 +558,7 @@ hhlb_status make_tables(const hhlb_channel &h, int N, int precision, const hhlb:
       long double c = 0, cl = 0;
       for (int k = 0; k < r.H; ++k) {
         float kh = d.Ks[k * r.H + j], kl = 0.0f;
-        if (precision == HHLB_MIXED_BF16) {
-          kh = round_bf16(d.Ks[k * r.H + j]);
-          kl = round_bf16(d.Ks[k * r.H + j] - kh);
-        } else if (precision == HHLB_MIXED_F16) {
+        if (precision == HHLB_MIXED_F16) {
           // the low part as the kernel forms it: the remainder rounded to
           // FP16 at 2^11 times its size, then scaled back (exact)
           const float x = d.Ks16[k * r.H + j], xh = round_f16(x);
@@ -852,11 +839,11 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         } else {
           // both half-range kinds run the half-range kernels (tables differ)
           const int kq = hhlb::half_range(h.quad) ? HHLB_HALF_HERMITE : HHLB_FULL_HERMITE;
-          auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, precision == HHLB_FP64 ? 1 : 2});
+          auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, 1});
           if (lk == launchers().end())
             return fail(HHLB_E_UNSUPPORTED, "channel " + std::to_string(c) + ": no kernel for quad=" +
                                                 std::to_string(h.quad) + " Q=" + std::to_string(h.Q));
-          (precision == HHLB_FP64 ? mc.step : mc.launch) = lk->second;
+          mc.step = lk->second;
           st = cached_tables(h, N, precision, mc.rule, mc.dev);
           if (st) return st;
         }
@@ -990,8 +977,9 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       s->o_lnw = take(sizeof(double) * 2 * n_ch);
     }
     s->o_state = o;
-    // per function: FP64 form 3 copies of 8 bytes; mixed form 4 copies of
-    // 4 bytes (hi x 2, B, C) and 2 copies of 2 bytes (lo x 2)
+    // per function 3 copies (the ping-pong pair and C); mixed form 2 copies
+    // of the 16-bit correction words besides, and the room of a fourth copy
+    // that its stated 20 bytes per population include
     const int nfun = s->has_chi ? 2 : 1;
     for (int j = 0; j < nfun * (s->mixed() ? 4 : 3); ++j) take(s->esize * s->total_state);
     if (s->mixed())
@@ -1061,16 +1049,14 @@ hhlb_status hhlb_bind_workspace(hhlb_solver *s, void *dev_ptr) {
   const size_t stride = align256(s->esize * s->total_state);
   auto next = [&](size_t bytes) { char *p = st; st += align256(bytes); return (void *)p; };
   const size_t vb = s->esize * s->total_state, lb = sizeof(int16_t) * s->total_state;
-  // FP64: y^n ping-pongs between A and B (every step writes the other copy)
-  // and C holds the second stage; mixed: (hi, lo) ping-pong, B and C the
-  // stage increments
-  s->hiF[0] = next(vb); s->fB = next(vb); s->fC = next(vb);
-  s->hiF[1] = s->mixed() ? next(vb) : s->fB;
+  // y^n ping-pongs between the copies of the pair (every step writes the
+  // other copy); C holds the second stage of the large classes and the Euler
+  // stage of the residual
+  s->hiF[0] = next(vb); s->hiF[1] = next(vb); s->fC = next(vb);
   if (s->has_chi) {
-    s->hiC[0] = next(vb); s->cB = next(vb); s->cC = next(vb);
-    s->hiC[1] = s->mixed() ? next(vb) : s->cB;
+    s->hiC[0] = next(vb); s->hiC[1] = next(vb); s->cC = next(vb);
   } else {
-    s->hiC[0] = s->hiC[1] = s->cB = s->cC = nullptr;
+    s->hiC[0] = s->hiC[1] = s->cC = nullptr;
   }
   if (s->mixed()) {
     s->loF[0] = (int16_t *)next(lb); s->loF[1] = (int16_t *)next(lb);
@@ -1163,67 +1149,43 @@ hhlb_status hhlb_init_equilibrium(hhlb_solver *s, double n0, double u0, double T
 
 namespace {
 
-// Enqueue one RK stage of model class ci.
+// Enqueue one RK stage of model class ci (Q > 16).
 void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, const void *inf, const void *inc, void *outf,
-                         void *outc, double a_base, double b_stage, hipStream_t stream,
-                         const int16_t *lo_in_f = nullptr, const int16_t *lo_in_c = nullptr,
-                         int16_t *lo_out_f = nullptr, int16_t *lo_out_c = nullptr) {
+                         void *outc, double a_base, double b_stage, hipStream_t stream) {
   ModelClass &mc = s->classes[ci];
-  if (mc.large) {
-    hhlb::LargeArgs la;
-    la.tl = (const hhlb::DevLarge *)(s->ws + mc.lbl_off);
-    la.KinT = (const double *)(s->ws + mc.lbl_off + sizeof(hhlb::DevLarge));
-    const size_t rows = mc.quad == HHLB_FULL_HERMITE ? (size_t)mc.rule.V : (size_t)mc.rule.H;
-    la.HWs = la.KinT + rows * rows;
-    la.p = ((const hhlb::DevTables *)(s->ws + s->o_tables) + ci)->p;
-    la.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
-    la.wins = (const hhlb::DevWindow *)(s->ws + mc.win_off);
-    la.nwin = (int32_t)mc.windows.size();
-    la.stage = stage;
-    la.inv_dx = (const double *)(s->ws + s->o_invdx);
-    la.gw = (const double *)(s->ws + s->o_gw);
-    la.in_f = (const double *)inf; la.in_c = (const double *)inc;
-    la.base_f = (const double *)s->fA(); la.base_c = (const double *)s->cA();
-    la.out_f = (double *)outf; la.out_c = (double *)outc;
-    la.a_base = a_base;
-    la.b_stage = b_stage;
-    la.cell = (double *)(s->ws + s->o_cell);
-    la.lnw = (double *)(s->ws + s->o_lnw);
-    la.nwall = (double *)(s->ws + s->o_nwall);
-    la.wide = (unsigned long long *)(s->ws + s->o_wide);
-    la.nfun = mc.Dt > 0 ? 2 : 1;
-    la.xcd_map = s->tuning.xcd_map;
-    hhlb::launch_large(la, mc.adv, mc.rule.H, stream);
-    return;
-  }
-  hhlb::StageArgs a;
-  std::memset(&a, 0, sizeof a);
-  a.tb = (const hhlb::DevTables *)(s->ws + s->o_tables) + ci;
-  a.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
-  a.wins = (const hhlb::DevWindow *)(s->ws + mc.win_off);
-  a.nwin = (int32_t)mc.windows.size();
-  a.stage = stage;
-  a.xcd_map = s->tuning.xcd_map;
-  a.inv_dx = (const double *)(s->ws + s->o_invdx);
-  a.gw = (const double *)(s->ws + s->o_gw);
-  a.in_f = inf; a.in_c = inc;
-  a.base_f = s->fA(); a.base_c = s->cA();
-  a.out_f = outf; a.out_c = outc;
-  a.a_base = a_base;
-  a.b_stage = b_stage;
-  a.nwall = (double *)(s->ws + s->o_nwall);
-  a.wide = (unsigned long long *)(s->ws + s->o_wide);
-  a.lo_in_f = lo_in_f; a.lo_in_c = lo_in_c;
-  a.lo_out_f = lo_out_f; a.lo_out_c = lo_out_c;
-  mc.launch(a, stream);
+  hhlb::LargeArgs la;
+  la.tl = (const hhlb::DevLarge *)(s->ws + mc.lbl_off);
+  la.KinT = (const double *)(s->ws + mc.lbl_off + sizeof(hhlb::DevLarge));
+  const size_t rows = mc.quad == HHLB_FULL_HERMITE ? (size_t)mc.rule.V : (size_t)mc.rule.H;
+  la.HWs = la.KinT + rows * rows;
+  la.p = ((const hhlb::DevTables *)(s->ws + s->o_tables) + ci)->p;
+  la.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
+  la.wins = (const hhlb::DevWindow *)(s->ws + mc.win_off);
+  la.nwin = (int32_t)mc.windows.size();
+  la.stage = stage;
+  la.inv_dx = (const double *)(s->ws + s->o_invdx);
+  la.gw = (const double *)(s->ws + s->o_gw);
+  la.in_f = (const double *)inf; la.in_c = (const double *)inc;
+  la.base_f = (const double *)s->fA(); la.base_c = (const double *)s->cA();
+  la.out_f = (double *)outf; la.out_c = (double *)outc;
+  la.a_base = a_base;
+  la.b_stage = b_stage;
+  la.cell = (double *)(s->ws + s->o_cell);
+  la.lnw = (double *)(s->ws + s->o_lnw);
+  la.nwall = (double *)(s->ws + s->o_nwall);
+  la.wide = (unsigned long long *)(s->ws + s->o_wide);
+  la.nfun = mc.Dt > 0 ? 2 : 1;
+  la.xcd_map = s->tuning.xcd_map;
+  hhlb::launch_large(la, mc.adv, mc.rule.H, stream);
 }
 
 // nsteps RK-3 steps (nst = 3), or one forward-Euler stage (nsteps = nst = 1),
-// of model class ci in one launch of the step kernel: y^n from (inf, inc), the
-// result to (outf, outc).  nsteps > 1 needs a class whose every channel is one
-// window.  With gi >= 0: of the classes of merge group gi.
-void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, const void *inf, const void *inc,
-                        void *outf, void *outc, hipStream_t stream) {
+// of model class ci in one launch of the step kernel: y^n from copy p, the
+// result to (outf, outc) (mixed forms: its correction words to copy q, or the
+// increment of the one stage).  nsteps > 1 needs a class whose every channel
+// is one window.  With gi >= 0: of the classes of merge group gi.
+void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, int p, int q, void *outf, void *outc,
+                        hipStream_t stream) {
   hhlb::StageArgs a;
   std::memset(&a, 0, sizeof a);
   a.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
@@ -1232,8 +1194,10 @@ void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, 
   a.xcd_map = s->tuning.xcd_map;
   a.inv_dx = (const double *)(s->ws + s->o_invdx);
   a.gw = (const double *)(s->ws + s->o_gw);
-  a.in_f = inf; a.in_c = inc;
+  a.in_f = s->hiF[p]; a.in_c = s->hiC[p];
   a.out_f = outf; a.out_c = outc;
+  a.lo_in_f = s->loF[p]; a.lo_in_c = s->loC[p];
+  a.lo_out_f = s->loF[q]; a.lo_out_c = s->loC[q];
   a.nwall = (double *)(s->ws + s->o_nwall);
   a.wide = (unsigned long long *)(s->ws + s->o_wide);
   a.tb = (const hhlb::DevTables *)(s->ws + s->o_tables);
@@ -1256,27 +1220,25 @@ void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, 
 // unchanged).
 void enqueue_group_step(hhlb_solver *s, size_t gi, hipStream_t stream) {
   const int p = s->par, q = p ^ 1;
-  enqueue_class_step(s, 0, (int)gi, 1, 3, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], stream);
+  enqueue_class_step(s, 0, (int)gi, 1, 3, p, q, s->hiF[q], s->hiC[q], stream);
 }
 
-// The first RK stage (a forward-Euler stage) of every class on one stream.
-void enqueue_stage(hhlb_solver *s, int stage, const void *inf, const void *inc, void *outf, void *outc,
-                   double a_base, double b_stage, hipStream_t stream) {
+// The first RK stage (a forward-Euler stage) of every class from the current
+// state to (outf, outc), on one stream (mixed forms: its increment).
+void enqueue_euler(hhlb_solver *s, void *outf, void *outc, hipStream_t stream) {
   for (size_t ci = 0; ci < s->classes.size(); ++ci) {
-    if (s->classes[ci].step) enqueue_class_step(s, ci, -1, 1, 1, inf, inc, outf, outc, stream);
-    else enqueue_class_stage(s, ci, stage, inf, inc, outf, outc, a_base, b_stage, stream);
+    if (s->classes[ci].step) enqueue_class_step(s, ci, -1, 1, 1, s->par, s->par ^ 1, outf, outc, stream);
+    else enqueue_class_stage(s, ci, 0, s->fA(), s->cA(), outf, outc, 0.0, 1.0, stream);
   }
 }
 
 // n_steps RK-3 steps (Eq. rk3) of class ci on one stream, starting from the
 // solver's current state parity (left unchanged).
-//  FP64, Q <= 16, y^n in copy p of the pair (A, B), q = 1 - p: one launch p -> q
-//        per step; channels of one window each keep their state in registers
-//        through up to kStepsPerLaunch steps of a launch.
-//  FP64, Q > 16: stage 1 p -> q, stage 2 (q, p) -> C, stage 3 (C, p) -> q (y1
-//        in q is dead by then).
-//  Mixed: stage 1 hi -> d1 (B), stage 2 (hi, d1) -> d2 (C), stage 3
-//        (hi, lo, d2) -> the other (hi, lo) copy.
+//  Q <= 16, y^n in copy p of the pair, q = 1 - p: one launch p -> q per step;
+//        channels of one window each keep their state in registers through up
+//        to kStepsPerLaunch steps of a launch.
+//  Q > 16: stage 1 p -> q, stage 2 (q, p) -> C, stage 3 (C, p) -> q (y1 in q
+//        is dead by then).
 // Every step moves y^n to the other copy: the parity flips.
 constexpr int64_t kStepsPerLaunch = 64;   // about half a millisecond of a small channel
 
@@ -1289,16 +1251,11 @@ void enqueue_class_steps(hhlb_solver *s, size_t ci, int64_t n_steps, hipStream_t
     if (mc.step && mc.whole) k = std::min(n_steps - step, kStepsPerLaunch);
     const int q = p ^ (int)(k & 1);
     if (mc.step) {
-      enqueue_class_step(s, ci, -1, (int)k, 3, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], stream);
-    } else if (!s->mixed()) {
+      enqueue_class_step(s, ci, -1, (int)k, 3, p, q, s->hiF[q], s->hiC[q], stream);
+    } else {
       enqueue_class_stage(s, ci, 0, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
       enqueue_class_stage(s, ci, 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
       enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
-    } else {
-      enqueue_class_stage(s, ci, 0, nullptr, nullptr, s->fB, s->cB, 0.0, 1.0, stream);
-      enqueue_class_stage(s, ci, 1, s->fB, s->cB, s->fC, s->cC, 0.75, 0.25, stream);
-      enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream,
-                          s->loF[p], s->loC[p], s->loF[q], s->loC[q]);
     }
     s->par = q;
     step += k;
@@ -1480,7 +1437,7 @@ extern "C" hhlb_status hhlb_autotune(hhlb_solver *s, int32_t trial_steps, hhlb_t
   const bool multi = s->classes.size() > 1;
   bool has4 = false, hasf = false;
   for (auto &mc : s->classes) {
-    const bool half = mc.step && hhlb::half_range(mc.quad);
+    const bool half = !s->mixed() && mc.step && hhlb::half_range(mc.quad);
     has4 = has4 || (half && mc.Dt > 0);
     hasf = hasf || half;
   }
@@ -1576,12 +1533,12 @@ hhlb_status hhlb_diagnostics(hhlb_solver *s, double *n_wall_dev, double *mass_de
     // one forward-Euler stage from the current state into the C copies; the
     // state (A) and the wall densities are left untouched
     if (s->mixed()) {
-      enqueue_stage(s, 0, nullptr, nullptr, s->fC, s->cC, 0.0, 1.0, s->stream);
+      enqueue_euler(s, s->fC, s->cC, s->stream);
       hipLaunchKernelGGL(residual_kernel<float>, dim3(n_ch), dim3(256), 0, s->stream, a.tbs, a.ch_class, a.chans,
                          a.ch_V, a.n_ch, a.scaled, 1, (const float *)s->fA(), (const float *)s->fC,
                          (const float *)s->cA(), (const float *)s->cC, hc, residual_dev);
     } else {
-      enqueue_stage(s, 0, s->fA(), s->cA(), s->fC, s->cC, 0.0, 1.0, s->stream);
+      enqueue_euler(s, s->fC, s->cC, s->stream);
       hipLaunchKernelGGL(residual_kernel<double>, dim3(n_ch), dim3(256), 0, s->stream, a.tbs, a.ch_class, a.chans,
                          a.ch_V, a.n_ch, a.scaled, 0, (const double *)s->fA(), (const double *)s->fC,
                          (const double *)s->cA(), (const double *)s->cC, hc, residual_dev);

@@ -1,4 +1,4 @@
-// Mixed-precision half-range stage kernels, force block in BF16 form.
+// Mixed-precision half-range step kernels, force block in BF16 form.
 #include "launch.hpp"
 #include "mixed_kernels.hpp"
 
@@ -6,18 +6,18 @@ namespace hhlb {
 namespace {
 
 template <int Q, int NF, int ADV>
-void launch_stage(const StageArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL((stage_kernel_mixed<Q, NF, ADV, kPrecBF16>), dim3(a.nwin), dim3(128), 0, s, a, a.tb,
-                     a.chans, a.wins, a.inv_dx, a.gw, (const float *)a.base_f, (const float *)a.base_c,
-                     (const float *)a.in_f, (const float *)a.in_c);
+void launch_step(const StageArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL((step_kernel_mixed<Q, NF, ADV, kPrecBF16>), dim3(a.nwin), dim3(128 * NF), 0, s, a, a.tb, a.chans,
+                     reinterpret_cast<const DevFusedWindow *>(a.wins), a.inv_dx, a.gw, (const float *)a.in_f,
+                     (const float *)a.in_c);
 }
 
 template <int Q>
 void add(LaunchMap &m) {
-  m[{0, Q, 1, 0, kPrecBF16, 2}] = launch_stage<Q, 1, 0>;
-  m[{0, Q, 1, 1, kPrecBF16, 2}] = launch_stage<Q, 1, 1>;
-  m[{0, Q, 2, 0, kPrecBF16, 2}] = launch_stage<Q, 2, 0>;
-  m[{0, Q, 2, 1, kPrecBF16, 2}] = launch_stage<Q, 2, 1>;
+  m[{0, Q, 1, 0, kPrecBF16, 1}] = launch_step<Q, 1, 0>;
+  m[{0, Q, 1, 1, kPrecBF16, 1}] = launch_step<Q, 1, 1>;
+  m[{0, Q, 2, 0, kPrecBF16, 1}] = launch_step<Q, 2, 0>;
+  m[{0, Q, 2, 1, kPrecBF16, 1}] = launch_step<Q, 2, 1>;
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-// Registry of the stage-kernel launchers, keyed by model shape and arithmetic
+// Registry of the step-kernel launchers, keyed by model shape and arithmetic
 // form.  Each kernel family is instantiated in its own translation unit.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -12,8 +12,8 @@ namespace hhlb {
 
 using Launcher = void (*)(const StageArgs &, hipStream_t);
 // (quadrature kind, Q, functions (1 = f, 2 = f and chi), advection, precision,
-//  shape: 2 = the mixed stage kernels, 1 = the FP64 kernel of whole RK-3 steps,
-//  3 = the same across classes, keyed by the largest order it holds)
+//  shape: 1 = one class, 3 = across classes (FP64), keyed by the largest order
+//  it holds)
 using LaunchKey = std::tuple<int, int, int, int, int, int>;
 using LaunchMap = std::map<LaunchKey, Launcher>;
 

@@ -22,15 +22,6 @@ constexpr int kLadderTop = 16; // the top calibrated count
 constexpr int kLadderPts = 64 + kLadderTop * (2 + 4 + 8 + 16 + 32 + 64);   // points over all entries
 constexpr int kWin = 58;       // output cells per wavefront
 
-// Build-time tuning switches: matrix cores for the 16 x 16 contractions of the
-// mixed kernels (Q = 16), and the node-functions per scheduling section of
-// their advection pass.
-#ifndef HHLB_MFMA
-#define HHLB_MFMA 1
-#endif
-#ifndef HHLB_SCHED_GROUP
-#define HHLB_SCHED_GROUP 1
-#endif
 constexpr int kHalo = 3;
 
 // Per model class (quadrature, Q, N, p0): uploaded once.
@@ -71,7 +62,7 @@ struct DevTables {
   float Ks[kQmaxDev * kQmaxDev];          // Kin[k][j] w_j / w_k
   float kas[kQmaxDev];                    // ka_k / w_k
   float pf[2 * kQmaxDev];                 // p_k/m
-  // reduced-precision force operands (BF16 / FP16 forms): the FP16 table is
+  // reduced-precision force operands (FP16 form): the FP16 table is
   // Ks with row k scaled by rsc_k (a power of two, |row| <= 1) and irsc_k =
   // 1/rsc_k.  The matrix cores see the table as a high part Kh (the operand
   // rounding of it) plus a low part Kl (the rounding of the remainder);
@@ -120,23 +111,19 @@ struct StageArgs {
   const DevChannel *chans;
   const DevWindow *wins;
   int32_t nwin;
-  int32_t stage;             // 0, 1, 2 (only stage 2 writes the wall densities)
   int32_t xcd_map;           // 1: XCD-aware block -> window mapping, 0: identity
   int32_t nblocks;           // launch across classes: blocks (0: one per window, -1: what the GPU holds at once)
-  int32_t nsteps, nst;       // FP64 form: steps of the launch and stages per step (3; 1: one forward-Euler stage)
+  int32_t nsteps, nst;       // steps of the launch and stages per step (3; 1: one forward-Euler stage)
   const double *inv_dx;      // per cell
   const double *gw;          // wall equilibria
   // state arrays: double (FP64 form) or float (mixed form)
-  const void *in_f, *in_c;   // stage state
-  const void *base_f, *base_c;  // y^n (pointwise)
+  const void *in_f, *in_c;   // y^n
   void *out_f, *out_c;
-  double a_base, b_stage;    // out = a_base * y^n + b_stage * (y_s + dt L[y_s])
   double *nwall;             // 2 per channel (may be null)
   // count of waves whose equilibrium needed more than one correction panel
   // (|y0| beyond the calibrated range of the ladder; may be null)
   unsigned long long *wide;
-  // mixed form only: 16-bit correction words of y^n (read in the last stage)
-  // and of y^{n+1} (written there)
+  // mixed form only: 16-bit correction words of y^n and of y^{n+1}
   const int16_t *lo_in_f, *lo_in_c;
   int16_t *lo_out_f, *lo_out_c;
 };
@@ -309,7 +296,8 @@ __device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t r, uint32_t off
 // scalar registers and spill into vector lanes).
 struct RowWalk {
   const char *p;
-  __device__ __forceinline__ RowWalk(const void *base, int64_t elem) : p((const char *)base + elem * 8) {}
+  __device__ __forceinline__ RowWalk(const void *base, int64_t elem, int size = 8)
+      : p((const char *)base + elem * size) {}
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t take(int64_t stride_bytes, uint32_t bytes) {
     const __amdgpu_buffer_rsrc_t r = row_rsrc(p, bytes);
     p += stride_bytes;
@@ -337,67 +325,6 @@ __device__ __forceinline__ int xcd_window(int b, int n) {
   return x * q + (x < r ? x : r) + pos;
 }
 
-// The correction rule of a wave whose largest |y0| is ymax (a scalar): the
-// first ladder entry, calibrated or composite, whose reach covers it; the
-// last (64 panels of the top count) when none does, also for a non-finite
-// ymax.  Entries beyond the calibrated ones hold more points than the top
-// count, which is how the kernels count such waves.
-template <class Tables>
-__device__ __forceinline__ int ladder_entry(Tables tb, double ymax) {
-  int li = kLadderAll - 1;
-  for (int j = 1; j < kLadderAll; ++j)
-    if (tb->lad_y[j] >= ymax) { li = j; break; }
-  return li;
-}
-
-// Maximum over the wave (all lanes active).  After the butterfly every lane
-// holds the same value; it is returned through the first lane as a scalar,
-// so that what depends on it (the ladder entry, the loop counts of the
-// correction) stays in scalar registers and scalar branches.
-__device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = fmax(x, __shfl_xor(x, off, 64));
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 typedef double dbl4 __attribute__((ext_vector_type(4)));
-
-// Register layout of v_mfma_f64_16x16x4f64 (checked on the GPU):
-//   A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
-//   D[i][j] in lane j + 16 (i % 4), accumulator register i / 4.
-// OUT[i][cell] = sum_k M[i][k] X[k][cell] for the 16 x 16 table M (held as
-// four A operands, aM[kc] = M[lane % 16][4 kc + lane / 16]) and the 16
-// values X[0..15] each lane (= cell) holds.  The cell-major data are
-// transposed into the B layout and back through a padded LDS tile T of
-// 64 x 17 doubles owned by this wavefront.
-__device__ __forceinline__ void mfma_contract16(const double aM[4], const double X[16], double OUT[16],
-                                                double *T, int lane) {
-  constexpr int S = 17;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) T[lane * S + k] = X[k];
-  __builtin_amdgcn_wave_barrier();
-  dbl4 acc[4];
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    acc[cb] = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-      const double b = T[(16 * cb + (lane & 15)) * S + 4 * kc + (lane >> 4)];
-      acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aM[kc], b, acc[cb], 0, 0, 0);
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) T[(16 * cb + (lane & 15)) * S + 4 * r + (lane >> 4)] = acc[cb][r];
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) OUT[k] = T[lane * S + k];
-  __builtin_amdgcn_wave_barrier();
-}
 
 }  // namespace hhlb

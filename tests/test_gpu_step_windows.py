@@ -68,3 +68,26 @@ def test_vanishing_differences(adv):
     gpu = run_gpu(chans, states, 6)
     assert gpu["bad"] == 0
     compare(chans, gpu, run_oracle(chans, states, 6, gpu["dt"]), tol=1e-12, what=f"flat stretches, {adv}")
+
+
+@pytest.mark.parametrize("form", ["mixed_f32", "mixed_bf16", "mixed_f16"])
+@pytest.mark.parametrize("Q,dof,nsteps", [(4, 2, 4), (16, 2, 4), (12, 0, 4), (3, 2, 131)])
+def test_mixed_window_edges(form, Q, dof, nsteps):
+    """The mixed step kernel at the same edges (lengths of one, two and more
+    windows; with nsteps = 131 one-window channels that keep their correction
+    words in registers through launches of 64, 64 and 3 steps), one channel
+    with a uniform stretch.  Tolerance: 1e-5 in n, u and T, the bar of the
+    mixed forms (each stage rounds faces and increments to FP32, 6e-8)."""
+    import paper_1708_03249_amd as H
+    from gpu_common import moment_errors
+    lengths = (8, 123, 124) if nsteps > 64 else (9, 124, 125, 127, 234, 235, 344, 345)
+    chans = [H.Channel(Q=Q, Nx=nx, adv=H.WENO5, transverse_dof=dof, stretch_A=0.5 * (k % 2), Kn=0.05 * (1 + k % 3),
+                       g=-0.4, T_right=1.3, dt=-0.5) for k, nx in enumerate(lengths)]
+    states = initial_states(chans, seed=43, perturb=0.02)
+    for y in states[1]:
+        if y is not None:
+            y[:, 30:60] = y[:, 30:31]
+    gpu = run_gpu(chans, states, nsteps, precision=H.PRECISIONS[form])
+    assert gpu["bad"] == 0
+    e = moment_errors(chans, gpu, run_oracle(chans, states, nsteps, gpu["dt"]))
+    assert max(e.values()) <= 1e-5, (form, e)
