@@ -256,6 +256,7 @@ struct ModelClass {
   hhlb::DevTables dev;
   Launcher step = nullptr;      // Q <= 16: whole RK-3 steps per launch
   std::vector<hhlb::DevWindow> windows;
+  int max_out = 0;     // the longest of them
   size_t win_off = 0;  // byte offset in workspace
   std::vector<hhlb::DevFusedWindow> fwindows;   // the step kernel's windows (9-cell halos)
   size_t fwin_off = 0;
@@ -285,9 +286,10 @@ struct hhlb_solver {
   // workspace layout (byte offsets)
   size_t o_tables = 0, o_chans = 0, o_chclass = 0, o_V = 0, o_dx = 0, o_invdx = 0, o_gw = 0,
          o_nwall = 0, o_feq = 0, o_feqoff = 0, o_flag = 0, o_wide = 0, o_state = 0, bytes = 0;
-  // large classes: per-cell output of the cell phase and the stage's wall densities
-  size_t o_cell = 0, o_lnw = 0;
-  bool any_large = false;
+  // large classes: the partial sums per tile, cell and wall of the state a stage
+  // reads and of the one it writes, in turn
+  size_t o_sums[2] = {0, 0}, o_wall[2] = {0, 0};
+  int max_tiles = 0;
   char *ws = nullptr;
   // stored state: hi[par] = y^n, a ping-pong pair (par flips every step), C a
   // stage value or the residual's Euler stage.  Mixed form: hi[par] + lo[par] =
@@ -833,9 +835,9 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         const int nf = h.transverse_dof > 0 ? 2 : 1;
         if (large) {
           mc.large = true;
-          s->any_large = true;
           st = make_large_tables(h, N, mc.rule, mc.dev, mc.lblob);
           if (st) return st;
+          s->max_tiles = std::max(s->max_tiles, 2 * ((mc.rule.H + hhlb::kTileNodes - 1) / hhlb::kTileNodes));
         } else {
           // both half-range kinds run the half-range kernels (tables differ)
           const int kq = hhlb::half_range(h.quad) ? HHLB_HALF_HERMITE : HHLB_FULL_HERMITE;
@@ -912,7 +914,15 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       d.half_Dt = 0.5 * h.transverse_dof;
       d.inv_1pDt = 1.0 / (1.0 + h.transverse_dof);
       s->dch.push_back(d);
-      for (int i0 = 0; i0 < h.Nx; i0 += hhlb::kWin) mc.windows.push_back({c, i0});
+      // windows of at most kWin cells and nearly equal length, so that a wall's
+      // three nearest cells lie in one
+      const int nw = (h.Nx + hhlb::kWin - 1) / hhlb::kWin;
+      for (int w = 0, i0 = 0; w < nw; ++w) {
+        const int m = (h.Nx - i0 + nw - w - 1) / (nw - w);
+        mc.windows.push_back({c, i0, m});
+        mc.max_out = std::max(mc.max_out, m);
+        i0 += m;
+      }
       if (mc.step) {
         const size_t had = mc.fwindows.size();
         step_windows(c, h.Nx, mc.fwindows);
@@ -972,10 +982,11 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
     s->o_wide = take(sizeof(unsigned long long));
     for (auto &mc : s->classes)
       if (mc.large) mc.lbl_off = take(mc.lblob.size());
-    if (s->any_large) {
-      s->o_cell = take(sizeof(double) * hhlb::kCellStride * s->total_cells);
-      s->o_lnw = take(sizeof(double) * 2 * n_ch);
-    }
+    if (s->max_tiles)
+      for (int b = 0; b < 2; ++b) {
+        s->o_sums[b] = take(sizeof(double) * s->max_tiles * hhlb::kSums * s->total_cells);
+        s->o_wall[b] = take(sizeof(double) * s->max_tiles * n_ch);
+      }
     s->o_state = o;
     // per function 3 copies (the ping-pong pair and C); mixed form 2 copies
     // of the 16-bit correction words besides, and the room of a fourth copy
@@ -1149,11 +1160,12 @@ hhlb_status hhlb_init_equilibrium(hhlb_solver *s, double n0, double u0, double T
 
 namespace {
 
-// Enqueue one RK stage of model class ci (Q > 16).
-void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, const void *inf, const void *inc, void *outf,
-                         void *outc, double a_base, double b_stage, hipStream_t stream) {
-  ModelClass &mc = s->classes[ci];
+// Arguments of the large classes' kernels (Q > 16) for class ci; the partial
+// sums are read from buffer b and written to the other.
+hhlb::LargeArgs large_args(hhlb_solver *s, size_t ci, int b, const void *inf, const void *inc) {
+  const ModelClass &mc = s->classes[ci];
   hhlb::LargeArgs la;
+  std::memset(&la, 0, sizeof la);
   la.tl = (const hhlb::DevLarge *)(s->ws + mc.lbl_off);
   la.KinT = (const double *)(s->ws + mc.lbl_off + sizeof(hhlb::DevLarge));
   const size_t rows = mc.quad == HHLB_FULL_HERMITE ? (size_t)mc.rule.V : (size_t)mc.rule.H;
@@ -1162,21 +1174,38 @@ void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, const void *inf, 
   la.chans = (const hhlb::DevChannel *)(s->ws + s->o_chans);
   la.wins = (const hhlb::DevWindow *)(s->ws + mc.win_off);
   la.nwin = (int32_t)mc.windows.size();
-  la.stage = stage;
   la.inv_dx = (const double *)(s->ws + s->o_invdx);
   la.gw = (const double *)(s->ws + s->o_gw);
   la.in_f = (const double *)inf; la.in_c = (const double *)inc;
   la.base_f = (const double *)s->fA(); la.base_c = (const double *)s->cA();
+  la.sums_in = (const double *)(s->ws + s->o_sums[b]);
+  la.wall_in = (const double *)(s->ws + s->o_wall[b]);
+  la.sums_out = (double *)(s->ws + s->o_sums[b ^ 1]);
+  la.wall_out = (double *)(s->ws + s->o_wall[b ^ 1]);
+  la.ncells = (int32_t)s->total_cells;
+  la.nch = (int32_t)s->ch.size();
+  la.nwall = (double *)(s->ws + s->o_nwall);
+  la.wide = (unsigned long long *)(s->ws + s->o_wide);
+  la.xcd_map = s->tuning.xcd_map;
+  return la;
+}
+
+// Enqueue the partial sums of a state of class ci into buffer b.
+void enqueue_class_sums(hhlb_solver *s, size_t ci, int b, const void *inf, const void *inc, hipStream_t stream) {
+  const ModelClass &mc = s->classes[ci];
+  hhlb::launch_large_sums(large_args(s, ci, b ^ 1, inf, inc), mc.adv, mc.Dt > 0 ? 2 : 1, mc.rule.H, stream);
+}
+
+// Enqueue one RK stage of class ci; the partial sums of its input are in buffer b.
+void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, int b, const void *inf, const void *inc, void *outf,
+                         void *outc, double a_base, double b_stage, hipStream_t stream) {
+  const ModelClass &mc = s->classes[ci];
+  hhlb::LargeArgs la = large_args(s, ci, b, inf, inc);
+  la.stage = stage;
   la.out_f = (double *)outf; la.out_c = (double *)outc;
   la.a_base = a_base;
   la.b_stage = b_stage;
-  la.cell = (double *)(s->ws + s->o_cell);
-  la.lnw = (double *)(s->ws + s->o_lnw);
-  la.nwall = (double *)(s->ws + s->o_nwall);
-  la.wide = (unsigned long long *)(s->ws + s->o_wide);
-  la.nfun = mc.Dt > 0 ? 2 : 1;
-  la.xcd_map = s->tuning.xcd_map;
-  hhlb::launch_large(la, mc.adv, mc.rule.H, stream);
+  hhlb::launch_large(la, mc.adv, mc.Dt > 0 ? 2 : 1, mc.rule.H, mc.max_out, stream);
 }
 
 // nsteps RK-3 steps (nst = 3), or one forward-Euler stage (nsteps = nst = 1),
@@ -1228,7 +1257,10 @@ void enqueue_group_step(hhlb_solver *s, size_t gi, hipStream_t stream) {
 void enqueue_euler(hhlb_solver *s, void *outf, void *outc, hipStream_t stream) {
   for (size_t ci = 0; ci < s->classes.size(); ++ci) {
     if (s->classes[ci].step) enqueue_class_step(s, ci, -1, 1, 1, s->par, s->par ^ 1, outf, outc, stream);
-    else enqueue_class_stage(s, ci, 0, s->fA(), s->cA(), outf, outc, 0.0, 1.0, stream);
+    else {
+      enqueue_class_sums(s, ci, 0, s->fA(), s->cA(), stream);
+      enqueue_class_stage(s, ci, 0, 0, s->fA(), s->cA(), outf, outc, 0.0, 1.0, stream);
+    }
   }
 }
 
@@ -1253,9 +1285,12 @@ void enqueue_class_steps(hhlb_solver *s, size_t ci, int64_t n_steps, hipStream_t
     if (mc.step) {
       enqueue_class_step(s, ci, -1, (int)k, 3, p, q, s->hiF[q], s->hiC[q], stream);
     } else {
-      enqueue_class_stage(s, ci, 0, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
-      enqueue_class_stage(s, ci, 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
-      enqueue_class_stage(s, ci, 2, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
+      // the partial sums alternate between their two buffers with the stages
+      const int b = (int)(step & 1);
+      if (step == 0) enqueue_class_sums(s, ci, 0, s->hiF[p], s->hiC[p], stream);
+      enqueue_class_stage(s, ci, 0, b, s->hiF[p], s->hiC[p], s->hiF[q], s->hiC[q], 0.0, 1.0, stream);
+      enqueue_class_stage(s, ci, 1, b ^ 1, s->hiF[q], s->hiC[q], s->fC, s->cC, 0.75, 0.25, stream);
+      enqueue_class_stage(s, ci, 2, b, s->fC, s->cC, s->hiF[q], s->hiC[q], 1.0 / 3.0, 2.0 / 3.0, stream);
     }
     s->par = q;
     step += k;
@@ -1576,7 +1611,7 @@ hhlb_status hhlb_launch_info(const hhlb_solver *s, int32_t *launches_per_stage, 
     int32_t n = 0;
     const bool merge = s->tuning.merge_classes != 0;
     for (size_t ci = 0; ci < s->classes.size(); ++ci)
-      if (!merge || s->class_group[ci] < 0) n += s->classes[ci].large ? 2 : 1;   // large: cell and node phase
+      if (!merge || s->class_group[ci] < 0) ++n;
     if (merge) n += (int32_t)s->groups.size();
     *launches_per_stage = n;
   }

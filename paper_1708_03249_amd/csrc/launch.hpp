@@ -26,7 +26,9 @@ void register_classes(LaunchMap &m);
 // The node-parallel FP64 stage of large half-range classes (Q > 16):
 // kernels_large.hip.
 struct LargeArgs;
-void launch_large(const LargeArgs &a, int adv, int H, hipStream_t s);
+void launch_large(const LargeArgs &a, int adv, int nfun, int H, int max_out, hipStream_t s);
+// The partial sums of the state (in_f, in_c), which the first stage of a call reads.
+void launch_large_sums(const LargeArgs &a, int adv, int nfun, int H, hipStream_t s);
 
 // The mixed-quadrature (App. A) velocity-space stage: kernels_multi.hip.
 struct MultiArgs;

@@ -100,10 +100,9 @@ struct DevChannel {
 
 typedef const __attribute__((address_space(4))) DevChannel *ConstChannel;
 
-// Window: channel id and first output cell.
+// Window: channel id, first output cell and number of output cells.
 struct DevWindow {
-  int32_t ch;
-  int32_t i0;
+  int32_t ch, i0, nout;
 };
 
 struct StageArgs {
