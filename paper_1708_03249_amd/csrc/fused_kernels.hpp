@@ -67,11 +67,15 @@ struct DevFusedClassWindow {
 template <int QUAD, int Q>
 constexpr bool step_mfma() { return QUAD == 0 && Q >= HHLB_STEP_MFMA && Q % 4 == 0; }
 
+// Partial sums of a half and cell: n, momentum, energy and the projection of f;
+// with chi its sum and projection.
+constexpr int step_sums(int nfun) { return nfun > 1 ? 6 : 4; }
+
 // LDS of a window (doubles)
 template <int QUAD, int Q, int NFUN>
 constexpr int step_lds_doubles() {
   constexpr int H = QUAD == 0 ? Q : Q / 2;
-  constexpr int part = 2 * 6 * kStepCells;            // moment partials of the halves
+  constexpr int part = 2 * step_sums(NFUN) * kStepCells;   // moment partials of the halves
   constexpr int geq = 2 * 2 * H * 64;                 // equilibrium populations
   constexpr int y = QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells;   // dense force matrix: every node's population
   // matrix cores: a tile per wave, in the memory of the partials (dead by then)
@@ -391,7 +395,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     // ---- partial moments of this half and the rank-1 force projections ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     auto part = [&](int h, int q, int s) -> double & {
-      return s_part[((h * 6 + q) * 2 + plane[s]) * 64 + pl];
+      return s_part[((h * step_sums(NFUN) + q) * 2 + plane[s]) * 64 + pl];
     };
     {
       double m0[SLOTS] = {0.0, 0.0}, mb[SLOTS] = {0.0, 0.0};
@@ -411,7 +415,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           part(hw, 0, s) = m0[s];
           part(hw, 1, s) = sg * m1[s];
           part(hw, 2, s) = m2[s];
-          part(hw, 4, s) = mb[s];
+          part(hw, 3, s) = mb[s];
         }
       } else {
 #pragma unroll
@@ -423,7 +427,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
-          part(hw, 3, s) = m0[s];
+          part(hw, 4, s) = m0[s];
           part(hw, 5, s) = mb[s];
         }
       }
@@ -464,8 +468,8 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       const double ns = part(0, 0, s) + part(1, 0, s), mom = part(0, 1, s) + part(1, 1, s);
       const double s2 = part(0, 2, s) + part(1, 2, s);
       double ech = 0.0;
-      if constexpr (NFUN > 1) ech = part(0, 3, s) + part(1, 3, s);
-      bp[s] = QUAD == 0 ? part(0, 4 + fn, s) + part(1, 4 + fn, s) : 0.0;
+      if constexpr (NFUN > 1) ech = part(0, 4, s) + part(1, 4, s);
+      bp[s] = QUAD == 0 ? part(0, fn ? 5 : 3, s) + part(1, fn ? 5 : 3, s) : 0.0;
       const double rn = recip(ns);
       n[s] = inside[s] ? ns : 1.0;
       u[s] = inside[s] ? mom * rn : 0.0;

@@ -333,18 +333,19 @@ template <int Q, int PREC>
 constexpr bool mixed_mfma() { return PREC != kPrecF32 || Q == 16; }
 
 // LDS of a window (bytes): the moment partials, the equilibrium populations,
-// a tile per wave for the force block.  At H = 16 the tiles lie in the memory
-// of the partials: 48 KB, three blocks per CU (60 KB would leave two).
-constexpr int kMixedPart = 2 * 6 * kStepCells * 8;
+// a tile per wave for the force block.  At H = 16, and for f alone, the tiles
+// lie in the memory of the partials: 48 KB, three blocks per CU, where 60 KB
+// would leave two (f alone, Q = 6: 20 KB, seven blocks of two waves, not five).
+constexpr int mixed_part(int nfun) { return 2 * step_sums(nfun) * kStepCells * 8; }
 constexpr int kMixedTile = 64 * 16 * 4;
 template <int Q, int NFUN, int PREC>
-constexpr bool mixed_alias() { return mixed_mfma<Q, PREC>() && Q > 12; }
+constexpr bool mixed_alias() { return mixed_mfma<Q, PREC>() && (Q > 12 || NFUN == 1); }
 template <int Q, int NFUN, int PREC>
-constexpr int mixed_tile_offset() { return mixed_alias<Q, NFUN, PREC>() ? 0 : kMixedPart; }
+constexpr int mixed_tile_offset() { return mixed_alias<Q, NFUN, PREC>() ? 0 : mixed_part(NFUN); }
 template <int Q, int NFUN, int PREC>
 constexpr int mixed_geq_offset() {
   constexpr int tiles = mixed_mfma<Q, PREC>() ? 2 * NFUN * kMixedTile : 0;
-  return mixed_alias<Q, NFUN, PREC>() ? (tiles > kMixedPart ? tiles : kMixedPart) : kMixedPart + tiles;
+  return mixed_alias<Q, NFUN, PREC>() ? (tiles > mixed_part(NFUN) ? tiles : mixed_part(NFUN)) : mixed_part(NFUN) + tiles;
 }
 template <int Q, int NFUN, int PREC>
 constexpr int mixed_lds_bytes() { return mixed_geq_offset<Q, NFUN, PREC>() + 2 * 2 * Q * 64 * 8 + 2 * 8; }
@@ -473,7 +474,7 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     // ---- partial moments of this half (FP64) and the rank-1 force projections ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     auto part = [&](int h, int q, int s) -> double & {
-      return s_part[((h * 6 + q) * 2 + plane[s]) * 64 + pl];
+      return s_part[((h * step_sums(NFUN) + q) * 2 + plane[s]) * 64 + pl];
     };
     {
       double m0[SLOTS] = {0.0, 0.0}, mb[SLOTS] = {0.0, 0.0};
@@ -494,7 +495,7 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
           part(hw, 0, s) = m0[s];
           part(hw, 1, s) = sg * m1[s];
           part(hw, 2, s) = m2[s];
-          part(hw, 4, s) = mb[s];
+          part(hw, 3, s) = mb[s];
         }
       } else {
 #pragma unroll
@@ -507,7 +508,7 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
           }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
-          part(hw, 3, s) = m0[s];
+          part(hw, 4, s) = m0[s];
           part(hw, 5, s) = mb[s];
         }
       }
@@ -543,8 +544,8 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
       const double ns = part(0, 0, s) + part(1, 0, s), mom = part(0, 1, s) + part(1, 1, s);
       const double s2 = part(0, 2, s) + part(1, 2, s);
       double ech = 0.0;
-      if constexpr (NFUN > 1) ech = part(0, 3, s) + part(1, 3, s);
-      bp[s] = (float)(part(0, 4 + fn, s) + part(1, 4 + fn, s));
+      if constexpr (NFUN > 1) ech = part(0, 4, s) + part(1, 4, s);
+      bp[s] = (float)(part(0, fn ? 5 : 3, s) + part(1, fn ? 5 : 3, s));
       const double rn = recip(ns);
       n[s] = inside[s] ? ns : 1.0;
       u[s] = inside[s] ? mom * rn : 0.0;
