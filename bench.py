@@ -66,18 +66,15 @@ def workload(n_ch=N_CH, nx=NX, quad=None):
 
 
 def bytes_per_node_update(form="fp64", nfun=2):
-    """Algorithmic HBM bytes of one RK-3 step.  One kernel per stage, FP64:
-    stage 1 reads y^n and writes y1; stages 2 and 3 read the stage state and
-    y^n and write the next state: 8 passes of 8 bytes per function.  Mixed:
-    stage 1 reads hi (4) and writes d1 (4); stage 2 reads hi and d1 and writes
-    d2; stage 3 reads hi, lo (2) and d2 and writes hi and lo: 36 bytes per
-    function.  Fused FP64 step: y^n in, y^{n+1} out, 16 bytes per function
-    (the method's minimum)."""
-    return nfun * {"fp64": 64, "fp64_fused": 16}.get(form, 36)
+    """Algorithmic HBM bytes of one RK-3 step: y^n in, y^{n+1} out, per
+    function 16 bytes in FP64, 12 in the mixed forms (4 bytes of hi and 2 of
+    lo each way)."""
+    return nfun * {"fp64": 16, "fp64_fused": 16}.get(form, 12)
 
 
 def form_precision(H, form):
-    """Arithmetic form of a bench form name (fp64_fused: FP64, fused steps)."""
+    """Arithmetic form of a bench form name (fp64_fused: FP64 with the
+    step_fusion switch set, which selects nothing: every step is one launch)."""
     return H.PRECISIONS["fp64" if form == "fp64_fused" else form]
 
 
@@ -355,6 +352,8 @@ def _profile_record(form="fp64", name=None):
         rec = json.load(fh)
     h = hashlib.sha256()
     for f in rec.get("kernel_source_files", ()):
+        if not os.path.exists(os.path.join(ROOT, f)):
+            return None
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     if h.hexdigest() != rec.get("kernel_source_sha256"):
@@ -504,25 +503,24 @@ def run_form(H, torch, np, chans, form, args):
     mass_err = float(((mass - mass0) / mass0).abs().max().item())   # relative, from the start
     node_updates = sum(c.V * c.Nx for c in chans) * args.steps
     value = node_updates / (ms / 1e3)
-    # dominant kernel: the stage kernel (every launch of the timed region),
-    # or the fused-step kernel (one launch per class and step)
-    per_step = 1 if form == "fp64_fused" else 3
-    n_launch = per_step * args.steps * launches
+    # dominant kernel: the step kernel (every launch of the timed region, one
+    # per class and step)
+    n_launch = args.steps * launches
     avg_launch_s = ms / 1e3 / n_launch
     nu_per_launch = sum(c.V * c.Nx for c in chans) / launches
-    bpl = bytes_per_node_update(form) / per_step * nu_per_launch
+    bpl = bytes_per_node_update(form) * nu_per_launch
     nc = mean_ladder_points(s, mom, np)
-    # the fused kernel also computes its halo lanes: 64 lanes per 46 outputs
-    redundancy = 64.0 / 46.0 if form == "fp64_fused" else 1.0
-    fpl = flops_per_node_update(nc=nc) * redundancy / per_step * nu_per_launch
+    # the kernel also computes its halo cells: 128 per 110 outputs
+    redundancy = 128.0 / 110.0
+    fpl = flops_per_node_update(nc=nc) * redundancy * nu_per_launch
     gbs = bpl / avg_launch_s / 1e9
     tfs = fpl / avg_launch_s / 1e12
-    # the scope's roof for this streaming stencil is HBM (128 B per
-    # node-update in FP64, 72 in the mixed forms); the vector-ALU fraction of
+    # the scope's roof for this streaming stencil is HBM (32 B per
+    # node-update in FP64, 24 in the mixed forms); the vector-ALU fraction of
     # the executed flop count rides along
-    kname = {"fp64": "hhlb::stage_kernel_half<16,2,0> (one RK-3 stage, FP64)",
-             "fp64_fused": "hhlb::fused_kernel_half<16,2,0> (one whole RK-3 step, FP64)"}.get(
-        form, f"hhlb::stage_kernel_mixed<16,2,0,{form_precision(H, form)}> (one RK-3 stage, {form})")
+    fp64 = form in ("fp64", "fp64_fused")
+    kname = ("hhlb::step_kernel<0,16,2,0> (one RK-3 step, FP64)" if fp64 else
+             f"hhlb::step_kernel_mixed<16,2,0,{form_precision(H, form)}> (one RK-3 step, {form})")
     roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(form),
             "kernel": kname, "algorithmic_bytes_per_node_update": bytes_per_node_update(form),

@@ -235,8 +235,8 @@ struct WenoWeights {
     pL = q2 * q3; pC = q1 * q3; pR = q1 * q2;
     dd = fma(0.5, pR, fma(1.0 / 6.0, pL, pC));
   }
-  __device__ __forceinline__ WenoWeights(double dm, double dp, double DL, double D, double DR, double qL, double qD,
-                                         double qR) {
+  __device__ __forceinline__ void form(double dm, double dp, double DL, double D, double DR, double qL, double qD,
+                                       double qR) {
     constexpr double h = 0.5 / kSq1312;
     const double tL = fma(h, DL, dm), tC = fma(h, D, dm), tR = fma(-h, DR, dp);
     sL = fma(tL, tL, qL); sC = fma(tC, tC, qD); sR = fma(tR, tR, qR);
@@ -263,29 +263,58 @@ struct WenoWeights {
   }
 };
 
-template <int ADV>
-__device__ __forceinline__ void faces_down2(double ya, double yb, bool usedA, bool usedB, double &fa, double &fb) {
-  const double da = yb - ya, db = dpp_shl1(ya) - yb, dm = dpp_shr1(db);
+// The same for G nodes at once: one branch for all of them, so that their
+// chains interleave.
+template <int ADV, int G>
+__device__ __forceinline__ void faces_down2(const double (&ya)[G], const double (&yb)[G], bool usedA, bool usedB,
+                                            double (&fa)[G], double (&fb)[G]) {
+  double da[G], db[G], dm[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    da[g] = yb[g] - ya[g];
+    db[g] = dpp_shl1(ya[g]) - yb[g];
+    dm[g] = dpp_shr1(db[g]);
+  }
   if constexpr (ADV == 0) {
-    const double Da = kSq1312 * (da - dm), Db = kSq1312 * (db - da);
-    const double Dl = dpp_shr1(Db), Dr = dpp_shl1(Da);
-    const double qa = Da * Da, qb = Db * Db, dab = Da - Db;
-    WenoWeights wa(dm, da, Dl, Da, Db, Dl * Dl, qa, qb), wb(da, db, Da, Db, Dr, qa, qb, Dr * Dr);
-    if ((!wa.regular() && usedA) || (!wb.regular() && usedB)) {
-      wa.rescale();
-      wb.rescale();
+    WenoWeights wa[G], wb[G];
+    double dl[G], dab[G], dr[G];
+    bool odd = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const double Da = kSq1312 * (da[g] - dm[g]), Db = kSq1312 * (db[g] - da[g]);
+      const double Dl = dpp_shr1(Db), Dr = dpp_shl1(Da);
+      const double qa = Da * Da, qb = Db * Db;
+      wa[g].form(dm[g], da[g], Dl, Da, Db, Dl * Dl, qa, qb);
+      wb[g].form(da[g], db[g], Da, Db, Dr, qa, qb, Dr * Dr);
+      dl[g] = Dl - Da;
+      dab[g] = Da - Db;
+      dr[g] = Db - Dr;
+      odd |= (!wa[g].regular() && usedA) || (!wb[g].regular() && usedB);
     }
-    fa = wa.face(dm, da, Dl - Da, dab, ya);
-    fb = wb.face(da, db, dab, Db - Dr, yb);
+    if (odd) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        wa[g].rescale();
+        wb[g].rescale();
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      fa[g] = wa[g].face(dm[g], da[g], dl[g], dab[g], ya[g]);
+      fb[g] = wb[g].face(da[g], db[g], dab[g], dr[g], yb[g]);
+    }
   } else {
-    fa = fma(1.0 / 3.0, da, fma(1.0 / 6.0, dm, ya));
-    fb = fma(1.0 / 3.0, db, fma(1.0 / 6.0, da, yb));
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      fa[g] = fma(1.0 / 3.0, da[g], fma(1.0 / 6.0, dm[g], ya[g]));
+      fb[g] = fma(1.0 / 3.0, db[g], fma(1.0 / 6.0, da[g], yb[g]));
+    }
   }
 }
 
 // nsteps steps of nst stages (3; or 1: one forward-Euler stage, for the
 // residual) of one window, run by a block of 2 NFUN waves.
-template <int QUAD, int Q, int NFUN, int ADV>
+template <int QUAD, int Q, int NFUN, int ADV, int GROUP>
 __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables *tb, const DevChannel *chans,
                                             const DevFusedWindow win, const double *__restrict__ inv_dx,
                                             const double *__restrict__ gw, const double *__restrict__ in_f,
@@ -608,29 +637,40 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     const double sdx0 = -dxi[0] * bdt, sdx1 = -dxi[1] * bdt;
     asm volatile("" : "+s"(tp));
 #pragma unroll
-    for (int j = 0; j < H; ++j) {
-      const double v = tp->p[j];
-      double fa, fb;
-      faces_down2<ADV>(y[j][0], y[j][1], use0, use1, fa, fb);
-      if (up) {   // the emergent flux at the wall is the wall's own
-        asm volatile("");
-        if (wf0) fa = y[j][0];
-        if (wf1) fb = y[j][1];
+    for (int j0 = 0; j0 < H; j0 += GROUP) {
+      constexpr int G = H % GROUP == 0 ? GROUP : 1;
+      static_assert(G == GROUP || GROUP == 1, "whole groups");
+      double ya[G], yb[G], fa[G], fb[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        ya[g] = y[j0 + g][0];
+        yb[g] = y[j0 + g][1];
       }
-      const double fu = dpp_shr1(fb);
-      y[j][0] = fma(a_s, yn[j][0], fma(sdx0 * v, fa - fu, src[j][0]));
-      double src1;
-      if constexpr (kMfma) {
-        const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
-        const double geq = s_geq[((hw * 2 + 1) * H + j) * 64 + lane];
-        src1 = fma(b_s, y[j][1], fma(nT[1], geq, fma(-cT[1], y[j][1], cF * k1)));
-      } else {
-        src1 = src[j][1];
+      faces_down2<ADV, G>(ya, yb, use0, use1, fa, fb);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int j = j0 + g;
+        const double v = tp->p[j];
+        if (up) {   // the emergent flux at the wall is the wall's own
+          asm volatile("");
+          if (wf0) fa[g] = ya[g];
+          if (wf1) fb[g] = yb[g];
+        }
+        const double fu = dpp_shr1(fb[g]);
+        y[j][0] = fma(a_s, yn[j][0], fma(sdx0 * v, fa[g] - fu, src[j][0]));
+        double src1;
+        if constexpr (kMfma) {
+          const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
+          const double geq = s_geq[((hw * 2 + 1) * H + j) * 64 + lane];
+          src1 = fma(b_s, yb[g], fma(nT[1], geq, fma(-cT[1], yb[g], cF * k1)));
+        } else {
+          src1 = src[j][1];
+        }
+        y[j][1] = fma(a_s, yn[j][1], fma(sdx1 * v, fb[g] - fa[g], src1));
+        // keep the update here: sunk below the later nodes it would hold their
+        // faces and y^n at once
+        asm volatile("" : "+v"(y[j][0]), "+v"(y[j][1]));
       }
-      y[j][1] = fma(a_s, yn[j][1], fma(sdx1 * v, fb - fa, src1));
-      // keep the update here: sunk below the later nodes it would hold their
-      // faces and y^n at once
-      asm volatile("" : "+v"(y[j][0]), "+v"(y[j][1]));
       __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (kMfma) __syncthreads();   // the next partials overwrite the tiles
@@ -656,14 +696,26 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
   if (wide && lane == 0 && A.wide) atomicAdd(A.wide, (unsigned long long)wide);
 }
 
-template <int QUAD, int Q, int NFUN, int ADV>
-__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(step_waves(QUAD == 0 ? Q : Q / 2)))) void
+// Two forms.  With many windows the registers are fitted to step_waves and the
+// faces formed a node at a time; with FEW the whole register file serves the
+// one or two blocks a CU holds anyway and the faces of two nodes interleave
+// (their chains bound a lone wave: at Q = 8 the advection takes 8900 of a
+// stage's 17000 cycles, 1100 a node for some 100 instructions).  16 steps of one channel
+// of 512 cells, Q = 8: 411 -> 381 us, 64 steps of HLB(15;16) 1521 -> 1442 us, 16
+// steps of 64 channels, Q = 12: 882 -> 855 us; groups of four 378, 1434 and
+// 1066 us (beyond 256 registers).
+constexpr int few_group(int H) { return H % 2 == 0 ? 2 : 1; }
+// waves per SIMD that fit with FEW: 8 H doubles and the faces of two nodes
+constexpr int few_waves(int H) { return H <= 12 ? 2 : 1; }
+template <int QUAD, int Q, int NFUN, int ADV, bool FEW>
+__global__ __launch_bounds__(128 * NFUN)
+__attribute__((amdgpu_waves_per_eu(FEW ? 1 : step_waves(QUAD == 0 ? Q : Q / 2)))) void
 step_kernel(StageArgs A, const DevTables *__restrict__ tb, const DevChannel *__restrict__ chans,
             const DevFusedWindow *__restrict__ wins, const double *__restrict__ inv_dx,
             const double *__restrict__ gw, const double *__restrict__ in_f, const double *__restrict__ in_c) {
   __shared__ double s_lds[step_lds_doubles<QUAD, Q, NFUN>()];
   const int w = A.xcd_map ? xcd_window(blockIdx.x, A.nwin) : (int)blockIdx.x;
-  step_window<QUAD, Q, NFUN, ADV>(A, tb, chans, wins[w], inv_dx, gw, in_f, in_c, s_lds);
+  step_window<QUAD, Q, NFUN, ADV, FEW ? few_group(QUAD == 0 ? Q : Q / 2) : 1>(A, tb, chans, wins[w], inv_dx, gw, in_f, in_c, s_lds);
 }
 
 // One launch for the windows of several half-range model classes that share
@@ -688,7 +740,7 @@ step_kernel_classes(StageArgs A, const DevTables *__restrict__ tbs, const DevCha
 #define HHLB_CLASS_CASE(q)                                                            \
   case q:                                                                             \
     if constexpr (q <= QTOP)                                                          \
-      step_window<0, q, NFUN, ADV>(A, tb, chans, win, inv_dx, gw, in_f, in_c, s_lds); \
+      step_window<0, q, NFUN, ADV, 1>(A, tb, chans, win, inv_dx, gw, in_f, in_c, s_lds); \
     break;
       HHLB_CLASS_CASE(1) HHLB_CLASS_CASE(2) HHLB_CLASS_CASE(3) HHLB_CLASS_CASE(4)
       HHLB_CLASS_CASE(6) HHLB_CLASS_CASE(8) HHLB_CLASS_CASE(12) HHLB_CLASS_CASE(16)

@@ -5,11 +5,28 @@
 namespace hhlb {
 namespace {
 
-template <int QUAD, int Q, int NF, int ADV>
-void launch_step(const StageArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL((step_kernel<QUAD, Q, NF, ADV>), dim3(a.nwin), dim3(128 * NF), 0, s, a, a.tb, a.chans,
+constexpr int kSimds = 1024;   // 256 CUs
+
+template <int QUAD, int Q, int NF, int ADV, bool FEW>
+void launch(const StageArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL((step_kernel<QUAD, Q, NF, ADV, FEW>), dim3(a.nwin), dim3(128 * NF), 0, s, a, a.tb, a.chans,
                      reinterpret_cast<const DevFusedWindow *>(a.wins), a.inv_dx, a.gw, (const double *)a.in_f,
                      (const double *)a.in_c);
+}
+
+template <int QUAD, int Q, int NF, int ADV>
+void launch_step(const StageArgs &a, hipStream_t s) {
+  // FEW where its waves all fit the GPU at once: beyond that the many-window
+  // form's third or fourth wave per SIMD is worth more.  Up to four nodes per
+  // half it gains nothing (607 against 613 us for 64 steps of a 64-cell channel).
+  constexpr int H = QUAD == 0 ? Q : Q / 2;
+  if constexpr (H > 4) {
+    if ((int64_t)a.nwin * 2 * NF <= (int64_t)kSimds * few_waves(H)) {
+      launch<QUAD, Q, NF, ADV, true>(a, s);
+      return;
+    }
+  }
+  launch<QUAD, Q, NF, ADV, false>(a, s);
 }
 
 template <int QUAD, int Q>
