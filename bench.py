@@ -568,7 +568,7 @@ def run_ballistic(H, torch, np, nx=24, steps=2000, warmup=32):
     return {"workload": f"HHLB(20;200) V=400, 8 channels (the paper's ballistic cases) x Nx={nx} "
                         "tanh-stretched (A=0.99), WENO5+RK3, Kn=inf, "
                         + ("dt=1e-4" if nx == 24 else "CFL 0.5") + ", f only, FP64, "
-                        "node-parallel stage (cell kernel + MFMA node kernel per RK stage)",
+                        "node-parallel stage (one MFMA launch per RK stage)",
             "value": nu * steps / (ms / 1e3), "unit": "node-updates/s",
             "ms_per_step": ms / steps, "steps": steps}
 

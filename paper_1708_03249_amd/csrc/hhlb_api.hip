@@ -361,7 +361,7 @@ struct hhlb_solver {
   // classes one after the other, XCD-aware window mapping by default
   hhlb_tuning tuning = {0, 0, 1, 2, 0, 0, 0.0f};
   // launches across classes (hhlb_tuning.merge_classes): FP64 half-range
-  // classes with the same functions and scheme take one launch per stage
+  // classes with the same functions and scheme take one launch per step
   struct MergeGroup {
     Launcher launch = nullptr;
     int qtop = 0;

@@ -1,12 +1,7 @@
-// gfx950 kernels for one TVD RK-3 stage of the half-range (HHLB) and
-// full-range (HLB) lattice Boltzmann models with a force term.
-//
-// Mapping: one 64-lane wavefront per "window" of 64 consecutive cells of one
-// channel; lanes 3..60 own the 58 output cells, lanes 0..2 and 61..63 are the
-// 3-cell halo of the WENO-5 stencil.  Each lane keeps every velocity node of
-// its cell in registers (structure-of-arrays loads, one coalesced row per
-// node), so the per-cell algebra (moments, equilibrium, force matrix, BGK) is
-// lane-local and the x-neighbours of the stencil come from DPP wave shifts.
+// Records, lane moves and face values shared by the kernels of the half-range
+// (HHLB) and full-range (HLB) lattice Boltzmann models with a force term: the
+// tables of a model class, channels and windows, WENO-5 / upwind-3 faces of
+// lanes that run down the wind, rows as buffer resources, the block map.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -20,7 +15,7 @@ constexpr int kComposite = 6;  // beyond them: the top count on 2, 4, .., 64 pan
 constexpr int kLadderAll = kLadder + kComposite;
 constexpr int kLadderTop = 16; // the top calibrated count
 constexpr int kLadderPts = 64 + kLadderTop * (2 + 4 + 8 + 16 + 32 + 64);   // points over all entries
-constexpr int kWin = 58;       // output cells per wavefront
+constexpr int kWin = 58;       // most output cells of a window of the node-parallel stage (64 lanes)
 
 constexpr int kHalo = 3;
 

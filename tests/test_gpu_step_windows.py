@@ -91,3 +91,24 @@ def test_mixed_window_edges(form, Q, dof, nsteps):
     assert gpu["bad"] == 0
     e = moment_errors(chans, gpu, run_oracle(chans, states, nsteps, gpu["dt"]))
     assert max(e.values()) <= 1e-5, (form, e)
+
+
+@pytest.mark.parametrize("quad,Q,dof,adv", [("HALF_HERMITE", 6, 0, "WENO5"), ("HALF_HERMITE", 8, 2, "WENO5"),
+                                            ("HALF_HERMITE", 12, 2, "UPWIND3"), ("HALF_HERMITE", 16, 2, "WENO5"),
+                                            ("HALF_HERMITE", 16, 0, "WENO5"), ("FULL_HERMITE", 16, 2, "WENO5")])
+@pytest.mark.parametrize("over", [0, 1])
+def test_few_and_many_windows(quad, Q, dof, adv, over):
+    """The FP64 kernel's two forms on either side of the launch size where they
+    change: as many one-window channels as the few-window form takes (512
+    windows of four waves at two waves per SIMD, half of that at Q = 16, twice
+    that for f alone), and one more.  The first, a middle and the last channel
+    against the oracle."""
+    import paper_1708_03249_amd as H
+    n = 512 // (2 if quad == "HALF_HERMITE" and Q == 16 else 1) * (1 if dof else 2) + over
+    chans = [H.Channel(quad=getattr(H, quad), Q=Q, Nx=16, adv=getattr(H, adv), transverse_dof=dof,
+                       Kn=0.05 * (1 + k % 3), g=-0.4, T_right=1.3, dt=-0.5) for k in range(n)]
+    states = initial_states(chans, seed=53, perturb=0.03)
+    gpu = run_gpu(chans, states, 3)
+    assert gpu["bad"] == 0
+    ref = run_oracle(chans, states, 3, gpu["dt"], which=[0, n // 2, n - 1])
+    compare(chans, gpu, ref, tol=1e-12, what=f"{quad} Q={Q} dof={dof}: {n} windows")
