@@ -330,6 +330,11 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
   const int Nx = cp->Nx, c0 = win.c0;
   const double sg = hw ? -1.0 : 1.0;
   constexpr bool kMfma = step_mfma<QUAD, Q>();
+  // Shared arrays, by the barrier of a stage behind which they are read: the
+  // partials, s_nw and (full range) the populations s_y behind the first, the
+  // equilibrium s_geq behind the second.  Partials and s_nw are read before the
+  // second barrier, so the next stage may write them; s_y, and the tiles in the
+  // partials' memory, are read after it: a third barrier ends the stage.
   double *s_part = s_lds, *s_tile = s_lds + wv * H * 64;   // the tile: matrix cores only
   double *s_geq = s_lds + (step_lds_doubles<QUAD, Q, NFUN>() - 2 - 2 * 2 * H * 64 - (QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells));
   double *s_y = s_geq + 2 * 2 * H * 64;
@@ -673,7 +678,9 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (kMfma) __syncthreads();   // the next partials overwrite the tiles
+    // the next stage's partials overwrite the tiles, its populations the rows of
+    // s_y that the other half's waves read in pass 1
+    if constexpr (kMfma || QUAD == 1) __syncthreads();
     if (st == 2 && it + 1 < A.nsteps * A.nst) {
 #pragma unroll
       for (int j = 0; j < H; ++j)
