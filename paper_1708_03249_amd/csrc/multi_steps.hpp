@@ -144,13 +144,15 @@ __attribute__((amdgpu_waves_per_eu(NX <= 8 && NM <= 7 ? HHLB_MULTI_STEPS_OCC : 1
   const int ppw = 64 / P;
   const bool pow2 = (P & (P - 1)) == 0;
   // the lane's point and its y and z velocity; lanes past the last whole
-  // point of the wave repeat the first one's and store nothing
+  // point of the wave repeat the first one's, lanes past the last point of all
+  // that one's, and store nothing
   int seg0 = lane0 / P;
   const int sub = lane0 - seg0 * P;
   const bool spare = seg0 >= ppw;
   if (spare) seg0 = 0;
   const int j0 = d == 3 ? sub / Vz : 0, k0 = sub - j0 * Vz;
-  const int64_t pt0 = ((int64_t)blockIdx.x * kMultiWaves + wave) * ppw + seg0;
+  const int64_t pt_wave = ((int64_t)blockIdx.x * kMultiWaves + wave) * ppw;   // the wave's first point
+  const int64_t pt0 = pt_wave + seg0;
   const bool valid = !spare && pt0 < A.npts;
   const int64_t pt = pt0 < A.npts ? pt0 : A.npts - 1;
 
@@ -177,6 +179,9 @@ __attribute__((amdgpu_waves_per_eu(NX <= 8 && NM <= 7 ? HHLB_MULTI_STEPS_OCC : 1
     stage_rows(s_hx, 0, H0);
   }
   __syncthreads();
+  // (in, out) may be the same array: a wave without a point would read the last
+  // one while its own wave stores it
+  if (pt_wave >= A.npts) return;
   const double py = d == 3 ? A.tab[tm->p_off[1] + j0] : 0.0, pz = A.tab[tm->p_off[az] + k0];
   double kq[4];   // z matrix entries of the quad's lanes
   if constexpr (QZ) {

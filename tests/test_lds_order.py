@@ -1,11 +1,16 @@
-"""The step kernels' shared memory: in the loop over the stages, as it stands in
+"""The order of memory accesses in the step kernels, read from the source.
+
+Shared memory: in the loop over the stages, as it stands in
 the source, every two accesses that different waves may make to one array, one
 of them a write, have a barrier between them, also across the end of a stage
 and the start of the next.  A missing barrier shows in no result reliably (a
 wave would have to fall behind by most of a stage), so the order is read here.
 
 The loop's text is taken as straight-line code: `if constexpr` and the collision
-switch are resolved for each kind of kernel, other branches count as taken."""
+switch are resolved for each kind of kernel, other branches count as taken.
+
+Populations stepped in place (App. A): lanes without a point of their own read
+another lane's, so that lane has to be of the same wave."""
 import os
 import re
 
@@ -139,3 +144,14 @@ def test_a_removed_barrier_is_found():
     loop = resolve(stage_loop("fused_kernels.hpp"), env)
     for m in re.finditer(r"__syncthreads\(\);", loop):
         assert conflicts(loop[:m.start()] + loop[m.end():], False, True), loop[m.start() - 200:m.end()]
+
+
+def test_waves_without_a_point_read_none():
+    with open(os.path.join(CSRC, "multi_steps.hpp")) as fh:
+        text = re.sub(r"//[^\n]*", "", fh.read())
+    body = text[text.index("multi_steps_kernel(MultiArgs A)"):]
+    load = body.index("A.in + pt * V")
+    assert "pt0 < A.npts ? pt0 : A.npts - 1" in body[:load]   # the last point stands in
+    leave = body.index("if (pt_wave >= A.npts) return;")
+    last_barrier = max(m.start() for m in re.finditer(r"__syncthreads\(\)", body[:body.index("inline size_t")]))
+    assert last_barrier < leave < load
