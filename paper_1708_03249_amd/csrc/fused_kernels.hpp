@@ -330,11 +330,12 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
   const int Nx = cp->Nx, c0 = win.c0;
   const double sg = hw ? -1.0 : 1.0;
   constexpr bool kMfma = step_mfma<QUAD, Q>();
-  // Shared arrays, by the barrier of a stage behind which they are read: the
-  // partials, s_nw and (full range) the populations s_y behind the first, the
-  // equilibrium s_geq behind the second.  Partials and s_nw are read before the
-  // second barrier, so the next stage may write them; s_y, and the tiles in the
-  // partials' memory, are read after it: a third barrier ends the stage.
+  // Shared arrays: the partials, s_nw and (full range) the populations s_y are
+  // written before the first barrier of a stage and read behind it, before the
+  // last, so the next stage may write them; the energy's partial and its barrier
+  // lie between (full range); s_geq is written before the last barrier and read
+  // behind it.  The tiles, in the partials' memory, are read to the end of the
+  // stage, which then ends with a barrier.
   double *s_part = s_lds, *s_tile = s_lds + wv * H * 64;   // the tile: matrix cores only
   double *s_geq = s_lds + (step_lds_doubles<QUAD, Q, NFUN>() - 2 - 2 * 2 * H * 64 - (QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells));
   double *s_y = s_geq + 2 * 2 * H * 64;
@@ -441,15 +442,19 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           for (int s = 0; s < SLOTS; ++s) {
             m0[s] += y[j][s];
             m1[s] = fma(tp->p[j], y[j][s], m1[s]);
-            m2[s] = fma(tp->vv[j], y[j][s], m2[s]);
-            if constexpr (QUAD == 0) mb[s] = fma(tp->kb[j], y[j][s], mb[s]);
+            if constexpr (QUAD == 0) {
+              m2[s] = fma(tp->vv[j], y[j][s], m2[s]);
+              mb[s] = fma(tp->kb[j], y[j][s], mb[s]);
+            }
           }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           part(hw, 0, s) = m0[s];
           part(hw, 1, s) = sg * m1[s];
-          part(hw, 2, s) = m2[s];
-          part(hw, 3, s) = mb[s];
+          if constexpr (QUAD == 0) {
+            part(hw, 2, s) = m2[s];
+            part(hw, 3, s) = mb[s];
+          }
         }
       } else {
 #pragma unroll
@@ -462,7 +467,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           part(hw, 4, s) = m0[s];
-          part(hw, 5, s) = mb[s];
+          if constexpr (QUAD == 0) part(hw, 5, s) = mb[s];
         }
       }
     }
@@ -495,25 +500,54 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       if (hw == 0 && needR) A.nwall[2 * win.ch + 1] = nw_mine;
     }
 
-    // ---- moments (Eq. fmoms) ----
-    double n[SLOTS], u[SLOTS], T[SLOTS], bp[SLOTS];
+    // ---- moments (Eq. fmoms).  Half range: the energy from raw sums.  Full
+    // range: about u, its partials behind a barrier of their own (raw sums
+    // cancel, 2 to 5 times the rounding of T at |u| near 1) ----
+    const bool collide = cp->inv_Kn != 0.0;
+    double n[SLOTS], u[SLOTS], T[SLOTS], bp[SLOTS], rn[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
       const double ns = part(0, 0, s) + part(1, 0, s), mom = part(0, 1, s) + part(1, 1, s);
-      const double s2 = part(0, 2, s) + part(1, 2, s);
-      double ech = 0.0;
-      if constexpr (NFUN > 1) ech = part(0, 4, s) + part(1, 4, s);
       bp[s] = QUAD == 0 ? part(0, fn ? 5 : 3, s) + part(1, fn ? 5 : 3, s) : 0.0;
-      const double rn = recip(ns);
+      rn[s] = recip(ns);
       n[s] = inside[s] ? ns : 1.0;
-      u[s] = inside[s] ? mom * rn : 0.0;
-      T[s] = inside[s] ? fma(2.0, ech, fma(-u[s], mom, s2)) * (cp->inv_1pDt * rn) : 1.0;
+      u[s] = inside[s] ? mom * rn[s] : 0.0;
+      T[s] = 1.0;
+      if constexpr (QUAD == 0) {
+        const double s2 = part(0, 2, s) + part(1, 2, s);
+        double ech = 0.0;
+        if constexpr (NFUN > 1) ech = part(0, 4, s) + part(1, 4, s);
+        if (inside[s]) T[s] = fma(2.0, ech, fma(-u[s], mom, s2)) * (cp->inv_1pDt * rn[s]);
+      }
+    }
+    if constexpr (QUAD == 1) {
+      if (collide) {   // uniform over the block
+        if (fn == 0) {
+          double e2[SLOTS] = {0.0, 0.0};
+#pragma unroll
+          for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) {
+              const double c = fma(sg, tp->p[j], -u[s]);
+              e2[s] = fma(c * c, y[j][s], e2[s]);
+            }
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) part(hw, 2, s) = e2[s];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          const double e2 = part(0, 2, s) + part(1, 2, s);
+          double ech = 0.0;
+          if constexpr (NFUN > 1) ech = part(0, 4, s) + part(1, 4, s);
+          if (inside[s]) T[s] = fma(2.0, ech, e2) * (cp->inv_1pDt * rn[s]);
+        }
+      }
     }
 
     // ---- equilibrium populations g_k of this half: with f and chi, each of
     // the half's two waves takes one slot ----
     asm volatile("" : "+s"(tp), "+s"(cp));
-    const bool collide = cp->inv_Kn != 0.0;
     if (collide) {
 #pragma unroll 1
       for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 ? fn + 1 : SLOTS); ++e) {
@@ -550,6 +584,16 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           }
         }
       }
+    }
+    // full range: the other half's populations, read while they are those of
+    // this stage (its waves write the next ones behind the barrier)
+    double yo[QUAD == 1 ? H : 1][SLOTS];
+    if constexpr (QUAD == 1) {
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+          yo[j][s] = s_y[((fn * 2 * H + (1 - hw) * H + j) * 2 + plane[s]) * 64 + pl];
     }
     __syncthreads();
 
@@ -593,12 +637,6 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
         src[j][1] = k1;
       }
     } else {
-      double yo[H][SLOTS];   // the other half
-#pragma unroll
-      for (int j = 0; j < H; ++j)
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-          yo[j][s] = s_y[((fn * 2 * H + (1 - hw) * H + j) * 2 + plane[s]) * 64 + pl];
       const __attribute__((address_space(4))) double *Kr = tp->Kin + hw * H * Q;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
@@ -678,9 +716,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // the next stage's partials overwrite the tiles, its populations the rows of
-    // s_y that the other half's waves read in pass 1
-    if constexpr (kMfma || QUAD == 1) __syncthreads();
+    if constexpr (kMfma) __syncthreads();   // the next partials overwrite the tiles
     if (st == 2 && it + 1 < A.nsteps * A.nst) {
 #pragma unroll
       for (int j = 0; j < H; ++j)

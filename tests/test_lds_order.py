@@ -92,8 +92,12 @@ def events(text):
             pair = "()" if word == "part(" else "[]"
             rest = text[closing(text, m.end() - 1, pair) + 1:].lstrip()
             kind = "write" if rest.startswith("=") and not rest.startswith("==") else "read"
-            name = word[:-1]
-            yield ("s_geq" if name == "ge" else name), kind
+            if word == "part(":   # one array per sum, the second argument
+                which = text[m.end():closing(text, m.end() - 1, pair)].split(",")[1]
+                for q in re.findall(r"\d", which):
+                    yield "part" + q, kind
+            else:
+                yield {"ge[": "s_geq"}.get(word, word[:-1]), kind
 
 
 def conflicts(loop, alias, collide):
@@ -101,10 +105,10 @@ def conflicts(loop, alias, collide):
     def clash(a, b):
         if a[0] == b[0]:
             return a[0] != "tile" and {a[1], b[1]} == {"read", "write"}
-        return alias and {a[0], b[0]} == {"part", "tile"}
+        return alias and {a[0][:4], b[0][:4]} == {"part", "tile"}
     found, open_ = set(), []
     once = list(events(loop))
-    assert any(e == ("part", "write") for e in once) and any(e[0] == "barrier" for e in once)
+    assert ("part0", "write") in once and any(e[0] == "barrier" for e in once)
     for e in once + once:
         if e[0] == "barrier":
             open_ = []
