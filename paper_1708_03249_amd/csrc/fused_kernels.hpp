@@ -312,8 +312,8 @@ __device__ __forceinline__ void faces_down2(const double (&ya)[G], const double 
   }
 }
 
-// nsteps steps of nst stages (3; or 1: one forward-Euler stage, for the
-// residual) of one window, run by a block of 2 NFUN waves.
+// nsteps steps of nst stages (3; or 1: one forward-Euler stage, whose increment
+// dt L[y^n] goes to the output, for the residual) of one window, run by a block of 2 NFUN waves.
 template <int QUAD, int Q, int NFUN, int ADV, int GROUP>
 __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables *tb, const DevChannel *chans,
                                             const DevFusedWindow win, const double *__restrict__ inv_dx,
@@ -597,16 +597,16 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     }
     __syncthreads();
 
-    // ---- pass 1: b y + b dt (-F (K y)_k - (y_k - y^eq_k)/tau) ----
+    // ---- pass 1: b dt (-F (K y)_k + (y^eq_k - y_k)/tau), the difference formed
+    // first and b y added last, each rounded once at its own size ----
     asm volatile("" : "+s"(tp), "+s"(cp));
-    const double bdt = b_s * cp->dt;
+    const double bdt = b_s * cp->dt, b_y = A.nst == 1 ? 0.0 : b_s;   // the one stage for the residual: its increment
     const double cF = -cp->g * (QUAD == 0 ? sg : 1.0) * bdt;
-    double cT[SLOTS], nT[SLOTS];
+    double cT[SLOTS], nq[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
       cT[s] = n[s] * cp->inv_Kn * bdt;
-      nT[s] = n[s] * cT[s];
-      if (fn == 1) nT[s] *= cp->half_Dt * T[s];
+      nq[s] = fn == 1 ? n[s] * (cp->half_Dt * T[s]) : n[s];
     }
     // matrix cores: the second slot's force block stays in the tile until
     // pass 2 reads it, which keeps H values out of the register file
@@ -657,14 +657,13 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 #pragma unroll
         for (int s = 0; s < SREG; ++s) {
           const double geq = s_geq[((hw * 2 + s) * H + j) * 64 + lane];
-          const double v = fma(nT[s], geq, fma(-cT[s], y[j][s], cF * src[j][s]));
-          src[j][s] = fma(b_s, y[j][s], v);
+          src[j][s] = fma(cT[s], fma(nq[s], geq, -y[j][s]), cF * src[j][s]);
         }
     } else {
 #pragma unroll
       for (int j = 0; j < H; ++j)
 #pragma unroll
-        for (int s = 0; s < SREG; ++s) src[j][s] = fma(cF, src[j][s], b_s * y[j][s]);
+        for (int s = 0; s < SREG; ++s) src[j][s] *= cF;
       if constexpr (kMfma) {   // pass 2 reads the second slot's equilibrium
 #pragma unroll
         for (int j = 0; j < H; ++j) s_geq[((hw * 2 + 1) * H + j) * 64 + lane] = 0.0;
@@ -700,16 +699,16 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           if (wf1) fb[g] = yb[g];
         }
         const double fu = dpp_shr1(fb[g]);
-        y[j][0] = fma(a_s, yn[j][0], fma(sdx0 * v, fa[g] - fu, src[j][0]));
+        y[j][0] = fma(a_s, yn[j][0], fma(b_y, ya[g], fma(sdx0 * v, fa[g] - fu, src[j][0])));
         double src1;
         if constexpr (kMfma) {
           const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
           const double geq = s_geq[((hw * 2 + 1) * H + j) * 64 + lane];
-          src1 = fma(b_s, yb[g], fma(nT[1], geq, fma(-cT[1], yb[g], cF * k1)));
+          src1 = fma(cT[1], fma(nq[1], geq, -yb[g]), cF * k1);
         } else {
           src1 = src[j][1];
         }
-        y[j][1] = fma(a_s, yn[j][1], fma(sdx1 * v, fb[g] - fa[g], src1));
+        y[j][1] = fma(a_s, yn[j][1], fma(b_y, yb[g], fma(sdx1 * v, fb[g] - fa[g], src1)));
         // keep the update here: sunk below the later nodes it would hold their
         // faces and y^n at once
         asm volatile("" : "+v"(y[j][0]), "+v"(y[j][1]));

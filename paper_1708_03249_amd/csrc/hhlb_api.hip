@@ -189,13 +189,12 @@ __global__ void mass_kernel(const hhlb::DevTables *tbs, const int32_t *ch_class,
 }
 
 // Residual per channel: max over f (and chi) of ||y1 - y||_inf / (dt ||y||_inf)
-// with y1 = y + dt L[y] one forward-Euler stage from the current state.
-// d1 holds y1 (FP64 form) or the increment y1 - y (mixed form).
+// with y1 = y + dt L[y] one forward-Euler stage from the current state; df1 and
+// dc1 hold the increments y1 - y.
 template <typename S>
 __global__ void residual_kernel(const hhlb::DevTables *tbs, const int32_t *ch_class,
                                 const hhlb::DevChannel *chans, const int32_t *ch_V, int n_ch, int scaled,
-                                int increment, const S *f, const S *f1, const S *c, const S *c1, int has_chi,
-                                double *res) {
+                                const S *f, const S *df1, const S *c, const S *dc1, int has_chi, double *res) {
   const int ch = blockIdx.x;
   if (ch >= n_ch) return;
   const hhlb::DevChannel C = chans[ch];
@@ -207,13 +206,11 @@ __global__ void residual_kernel(const hhlb::DevTables *tbs, const int32_t *ch_cl
   const int64_t total = (int64_t)V * C.Nx;
   for (int64_t j = threadIdx.x; j < total; j += blockDim.x) {
     const double sc = node_scale(tb, V, (int)(j / C.Nx), scaled);
-    const double y = (double)f[C.off + j], y1 = (double)f1[C.off + j];
-    df = fmax(df, sc * fabs(increment ? y1 : y1 - y));
-    nf = fmax(nf, sc * fabs(y));
+    df = fmax(df, sc * fabs((double)df1[C.off + j]));
+    nf = fmax(nf, sc * fabs((double)f[C.off + j]));
     if (chi) {
-      const double x = (double)c[C.off + j], x1 = (double)c1[C.off + j];
-      dc = fmax(dc, sc * fabs(increment ? x1 : x1 - x));
-      nc = fmax(nc, sc * fabs(x));
+      dc = fmax(dc, sc * fabs((double)dc1[C.off + j]));
+      nc = fmax(nc, sc * fabs((double)c[C.off + j]));
     }
   }
   part[0][threadIdx.x] = df; part[1][threadIdx.x] = nf;
@@ -342,8 +339,8 @@ struct hhlb_solver {
   int max_tiles = 0;
   char *ws = nullptr;
   // stored state: hi[par] = y^n, a ping-pong pair (par flips every step), C a
-  // stage value or the residual's Euler stage.  Mixed form: hi[par] + lo[par] =
-  // y^n as FP32 value and 16-bit correction word, C = the Euler stage's
+  // stage value or the increment of the residual's Euler stage.  Mixed form:
+  // hi[par] + lo[par] = y^n as FP32 value and 16-bit correction word, C = that
   // increment in FP32.
   void *hiF[2] = {nullptr, nullptr}, *hiC[2] = {nullptr, nullptr};
   int16_t *loF[2] = {nullptr, nullptr}, *loC[2] = {nullptr, nullptr};
@@ -1248,20 +1245,21 @@ void enqueue_class_sums(hhlb_solver *s, size_t ci, int b, const void *inf, const
 
 // Enqueue one RK stage of class ci; the partial sums of its input are in buffer b.
 void enqueue_class_stage(hhlb_solver *s, size_t ci, int stage, int b, const void *inf, const void *inc, void *outf,
-                         void *outc, double a_base, double b_stage, hipStream_t stream) {
+                         void *outc, double a_base, double b_stage, hipStream_t stream, int increment = 0) {
   const ModelClass &mc = s->classes[ci];
   hhlb::LargeArgs la = large_args(s, ci, b, inf, inc);
   la.stage = stage;
+  la.increment = increment;
   la.out_f = (double *)outf; la.out_c = (double *)outc;
   la.a_base = a_base;
   la.b_stage = b_stage;
   hhlb::launch_large(la, mc.adv, mc.Dt > 0 ? 2 : 1, mc.rule.H, mc.max_out, stream);
 }
 
-// nsteps RK-3 steps (nst = 3), or one forward-Euler stage (nsteps = nst = 1),
-// of model class ci in one launch of the step kernel: y^n from copy p, the
-// result to (outf, outc) (mixed forms: its correction words to copy q, or the
-// increment of the one stage).  nsteps > 1 needs a class whose every channel
+// nsteps RK-3 steps (nst = 3), or the increment of one forward-Euler stage
+// (nsteps = nst = 1), of model class ci in one launch of the step kernel: y^n
+// from copy p, the result to (outf, outc) (mixed forms: the correction words of
+// a step to copy q).  nsteps > 1 needs a class whose every channel
 // is one window.  With gi >= 0: of the classes of merge group gi.
 void enqueue_class_step(hhlb_solver *s, size_t ci, int gi, int nsteps, int nst, int p, int q, void *outf, void *outc,
                         hipStream_t stream) {
@@ -1302,14 +1300,15 @@ void enqueue_group_step(hhlb_solver *s, size_t gi, hipStream_t stream) {
   enqueue_class_step(s, 0, (int)gi, 1, 3, p, q, s->hiF[q], s->hiC[q], stream);
 }
 
-// The first RK stage (a forward-Euler stage) of every class from the current
-// state to (outf, outc), on one stream (mixed forms: its increment).
+// The increment dt L[y] of the first RK stage (a forward-Euler stage) of every
+// class from the current state to (outf, outc), on one stream.  Not y + dt L[y]:
+// rounding that costs eps/dt of y, 2 % of a residual of 1e-10 at dt = 5e-5.
 void enqueue_euler(hhlb_solver *s, void *outf, void *outc, hipStream_t stream) {
   for (size_t ci = 0; ci < s->classes.size(); ++ci) {
     if (s->classes[ci].step) enqueue_class_step(s, ci, -1, 1, 1, s->par, s->par ^ 1, outf, outc, stream);
     else {
       enqueue_class_sums(s, ci, 0, s->fA(), s->cA(), stream);
-      enqueue_class_stage(s, ci, 0, 0, s->fA(), s->cA(), outf, outc, 0.0, 1.0, stream);
+      enqueue_class_stage(s, ci, 0, 0, s->fA(), s->cA(), outf, outc, 0.0, 1.0, stream, 1);
     }
   }
 }
@@ -1619,17 +1618,17 @@ hhlb_status hhlb_diagnostics(hhlb_solver *s, double *n_wall_dev, double *mass_de
     HIP_TRY(hipMemcpyAsync(n_wall_dev, s->ws + s->o_nwall, sizeof(double) * 2 * n_ch, hipMemcpyDeviceToDevice,
                            s->stream));
   if (residual_dev) {
-    // one forward-Euler stage from the current state into the C copies; the
+    // the increment of one forward-Euler stage into the C copies; the
     // state (A) and the wall densities are left untouched
     if (s->mixed()) {
       enqueue_euler(s, s->fC, s->cC, s->stream);
       hipLaunchKernelGGL(residual_kernel<float>, dim3(n_ch), dim3(256), 0, s->stream, a.tbs, a.ch_class, a.chans,
-                         a.ch_V, a.n_ch, a.scaled, 1, (const float *)s->fA(), (const float *)s->fC,
+                         a.ch_V, a.n_ch, a.scaled, (const float *)s->fA(), (const float *)s->fC,
                          (const float *)s->cA(), (const float *)s->cC, hc, residual_dev);
     } else {
       enqueue_euler(s, s->fC, s->cC, s->stream);
       hipLaunchKernelGGL(residual_kernel<double>, dim3(n_ch), dim3(256), 0, s->stream, a.tbs, a.ch_class, a.chans,
-                         a.ch_V, a.n_ch, a.scaled, 0, (const double *)s->fA(), (const double *)s->fC,
+                         a.ch_V, a.n_ch, a.scaled, (const double *)s->fA(), (const double *)s->fC,
                          (const double *)s->cA(), (const double *)s->cC, hc, residual_dev);
     }
     HIP_TRY(hipGetLastError());

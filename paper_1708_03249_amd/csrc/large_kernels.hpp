@@ -63,6 +63,7 @@ struct LargeArgs {
   double *nwall;                  // diagnostics copy (written in stage 2)
   unsigned long long *wide;       // cells whose equilibrium needed several correction panels
   int32_t xcd_map;                // 1: the tiles of a window run on one XCD
+  int32_t increment;              // 1: out = b dt L[in] (the residual), the sums of which nobody reads
 };
 
 // Sum over aligned segments of W lanes (W = 64: the whole wave).
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
       if (wall_face) fv = y0v;
       const double fo = dpp_shr1(fv);
       const double L = fma(-dx_inv * v, fv - fo, src);
-      const double yn = A.a_base * (fn == 0 ? bf0[q] : bc0[q]) + A.b_stage * (y0v + C.dt * L);
+      const double yn = A.a_base * (fn == 0 ? bf0[q] : bc0[q]) + A.b_stage * ((A.increment ? 0.0 : y0v) + C.dt * L);
       if (out_lane) (fn == 0 ? A.out_f : A.out_c)[o] = yn;
       (fn == 0 ? yf : yc)[q] = yn;
     }
