@@ -311,6 +311,9 @@ struct ModelClass {
   // Q > 16 (half-range Hermite, FP64): the node-parallel stage, whose tables
   // (DevLarge, then KinT and HWs) live in their own workspace block
   bool large = false;
+  int tiles = 0;       // of 16 nodes, over both halves
+  int32_t cells = 0;   // of its channels
+  size_t sums_at = 0;  // its partial sums (doubles) in either buffer
   std::vector<char> lblob;
   size_t lbl_off = 0;
 };
@@ -884,7 +887,8 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
           mc.large = true;
           st = make_large_tables(h, N, mc.rule, mc.dev, mc.lblob);
           if (st) return st;
-          s->max_tiles = std::max(s->max_tiles, 2 * ((mc.rule.H + hhlb::kTileNodes - 1) / hhlb::kTileNodes));
+          mc.tiles = 2 * ((mc.rule.H + hhlb::kTileNodes - 1) / hhlb::kTileNodes);
+          s->max_tiles = std::max(s->max_tiles, mc.tiles);
         } else {
           // both half-range kinds run the half-range kernels (tables differ)
           const int kq = hhlb::half_range(h.quad) ? HHLB_HALF_HERMITE : HHLB_FULL_HERMITE;
@@ -948,6 +952,8 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       d.off = s->off[c];
       d.Nx = h.Nx;
       d.cell_off = s->cell_off[c];
+      d.sum_off = mc.cells;
+      mc.cells += h.Nx;
       d.gw_off = (int32_t)s->gw.size();
       for (double v : gL) s->gw.push_back(v);
       for (double v : gR) s->gw.push_back(v);
@@ -1029,9 +1035,15 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
     s->o_wide = take(sizeof(unsigned long long));
     for (auto &mc : s->classes)
       if (mc.large) mc.lbl_off = take(mc.lblob.size());
+    size_t sums = 0;   // each class has the room its own tiles and cells need
+    for (auto &mc : s->classes)
+      if (mc.large) {
+        mc.sums_at = sums;
+        sums += (size_t)mc.tiles * hhlb::kSums * mc.cells;
+      }
     if (s->max_tiles)
       for (int b = 0; b < 2; ++b) {
-        s->o_sums[b] = take(sizeof(double) * s->max_tiles * hhlb::kSums * s->total_cells);
+        s->o_sums[b] = take(sizeof(double) * sums);
         s->o_wall[b] = take(sizeof(double) * s->max_tiles * n_ch);
       }
     s->o_state = o;
@@ -1225,11 +1237,11 @@ hhlb::LargeArgs large_args(hhlb_solver *s, size_t ci, int b, const void *inf, co
   la.gw = (const double *)(s->ws + s->o_gw);
   la.in_f = (const double *)inf; la.in_c = (const double *)inc;
   la.base_f = (const double *)s->fA(); la.base_c = (const double *)s->cA();
-  la.sums_in = (const double *)(s->ws + s->o_sums[b]);
+  la.sums_in = (const double *)(s->ws + s->o_sums[b]) + mc.sums_at;
   la.wall_in = (const double *)(s->ws + s->o_wall[b]);
-  la.sums_out = (double *)(s->ws + s->o_sums[b ^ 1]);
+  la.sums_out = (double *)(s->ws + s->o_sums[b ^ 1]) + mc.sums_at;
   la.wall_out = (double *)(s->ws + s->o_wall[b ^ 1]);
-  la.ncells = (int32_t)s->total_cells;
+  la.ncells = mc.cells;
   la.nch = (int32_t)s->ch.size();
   la.nwall = (double *)(s->ws + s->o_nwall);
   la.wide = (unsigned long long *)(s->ws + s->o_wide);

@@ -55,8 +55,8 @@ struct LargeArgs {
   const double *base_f, *base_c;  // y^n
   double *out_f, *out_c;
   double a_base, b_stage;
-  // partial sums of the state read and of the state written: per cell
-  // [tile][sum][cell], per wall [tile][channel]
+  // partial sums of the state read and of the state written: per cell of the
+  // class [tile][sum][cell], per wall [tile][channel]
   const double *sums_in, *wall_in;
   double *sums_out, *wall_out;
   int32_t ncells, nch;
@@ -213,7 +213,7 @@ struct LargeNodes {
 // s_wall (kNodeWaves) to memory.  Called by every wave of the block.
 template <int ADV>
 __device__ __forceinline__ void emit_sums(const LargeArgs &A, const LargePlace &P, const LargeNodes &K, int Nx,
-                                          int cell_off, int nfun, bool collide, const double (&y)[kWaveNodes],
+                                          int sum_off, int nfun, bool collide, const double (&y)[kWaveNodes],
                                           const double (&x)[kWaveNodes], double *s_sum, double *s_wall) {
   const double sg = P.hw ? -1.0 : 1.0;
   double m[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -256,7 +256,7 @@ __device__ __forceinline__ void emit_sums(const LargeArgs &A, const LargePlace &
 #pragma unroll
     for (int w = 0; w < kNodeWaves; ++w) v += s_sum[(w * kSums + q) * 64 + r];
     if (r >= kHalo && r < kHalo + P.win.nout)
-      A.sums_out[((int64_t)P.ty * kSums + q) * A.ncells + cell_off + P.win.i0 - kHalo + r] = v;
+      A.sums_out[((int64_t)P.ty * kSums + q) * A.ncells + sum_off + P.win.i0 - kHalo + r] = v;
   }
   if (wall && threadIdx.x == 0) {
     double v = 0.0;
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(64 * kNodeWaves) void large_sums_kernel(LargeArgs A
     y[q] = ok ? A.in_f[o] : 0.0;
     x[q] = NFUN > 1 && ok ? A.in_c[o] : 0.0;
   }
-  emit_sums<ADV>(A, P, K, Nx, C->cell_off, NFUN, C->inv_Kn != 0.0, y, x, s_sum, s_wall);
+  emit_sums<ADV>(A, P, K, Nx, C->sum_off, NFUN, C->inv_Kn != 0.0, y, x, s_sum, s_wall);
 }
 
 // One stage.  The rows of the contraction D[node][cell] = sum_j K[node][j]
@@ -313,8 +313,8 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
   const LargePlace P(A, H);
   const LargeNodes K(A, P);
   ConstChannel cp = (ConstChannel)A.chans + P.win.ch;
-  struct { int64_t off; int32_t Nx, cell_off, gw_off; double g, inv_Kn, dt, TL, TR, inv_DL, inv_DR, half_Dt, inv_1pDt; } C{
-      cp->off, cp->Nx, cp->cell_off, cp->gw_off, cp->g, cp->inv_Kn, cp->dt, cp->TL, cp->TR, cp->inv_DL, cp->inv_DR,
+  struct { int64_t off; int32_t Nx, cell_off, sum_off, gw_off; double g, inv_Kn, dt, TL, TR, inv_DL, inv_DR, half_Dt, inv_1pDt; } C{
+      cp->off, cp->Nx, cp->cell_off, cp->sum_off, cp->gw_off, cp->g, cp->inv_Kn, cp->dt, cp->TL, cp->TR, cp->inv_DL, cp->inv_DR,
       cp->half_Dt, cp->inv_1pDt};
   const int Nx = C.Nx, hw = P.hw, lane = P.lane, wave = P.wave, i = P.i, k0 = P.k0, ng = P.ng;
   const bool inside = i >= 0 && i < Nx;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
   double pv[NT][kSums];
   auto tile_sums = [&](int t) {
     const int tile = wave + NW * t < ntile ? wave + NW * t : 0;
-    return A.sums_in + (int64_t)tile * kSums * A.ncells + C.cell_off + ic;
+    return A.sums_in + (int64_t)tile * kSums * A.ncells + C.sum_off + ic;
   };
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(64 * kNodeWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
   for (int q = 0; q < NG; ++q)
     if (q >= ng) yf[q] = yc[q] = 0.0;
-  emit_sums<ADV>(A, P, K, Nx, C.cell_off, NFUN, collide, yf, yc, s_sum, s_wall);
+  emit_sums<ADV>(A, P, K, Nx, C.sum_off, NFUN, collide, yf, yc, s_sum, s_wall);
 }
 
 }  // namespace hhlb

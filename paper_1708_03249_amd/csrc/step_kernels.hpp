@@ -82,7 +82,7 @@ struct DevChannel {
   int32_t Nx;
   int32_t cell_off;   // offset of this channel's cells in per-cell arrays
   int32_t gw_off;     // offset of the wall equilibria (2V doubles: left, right)
-  int32_t pad;
+  int32_t sum_off;    // Q > 16: offset of its cells among those of its class
   double g;           // acceleration (F = m g)
   double inv_Kn;      // 1/Kn (0 when collisionless)
   double dt;
