@@ -9,14 +9,19 @@
 // memory twice per function and step: y^n in, y^{n+1} out.
 //
 // Mapping: a block of one wave per momentum half and function (f, chi) holds
-// 128 consecutive cells, two neighbouring cells per lane.  Two cells per lane
-// halve the lane shifts of the WENO-5 stencil (10 moves per two faces instead
-// of 20) and the share of halo lanes (110 of 128 cells are written, where a
-// window of 64 would write 46 of 64), and give every wave two independent
-// chains.  The waves of a half share the equilibrium: each evaluates it for
-// one of the two cells of its lanes.  The halves meet in LDS: moment sums,
-// wall densities, the equilibrium populations (and, full range, the
+// 128 consecutive cells, two neighbouring cells (slots) per lane.  Two cells per
+// lane halve the lane shifts of the WENO-5 stencil (10 moves per two faces
+// instead of 20) and the share of halo lanes (110 of 128 cells are written,
+// where a window of 64 would write 46 of 64), and give every wave two
+// independent chains.  The waves of a half share the equilibrium: each evaluates
+// it for one of the two cells of its lanes.  The halves meet in LDS: moment
+// sums, wall densities, the equilibrium populations (and, full range, the
 // populations the dense force matrix couples), two barriers per stage.
+//
+// Classes of short channels take windows of 64 cells instead, one slot per lane
+// (the host weighs the two, see slots_of): most positions of a 128-cell window
+// would hold no cell of a 48-cell channel, and the lanes work on them all the
+// same.
 //
 // Window geometry.  Position q holds cell c0 + q.  Each stage's stencil reaches
 // 3 cells, so the cells next to a window edge that is not a wall go stale at 3
@@ -24,29 +29,32 @@
 // wall the closure (Sec. IV.C.3) rebuilds the ghosts from the current stage
 // every stage, so nothing is lost there; the faces read the first two ghosts
 // only, and a wall sits where those two fit (cell 0 at position 2, cell Nx-1
-// at position 125 or below).  The host builds each channel's windows
-// (step_windows).  A channel that fits one window (Nx <= 124) needs no
-// neighbour at all: such classes take many steps in one launch.
+// at the third position from the end or below).  The host builds each channel's
+// windows (step_windows).  A channel that fits one window (Nx <= 124, or 60)
+// needs no neighbour at all: such classes take many steps in one launch.
 //
-// Lanes run down the wind of their half (see weno5_down): wind position 2 l + s
-// of slot s of lane l is position 2 l + s for p > 0 and 127 - (2 l + s) for
-// p < 0.
+// Lanes run down the wind of their half (see weno5_down): wind position
+// S l + s of slot s of lane l (S slots) is position S l + s for p > 0 and
+// 64 S - 1 - (S l + s) for p < 0.
 #pragma once
 #include "step_kernels.hpp"
 
 namespace hhlb {
 
-constexpr int kStepCells = 128;         // cells a window holds
 constexpr int kStepHalo = 3 * kHalo;    // stale cells at an edge that is not a wall
 constexpr int kStepGhosts = 2;          // ghosts kept beyond a wall
-// output cells: both walls in the window, one, none
-constexpr int kStepSingle = kStepCells - 2 * kStepGhosts;
-constexpr int kStepWall = kStepCells - kStepGhosts - kStepHalo;
-constexpr int kStepInner = kStepCells - 2 * kStepHalo;
+// cells a window of `slots` cells per lane holds, and its output cells: both
+// walls in the window, one, none
+constexpr int step_cells(int slots) { return 64 * slots; }
+constexpr int step_single(int slots) { return step_cells(slots) - 2 * kStepGhosts; }
+constexpr int step_wall(int slots) { return step_cells(slots) - kStepGhosts - kStepHalo; }
+constexpr int step_inner(int slots) { return step_cells(slots) - 2 * kStepHalo; }
 
 // waves per SIMD the registers are fitted to: y^n, the stage state and the
-// sources take 6 H doubles per lane
-constexpr int step_waves(int H) { return H <= 4 ? 4 : (H <= 8 ? 3 : 2); }
+// sources take 3 H doubles per lane and slot
+constexpr int step_waves(int H, int slots) {
+  return slots == 1 ? (H <= 12 ? 4 : 3) : (H <= 4 ? 4 : (H <= 8 ? 3 : 2));
+}
 
 // One window: channel, first output cell, cell of position 0 and the number
 // of output cells.
@@ -56,7 +64,8 @@ struct DevFusedWindow {
 struct DevFusedClassWindow {
   int32_t ch, i0, c0, nout;
   int32_t cls, Q;   // model class (index of its tables) and its order
-  int32_t pad[2];
+  int32_t slots;    // cells per lane of the window
+  int32_t pad;
 };
 
 // Orders whose H x H contractions (equilibrium table, force block) run on the
@@ -71,17 +80,25 @@ constexpr bool step_mfma() { return QUAD == 0 && Q >= HHLB_STEP_MFMA && Q % 4 ==
 // with chi its sum and projection.
 constexpr int step_sums(int nfun) { return nfun > 1 ? 6 : 4; }
 
-// LDS of a window (doubles)
-template <int QUAD, int Q, int NFUN>
-constexpr int step_lds_doubles() {
-  constexpr int H = QUAD == 0 ? Q : Q / 2;
-  constexpr int part = 2 * step_sums(NFUN) * kStepCells;   // moment partials of the halves
-  constexpr int geq = 2 * 2 * H * 64;                 // equilibrium populations
-  constexpr int y = QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells;   // dense force matrix: every node's population
-  // matrix cores: a tile per wave, in the memory of the partials (dead by then)
-  constexpr int tile = step_mfma<QUAD, Q>() ? 2 * NFUN * H * 64 : 0;
-  return (tile > part ? tile : part) + geq + y + 2;
-}
+// LDS of a window (doubles): the moment partials of the halves; a tile of H x 64
+// per wave for the matrix cores, in the partials' memory; the equilibrium
+// populations; every node's population for the dense force matrix.  f alone with
+// one slot (kOwnEq): the wave takes the equilibrium from its tile into its
+// sources at once, so the tile serves both products (20 KB a block at Q = 16).
+template <int QUAD, int Q, int NFUN, int SLOTS>
+struct StepLds {
+  static constexpr int H = QUAD == 0 ? Q : Q / 2;
+  static constexpr bool kMfma = step_mfma<QUAD, Q>();
+  static constexpr bool kOwnEq = kMfma && NFUN == 1 && SLOTS == 1;
+  static constexpr bool kAlias = kMfma && !kOwnEq;
+  static constexpr int part = 2 * step_sums(NFUN) * 64 * SLOTS;
+  static constexpr int tiles = kMfma ? 2 * NFUN * H * 64 : 0;
+  static constexpr int tile_at = kAlias ? 0 : part;
+  static constexpr int geq_at = kAlias ? (tiles > part ? tiles : part) : part + tiles;
+  static constexpr int y_at = geq_at + (kOwnEq ? 0 : 2 * SLOTS * H * 64);
+  static constexpr int nw_at = y_at + (QUAD == 0 ? 0 : NFUN * 2 * H * 64 * SLOTS);
+  static constexpr int doubles = nw_at + 2;
+};
 
 // Register layout of v_mfma_f64_16x16x4f64 (checked on the GPU):
 //   A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
@@ -312,15 +329,49 @@ __device__ __forceinline__ void faces_down2(const double (&ya)[G], const double 
   }
 }
 
+// The faces of one cell per lane, of G nodes.
+template <int ADV, int G>
+__device__ __forceinline__ void faces_down1(const double (&y)[G], bool used, double (&f)[G]) {
+  double dp[G], dm[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    dp[g] = dpp_shl1(y[g]) - y[g];
+    dm[g] = dpp_shr1(dp[g]);
+  }
+  if constexpr (ADV == 0) {
+    WenoWeights w[G];
+    double dl[G], dr[G];
+    bool odd = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const double D = kSq1312 * (dp[g] - dm[g]), Dl = dpp_shr1(D), Dr = dpp_shl1(D);
+      w[g].form(dm[g], dp[g], Dl, D, Dr, Dl * Dl, D * D, Dr * Dr);
+      dl[g] = Dl - D;
+      dr[g] = D - Dr;
+      odd |= !w[g].regular() && used;
+    }
+    if (odd) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) w[g].rescale();
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) f[g] = w[g].face(dm[g], dp[g], dl[g], dr[g], y[g]);
+  } else {
+#pragma unroll
+    for (int g = 0; g < G; ++g) f[g] = fma(1.0 / 3.0, dp[g], fma(1.0 / 6.0, dm[g], y[g]));
+  }
+}
+
 // nsteps steps of nst stages (3; or 1: one forward-Euler stage, whose increment
 // dt L[y^n] goes to the output, for the residual) of one window, run by a block of 2 NFUN waves.
-template <int QUAD, int Q, int NFUN, int ADV, int GROUP>
+template <int QUAD, int Q, int NFUN, int ADV, int GROUP, int SLOTS>
 __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables *tb, const DevChannel *chans,
                                             const DevFusedWindow win, const double *__restrict__ inv_dx,
                                             const double *__restrict__ gw, const double *__restrict__ in_f,
                                             const double *__restrict__ in_c, double *s_lds) {
-  constexpr int H = QUAD == 0 ? Q : Q / 2;
-  constexpr int SLOTS = 2;
+  using L = StepLds<QUAD, Q, NFUN, SLOTS>;
+  constexpr int H = L::H, P = step_cells(SLOTS);
+  constexpr bool kMfma = L::kMfma, kOwnEq = L::kOwnEq, kAlias = L::kAlias;
   ConstTables tp = (ConstTables)tb;
   ConstChannel cp = (ConstChannel)(chans + win.ch);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -329,25 +380,23 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
   const int pl = hw ? 63 - lane : lane;                 // index of the lane's cells in the shared arrays
   const int Nx = cp->Nx, c0 = win.c0;
   const double sg = hw ? -1.0 : 1.0;
-  constexpr bool kMfma = step_mfma<QUAD, Q>();
   // Shared arrays: the partials, s_nw and (full range) the populations s_y are
   // written before the first barrier of a stage and read behind it, before the
   // last, so the next stage may write them; the energy's partial and its barrier
   // lie between (full range); s_geq is written before the last barrier and read
-  // behind it.  The tiles, in the partials' memory, are read to the end of the
-  // stage, which then ends with a barrier.
-  double *s_part = s_lds, *s_tile = s_lds + wv * H * 64;   // the tile: matrix cores only
-  double *s_geq = s_lds + (step_lds_doubles<QUAD, Q, NFUN>() - 2 - 2 * 2 * H * 64 - (QUAD == 0 ? 0 : NFUN * 2 * H * kStepCells));
-  double *s_y = s_geq + 2 * 2 * H * 64;
-  double *s_nw = s_lds + step_lds_doubles<QUAD, Q, NFUN>() - 2;
-  // plane (parity of the position) and cell of each slot
-  const int plane[SLOTS] = {hw, 1 - hw};
-  const int i[SLOTS] = {hw ? c0 + 127 - 2 * lane : c0 + 2 * lane, hw ? c0 + 126 - 2 * lane : c0 + 2 * lane + 1};
+  // behind it.  Tiles in the partials' memory are written behind the last barrier
+  // and read to the end of the stage, which then ends with a barrier.
+  double *s_part = s_lds, *s_tile = s_lds + L::tile_at + wv * H * 64;   // the tile: matrix cores only
+  double *s_geq = s_lds + L::geq_at, *s_y = s_lds + L::y_at, *s_nw = s_lds + L::nw_at;
+  // plane (position modulo the slots) and cell of each slot (the first, of one)
+  const int plane[2] = {SLOTS == 1 ? 0 : hw, 1 - hw};
+  const int i[2] = {hw ? c0 + (P - 1) - SLOTS * lane : c0 + SLOTS * lane,
+                    hw ? c0 + (P - 2) - SLOTS * lane : c0 + SLOTS * lane + 1};
   const int first = win.i0 - c0, last = first + win.nout - 1;   // output positions
-  const bool needL = c0 < 0, needR = Nx - 1 - c0 <= kStepCells - 1 - kStepGhosts;
+  const bool needL = c0 < 0, needR = Nx - 1 - c0 <= P - 1 - kStepGhosts;
   const bool down = hw ? needL : needR, up = hw ? needR : needL;
 
-  const int w0 = c0 < 0 ? 0 : c0, w1 = c0 + kStepCells < Nx ? c0 + kStepCells : Nx;
+  const int w0 = c0 < 0 ? 0 : c0, w1 = c0 + P < Nx ? c0 + P : Nx;
   const uint32_t wbytes = (uint32_t)(w1 - w0) * 8u;
   uint32_t off[SLOTS];
   bool inside[SLOTS];
@@ -383,7 +432,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     const double b_s = st == 0 ? 1.0 : (st == 1 ? 0.25 : 2.0 / 3.0);
     // positions whose result is still exact after this stage
     const int left = 3 * (A.nst - 1 - st);
-    const int lo = needL ? 0 : first - left, hi = needR ? kStepCells - 1 : last + left;
+    const int lo = needL ? 0 : first - left, hi = needR ? P - 1 : last + left;
 
     // ---- closure, part 1: ghosts of the nodes flowing into a wall are
     // extrapolated quadratically from the three nearest cells (Sec. IV.C.3)
@@ -392,14 +441,14 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     if (down) {
       int ln = lane;   // what the closure needs of the lane is formed anew, not kept through the steps
       asm volatile("" : "+v"(ln));
-      const int pd = hw ? kStepCells - 1 + c0 : Nx - 1 - c0;   // wind position of the wall cell
-      const int lp = pd >> 1;
+      const int pd = hw ? P - 1 + c0 : Nx - 1 - c0;   // wind position of the wall cell
+      const int lp = SLOTS == 2 ? pd >> 1 : pd;
       const bool odd = pd & 1;
       double c_[3][SLOTS];
       bool ghost[SLOTS];
 #pragma unroll
       for (int s = 0; s < SLOTS; ++s) {
-        const int gi = 2 * ln + s - pd;   // ghost order 1, 2 (else <= 0)
+        const int gi = SLOTS * ln + s - pd;   // ghost order 1, 2 (else <= 0)
         ghost[s] = gi == 1 || gi == 2;
         c_[0][s] = gi == 1 ? 3.0 : 6.0;
         c_[1][s] = gi == 1 ? -3.0 : -8.0;
@@ -410,10 +459,22 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        const double e0 = readlane_d(y[j][0], lp), o0 = readlane_d(y[j][1], odd ? lp : lp - 1),
-                     e1 = readlane_d(y[j][0], lp - 1), o1 = readlane_d(y[j][1], lp - 1);
-        const double y0 = odd ? o0 : e0, y1 = odd ? e0 : o0, y2 = odd ? o1 : e1;
+        double y0, y1, y2;
+        if constexpr (SLOTS == 1) {
+          y0 = readlane_d(y[j][0], lp);
+          y1 = readlane_d(y[j][0], lp - 1);
+          y2 = readlane_d(y[j][0], lp - 2);
+        } else {
+          const double e0 = readlane_d(y[j][0], lp), o0 = readlane_d(y[j][1], odd ? lp : lp - 1),
+                       e1 = readlane_d(y[j][0], lp - 1), o1 = readlane_d(y[j][1], lp - 1);
+          y0 = odd ? o0 : e0;
+          y1 = odd ? e0 : o0;
+          y2 = odd ? o1 : e1;
+        }
         if (ln == j) { a0 = y0; a1 = y1; a2 = y2; }
+        // taken here: sunk to where the f wave uses them, every node's values
+        // would stay in scalar registers (Q = 16: 100 of them spilled)
+        if constexpr (H > 12) asm volatile("" : "+v"(a0), "+v"(a1), "+v"(a2));
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
           if (ghost[s]) y[j][s] = fma(c_[2][s], y2, fma(c_[1][s], y1, c_[0][s] * y0));
@@ -430,12 +491,12 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     // ---- partial moments of this half and the rank-1 force projections ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     auto part = [&](int h, int q, int s) -> double & {
-      return s_part[((h * step_sums(NFUN) + q) * 2 + plane[s]) * 64 + pl];
+      return s_part[((h * step_sums(NFUN) + q) * SLOTS + plane[s]) * 64 + pl];
     };
     {
-      double m0[SLOTS] = {0.0, 0.0}, mb[SLOTS] = {0.0, 0.0};
+      double m0[SLOTS] = {}, mb[SLOTS] = {};
       if (fn == 0) {   // uniform over the wave
-        double m1[SLOTS] = {0.0, 0.0}, m2[SLOTS] = {0.0, 0.0};
+        double m1[SLOTS] = {}, m2[SLOTS] = {};
 #pragma unroll
         for (int j = 0; j < H; ++j)
 #pragma unroll
@@ -475,7 +536,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 #pragma unroll
       for (int j = 0; j < H; ++j)
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) s_y[((fn * 2 * H + hw * H + j) * 2 + plane[s]) * 64 + pl] = y[j][s];
+        for (int s = 0; s < SLOTS; ++s) s_y[((fn * 2 * H + hw * H + j) * SLOTS + plane[s]) * 64 + pl] = y[j][s];
     }
     if (fn == 0 && lane == 0) s_nw[hw] = nw_mine;
     __syncthreads();
@@ -487,7 +548,9 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       typedef const __attribute__((address_space(4))) double *ConstDoubles;
       ConstDoubles gww = (ConstDoubles)gw + cp->gw_off + (hw ? 3 * H : 0);
       asm volatile("" : "+s"(gww));
-      const bool gh[SLOTS] = {hw ? i[0] >= Nx : i[0] < 0, hw ? i[1] >= Nx : i[1] < 0};
+      bool gh[SLOTS];
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) gh[s] = hw ? i[s] >= Nx : i[s] < 0;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
         const double ghost = sc * gww[j];
@@ -523,7 +586,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
     if constexpr (QUAD == 1) {
       if (collide) {   // uniform over the block
         if (fn == 0) {
-          double e2[SLOTS] = {0.0, 0.0};
+          double e2[SLOTS] = {};
 #pragma unroll
           for (int j = 0; j < H; ++j)
 #pragma unroll
@@ -545,18 +608,24 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       }
     }
 
+    // matrix cores, two slots: the second slot's force block stays in the tile
+    // until pass 2 reads it, which keeps H values out of the register file
+    constexpr bool kDefer = kMfma && SLOTS == 2;
+    constexpr int SREG = kDefer ? 1 : SLOTS;
+    double src[H][SREG];
+
     // ---- equilibrium populations g_k of this half: with f and chi, each of
-    // the half's two waves takes one slot ----
+    // the half's two waves takes one slot (of one slot, the f wave) ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     if (collide) {
 #pragma unroll 1
-      for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 ? fn + 1 : SLOTS); ++e) {
-        const double ue = e == 0 ? u[0] : u[1], Te = e == 0 ? T[0] : T[1];
+      for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 && (SLOTS == 2 || fn == 0) ? fn + 1 : SLOTS); ++e) {
+        const double ue = e == 0 ? u[0] : u[SLOTS - 1], Te = e == 0 ? T[0] : T[SLOTS - 1];
         double G[Q];
         if constexpr (QUAD == 0) {
-          const int qp = (e == 0 ? plane[0] : plane[1]) + 2 * pl;   // position
-          half_range_coeffs<Q>(tp, ue, Te, sg, lane, lad, (e == 0 ? inside[0] : inside[1]) && qp >= lo && qp <= hi,
-                               wide, G);
+          const int qp = (e == 0 ? plane[0] : plane[SLOTS - 1]) + SLOTS * pl;   // position
+          half_range_coeffs<Q>(tp, ue, Te, sg, lane, lad,
+                               (e == 0 ? inside[0] : inside[SLOTS - 1]) && qp >= lo && qp <= hi, wide, G);
         } else {
           // closed form (Sec. IV.A.3): G_{l+1} = ub G_l + l a G_{l-1}
           const double aa = fma(Te * tp->inv_p0, tp->inv_p0, -1.0), bb = ue * tp->inv_p0;
@@ -566,7 +635,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
           for (int l = 1; l + 1 < Q; ++l) G[l + 1] = fma(bb, G[l], ((double)l * aa) * G[l - 1]);
         }
         asm volatile("" : "+s"(tp));
-        double *ge = s_geq + (hw * 2 + e) * H * 64;
+        double *ge = kOwnEq ? s_tile : s_geq + (hw * SLOTS + e) * H * 64;
         if constexpr (kMfma) {
           double aH[H / 4];
           mfma_operand<H>(tb->HWs, lane, aH);
@@ -585,6 +654,11 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
         }
       }
     }
+    if constexpr (kOwnEq) {   // n g_k - y_k
+#pragma unroll
+      for (int j = 0; j < H; ++j) src[j][0] = collide ? fma(n[0], s_tile[j * 64 + lane], -y[j][0]) : 0.0;
+      __builtin_amdgcn_wave_barrier();
+    }
     // full range: the other half's populations, read while they are those of
     // this stage (its waves write the next ones behind the barrier)
     double yo[QUAD == 1 ? H : 1][SLOTS];
@@ -593,7 +667,7 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       for (int j = 0; j < H; ++j)
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
-          yo[j][s] = s_y[((fn * 2 * H + (1 - hw) * H + j) * 2 + plane[s]) * 64 + pl];
+          yo[j][s] = s_y[((fn * 2 * H + (1 - hw) * H + j) * SLOTS + plane[s]) * 64 + pl];
     }
     __syncthreads();
 
@@ -608,10 +682,6 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       cT[s] = n[s] * cp->inv_Kn * bdt;
       nq[s] = fn == 1 ? n[s] * (cp->half_Dt * T[s]) : n[s];
     }
-    // matrix cores: the second slot's force block stays in the tile until
-    // pass 2 reads it, which keeps H values out of the register file
-    constexpr int SREG = kMfma ? 1 : SLOTS;
-    double src[H][SREG];
     if constexpr (kMfma) {
       double aK[H / 4];
       mfma_operand<H>(tb->Kin, lane, aK);
@@ -619,64 +689,78 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
       for (int j = 0; j < H; ++j) s_tile[j * 64 + lane] = y[j][0];
       mfma_tile<H>(aK, s_tile, lane);
 #pragma unroll
-      for (int j = 0; j < H; ++j) src[j][0] = fma(tp->ka[j], bp[0], s_tile[j * 64 + lane]);
-      __builtin_amdgcn_wave_barrier();
+      for (int j = 0; j < H; ++j) {
+        const double k0 = fma(tp->ka[j], bp[0], s_tile[j * 64 + lane]);
+        src[j][0] = kOwnEq ? fma(cT[0], src[j][0], cF * k0) : k0;
+      }
+      if constexpr (kDefer) {
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int j = 0; j < H; ++j) s_tile[j * 64 + lane] = y[j][1];
-      mfma_tile<H>(aK, s_tile, lane);
+        for (int j = 0; j < H; ++j) s_tile[j * 64 + lane] = y[j][1];
+        mfma_tile<H>(aK, s_tile, lane);
+      }
     } else if constexpr (QUAD == 0) {
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        double k0 = tp->ka[j] * bp[0], k1 = tp->ka[j] * bp[1];
+        double k_[SLOTS];
 #pragma unroll
-        for (int jj = 0; jj < H; ++jj) {
-          k0 = fma(tp->Kin[j * H + jj], y[jj][0], k0);
-          k1 = fma(tp->Kin[j * H + jj], y[jj][1], k1);
-        }
-        src[j][0] = k0;
-        src[j][1] = k1;
+        for (int s = 0; s < SLOTS; ++s) k_[s] = tp->ka[j] * bp[s];
+#pragma unroll
+        for (int jj = 0; jj < H; ++jj)
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) k_[s] = fma(tp->Kin[j * H + jj], y[jj][s], k_[s]);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) src[j][s] = k_[s];
       }
     } else {
       const __attribute__((address_space(4))) double *Kr = tp->Kin + hw * H * Q;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        double k0 = 0.0, k1 = 0.0;
+        double k_[SLOTS] = {};
 #pragma unroll
         for (int jj = 0; jj < H; ++jj) {
           const double ks = Kr[j * Q + hw * H + jj], ko = Kr[j * Q + (1 - hw) * H + jj];
-          k0 = fma(ko, yo[jj][0], fma(ks, y[jj][0], k0));
-          k1 = fma(ko, yo[jj][1], fma(ks, y[jj][1], k1));
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) k_[s] = fma(ko, yo[jj][s], fma(ks, y[jj][s], k_[s]));
         }
-        src[j][0] = k0;
-        src[j][1] = k1;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) src[j][s] = k_[s];
       }
     }
-    if (collide) {
+    if constexpr (!kOwnEq) {
+      if (collide) {
 #pragma unroll
-      for (int j = 0; j < H; ++j)
+        for (int j = 0; j < H; ++j)
 #pragma unroll
-        for (int s = 0; s < SREG; ++s) {
-          const double geq = s_geq[((hw * 2 + s) * H + j) * 64 + lane];
-          src[j][s] = fma(cT[s], fma(nq[s], geq, -y[j][s]), cF * src[j][s]);
+          for (int s = 0; s < SREG; ++s) {
+            const double geq = s_geq[((hw * SLOTS + s) * H + j) * 64 + lane];
+            src[j][s] = fma(cT[s], fma(nq[s], geq, -y[j][s]), cF * src[j][s]);
+          }
+      } else {
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+          for (int s = 0; s < SREG; ++s) src[j][s] *= cF;
+        if constexpr (kDefer) {   // pass 2 reads the second slot's equilibrium
+#pragma unroll
+          for (int j = 0; j < H; ++j) s_geq[((hw * SLOTS + 1) * H + j) * 64 + lane] = 0.0;
         }
-    } else {
-#pragma unroll
-      for (int j = 0; j < H; ++j)
-#pragma unroll
-        for (int s = 0; s < SREG; ++s) src[j][s] *= cF;
-      if constexpr (kMfma) {   // pass 2 reads the second slot's equilibrium
-#pragma unroll
-        for (int j = 0; j < H; ++j) s_geq[((hw * 2 + 1) * H + j) * 64 + lane] = 0.0;
       }
     }
 
     // ---- pass 2: advection (WENO-5 / upwind-3 face fluxes, Sec. IV.C.2) and
     // the RK-3 combination into the registers; the faces of node j read only
     // node j's values, so y[j] is replaced once its fluxes are formed ----
-    const int q0 = plane[0] + 2 * pl, q1 = plane[1] + 2 * pl;
-    const bool use0 = inside[0] && q0 >= lo - 1 && q0 <= hi + 1, use1 = inside[1] && q1 >= lo - 1 && q1 <= hi + 1;
-    const bool wf0 = hw ? i[0] == Nx : i[0] == -1, wf1 = hw ? i[1] == Nx : i[1] == -1;
-    const double sdx0 = -dxi[0] * bdt, sdx1 = -dxi[1] * bdt;
+    // position, use and scale of each slot
+    bool use[SLOTS], wf[SLOTS];
+    double sdx[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      const int q = plane[s] + SLOTS * pl;
+      use[s] = inside[s] && q >= lo - 1 && q <= hi + 1;
+      wf[s] = hw ? i[s] == Nx : i[s] == -1;
+      sdx[s] = -dxi[s] * bdt;
+    }
     asm volatile("" : "+s"(tp));
 #pragma unroll
     for (int j0 = 0; j0 < H; j0 += GROUP) {
@@ -686,36 +770,41 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         ya[g] = y[j0 + g][0];
-        yb[g] = y[j0 + g][1];
+        yb[g] = y[j0 + g][SLOTS - 1];
       }
-      faces_down2<ADV, G>(ya, yb, use0, use1, fa, fb);
+      if constexpr (SLOTS == 2) faces_down2<ADV, G>(ya, yb, use[0], use[1], fa, fb);
+      else faces_down1<ADV, G>(ya, use[0], fa);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int j = j0 + g;
         const double v = tp->p[j];
         if (up) {   // the emergent flux at the wall is the wall's own
           asm volatile("");
-          if (wf0) fa[g] = ya[g];
-          if (wf1) fb[g] = yb[g];
+          if (wf[0]) fa[g] = ya[g];
+          if constexpr (SLOTS == 2)
+            if (wf[1]) fb[g] = yb[g];
         }
-        const double fu = dpp_shr1(fb[g]);
-        y[j][0] = fma(a_s, yn[j][0], fma(b_y, ya[g], fma(sdx0 * v, fa[g] - fu, src[j][0])));
-        double src1;
-        if constexpr (kMfma) {
-          const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
-          const double geq = s_geq[((hw * 2 + 1) * H + j) * 64 + lane];
-          src1 = fma(cT[1], fma(nq[1], geq, -yb[g]), cF * k1);
-        } else {
-          src1 = src[j][1];
+        const double fu = dpp_shr1(SLOTS == 2 ? fb[g] : fa[g]);
+        y[j][0] = fma(a_s, yn[j][0], fma(b_y, ya[g], fma(sdx[0] * v, fa[g] - fu, src[j][0])));
+        if constexpr (SLOTS == 2) {
+          double src1;
+          if constexpr (kDefer) {
+            const double k1 = fma(tp->ka[j], bp[1], s_tile[j * 64 + lane]);
+            const double geq = s_geq[((hw * SLOTS + 1) * H + j) * 64 + lane];
+            src1 = fma(cT[1], fma(nq[1], geq, -yb[g]), cF * k1);
+          } else {
+            src1 = src[j][1];
+          }
+          y[j][1] = fma(a_s, yn[j][1], fma(b_y, yb[g], fma(sdx[1] * v, fb[g] - fa[g], src1)));
         }
-        y[j][1] = fma(a_s, yn[j][1], fma(b_y, yb[g], fma(sdx1 * v, fb[g] - fa[g], src1)));
         // keep the update here: sunk below the later nodes it would hold their
         // faces and y^n at once
-        asm volatile("" : "+v"(y[j][0]), "+v"(y[j][1]));
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) asm volatile("" : "+v"(y[j][s]));
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (kMfma) __syncthreads();   // the next partials overwrite the tiles
+    if constexpr (kAlias) __syncthreads();   // the next partials overwrite the tiles
     if (st == 2 && it + 1 < A.nsteps * A.nst) {
 #pragma unroll
       for (int j = 0; j < H; ++j)
@@ -747,45 +836,53 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 // steps of 64 channels, Q = 12: 882 -> 855 us; groups of four 378, 1434 and
 // 1066 us (beyond 256 registers).
 constexpr int few_group(int H) { return H % 2 == 0 ? 2 : 1; }
-// waves per SIMD that fit with FEW: 8 H doubles and the faces of two nodes
-constexpr int few_waves(int H) { return H <= 12 ? 2 : 1; }
-template <int QUAD, int Q, int NFUN, int ADV, bool FEW>
+// waves per SIMD that fit with FEW: 4 H doubles per slot and the faces of two
+// nodes (f alone at H = 16 holds both tables' operands besides)
+constexpr int few_waves(int H, int slots, int nfun) { return H <= 12 || (slots == 1 && nfun > 1) ? 2 : 1; }
+template <int QUAD, int Q, int NFUN, int ADV, bool FEW, int SLOTS>
 __global__ __launch_bounds__(128 * NFUN)
-__attribute__((amdgpu_waves_per_eu(FEW ? 1 : step_waves(QUAD == 0 ? Q : Q / 2)))) void
+__attribute__((amdgpu_waves_per_eu(FEW ? 1 : step_waves(QUAD == 0 ? Q : Q / 2, SLOTS)))) void
 step_kernel(StageArgs A, const DevTables *__restrict__ tb, const DevChannel *__restrict__ chans,
             const DevFusedWindow *__restrict__ wins, const double *__restrict__ inv_dx,
             const double *__restrict__ gw, const double *__restrict__ in_f, const double *__restrict__ in_c) {
-  __shared__ double s_lds[step_lds_doubles<QUAD, Q, NFUN>()];
+  __shared__ double s_lds[StepLds<QUAD, Q, NFUN, SLOTS>::doubles];
   const int w = A.xcd_map ? xcd_window(blockIdx.x, A.nwin) : (int)blockIdx.x;
-  step_window<QUAD, Q, NFUN, ADV, FEW ? few_group(QUAD == 0 ? Q : Q / 2) : 1>(A, tb, chans, wins[w], inv_dx, gw, in_f, in_c, s_lds);
+  step_window<QUAD, Q, NFUN, ADV, FEW ? few_group(QUAD == 0 ? Q : Q / 2) : 1, SLOTS>(A, tb, chans, wins[w], inv_dx, gw,
+                                                                                     in_f, in_c, s_lds);
 }
 
 // One launch for the windows of several half-range model classes that share
-// the functions and the scheme.  Record b names the window and its class; the
-// class's order Q, the same for the whole block, selects the per-order code
+// the functions and the scheme.  Record b names the window, its class and slots;
+// the class's order Q and slots, the same for the whole block, select the code
 // (orders up to QTOP).  Persistent form: with fewer blocks than windows each
 // block takes windows b, b + gridDim.x, .. in turn.
 template <int QTOP, int NFUN, int ADV, bool PERSIST>
-__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(step_waves(QTOP)))) void
+__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(step_waves(QTOP, 2)))) void
 step_kernel_classes(StageArgs A, const DevTables *__restrict__ tbs, const DevChannel *__restrict__ chans,
                     const DevFusedClassWindow *__restrict__ wins, const double *__restrict__ inv_dx,
                     const double *__restrict__ gw, const double *__restrict__ in_f,
                     const double *__restrict__ in_c) {
-  __shared__ double s_lds[step_lds_doubles<0, QTOP, NFUN>()];
+  __shared__ double s_lds[StepLds<0, QTOP, NFUN, 2>::doubles];
   for (int b = blockIdx.x; b < A.nwin; b += gridDim.x) {
     if (PERSIST && b != (int)blockIdx.x) __syncthreads();   // the last window's LDS reads are done
     const int w = A.xcd_map ? xcd_window(b, A.nwin) : b;
     const DevFusedClassWindow cw = wins[w];
     const DevFusedWindow win{cw.ch, cw.i0, cw.c0, cw.nout};
     const DevTables *tb = tbs + __builtin_amdgcn_readfirstlane(cw.cls);
-    switch (__builtin_amdgcn_readfirstlane(cw.Q)) {
-#define HHLB_CLASS_CASE(q)                                                            \
-  case q:                                                                             \
-    if constexpr (q <= QTOP)                                                          \
-      step_window<0, q, NFUN, ADV, 1>(A, tb, chans, win, inv_dx, gw, in_f, in_c, s_lds); \
+    switch (__builtin_amdgcn_readfirstlane(2 * cw.Q + cw.slots - 1)) {
+#define HHLB_CLASS_CASE(q, slots)                                                              \
+  case 2 * q + slots - 1:                                                                      \
+    if constexpr (q <= QTOP) {                                                                 \
+      static_assert(StepLds<0, q, NFUN, slots>::doubles <= StepLds<0, QTOP, NFUN, 2>::doubles); \
+      step_window<0, q, NFUN, ADV, 1, slots>(A, tb, chans, win, inv_dx, gw, in_f, in_c, s_lds); \
+    }                                                                                          \
     break;
-      HHLB_CLASS_CASE(1) HHLB_CLASS_CASE(2) HHLB_CLASS_CASE(3) HHLB_CLASS_CASE(4)
-      HHLB_CLASS_CASE(6) HHLB_CLASS_CASE(8) HHLB_CLASS_CASE(12) HHLB_CLASS_CASE(16)
+#define HHLB_CLASS_CASES(slots)                                                                \
+  HHLB_CLASS_CASE(1, slots) HHLB_CLASS_CASE(2, slots) HHLB_CLASS_CASE(3, slots) HHLB_CLASS_CASE(4, slots) \
+  HHLB_CLASS_CASE(6, slots) HHLB_CLASS_CASE(8, slots) HHLB_CLASS_CASE(12, slots) HHLB_CLASS_CASE(16, slots)
+      HHLB_CLASS_CASES(1)
+      HHLB_CLASS_CASES(2)
+#undef HHLB_CLASS_CASES
 #undef HHLB_CLASS_CASE
       default: break;
     }

@@ -309,7 +309,10 @@ struct ModelClass {
   double p0;
   hhlb::Rule rule;
   hhlb::DevTables dev;
-  Launcher step = nullptr;      // Q <= 16: whole RK-3 steps per launch
+  // Q <= 16: whole RK-3 steps per launch, windows of `slots` cells per lane
+  Launcher step = nullptr, step_of[2] = {nullptr, nullptr};
+  int slots = 2;
+  int64_t positions[2] = {0, 0};   // of its windows with either number of slots
   std::vector<hhlb::DevWindow> windows;
   int max_out = 0;     // the longest of them
   size_t win_off = 0;  // byte offset in workspace
@@ -325,6 +328,24 @@ struct ModelClass {
   std::vector<char> lblob;
   size_t lbl_off = 0;
 };
+
+namespace {
+
+// Cells per lane of a class's windows, by the positions the windows of its
+// channels take with one and with two.  A position of one cell per lane costs
+// 1.03 to 1.15 of one of two (2048 channels of 64 cells, 128 positions either way:
+// FP64 Q = 4 69 against 65 us a step, Q = 8 123 against 120, Q = 16 312 against
+// 296; FP32 Q = 8 101 against 95), so one is taken where it needs a tenth less:
+// 4096 channels of 48 cells, Q = 8, 131 against 229 us (183 with a stage per
+// launch), 2307 of 130 cells 197 against 255.  f alone on the matrix cores is
+// bound by LDS with two, one and a half waves per SIMD: 127 against 185 us at 64
+// cells (Q = 16, upwind-3), 527 against 602 at 16384.
+int slots_of(const ModelClass &mc) {
+  const double cost = mc.Dt == 0 && mc.Q == 16 && hhlb::half_range(mc.quad) ? 0.7 : 1.1;
+  return mc.positions[0] * cost < mc.positions[1] ? 1 : 2;
+}
+
+}  // namespace
 
 struct hhlb_solver {
   std::vector<hhlb_channel> ch;
@@ -474,26 +495,33 @@ void make_grid(const hhlb_channel &c, std::vector<double> &dx) {
 // operands see them (finite values of normal range).
 float round_f16(float x) { return (float)(_Float16)x; }
 
-// Windows of the step kernel for one channel of Nx cells.  A window's edge is
-// a wall whose first two ghosts fit among its 128 positions, or lies 9 cells
-// beyond its outputs inside the channel.  As few windows as hold the channel
-// (one up to 124 cells, two up to 234, 110 more each), of nearly equal
-// length: with two or more windows each writes 62 cells at least, so every
-// halo finds its cells.
-void step_windows(int ch, int Nx, std::vector<hhlb::DevFusedWindow> &w) {
+// Windows of the step kernel, of 64 cells per slot, for one channel of Nx cells.
+// A window's edge is a wall whose first two ghosts fit among its positions, or
+// lies 9 cells beyond its outputs inside the channel.  As few windows as hold the
+// channel (two slots: one up to 124 cells, two up to 234, 110 more each; one
+// slot: 60, 106, 46), of nearly equal length: with two or more windows each
+// writes 62 cells at least (30), so every halo finds its cells.
+int step_window_count(int Nx, int slots) {
   using namespace hhlb;
-  if (Nx <= kStepSingle) {
+  if (Nx <= step_single(slots)) return 1;
+  const int extra = Nx - 2 * step_wall(slots);
+  return 2 + (extra > 0 ? (extra + step_inner(slots) - 1) / step_inner(slots) : 0);
+}
+
+void step_windows(int ch, int Nx, int slots, std::vector<hhlb::DevFusedWindow> &w) {
+  using namespace hhlb;
+  int left = step_window_count(Nx, slots);
+  if (left == 1) {
     w.push_back({ch, 0, -kStepGhosts, Nx});
     return;
   }
-  const int extra = Nx - 2 * kStepWall;
-  int left = 2 + (extra > 0 ? (extra + kStepInner - 1) / kStepInner : 0);
+  const int wall = step_wall(slots), inner = step_inner(slots);
   int o = 0;
   bool first = true;
   for (; left > 1; --left) {
     // an equal share, or more where the windows after this one could not hold the rest
-    const int rest = kStepInner * (left - 2) + kStepWall;
-    const int m = std::min(first ? kStepWall : kStepInner, std::max((Nx - o + left - 1) / left, Nx - o - rest));
+    const int rest = inner * (left - 2) + wall;
+    const int m = std::min(first ? wall : inner, std::max((Nx - o + left - 1) / left, Nx - o - rest));
     w.push_back({ch, o, first ? -kStepGhosts : o - kStepHalo, m});
     o += m;
     first = false;
@@ -900,11 +928,13 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         } else {
           // both half-range kinds run the half-range kernels (tables differ)
           const int kq = hhlb::half_range(h.quad) ? HHLB_HALF_HERMITE : HHLB_FULL_HERMITE;
-          auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, 1});
-          if (lk == launchers().end())
+          for (int slots : {1, 2}) {
+            auto lk = launchers().find({kq, h.Q, nf, h.adv, precision, slots});
+            if (lk != launchers().end()) mc.step_of[slots - 1] = lk->second;
+          }
+          if (!mc.step_of[0] || !mc.step_of[1])
             return fail(HHLB_E_UNSUPPORTED, "channel " + std::to_string(c) + ": no kernel for quad=" +
                                                 std::to_string(h.quad) + " Q=" + std::to_string(h.Q));
-          mc.step = lk->second;
           st = cached_tables(h, N, precision, mc.rule, mc.dev);
           if (st) return st;
         }
@@ -915,12 +945,14 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         id = it->second;
       }
       s->ch_class.push_back(id);
-      const ModelClass &mc = s->classes[id];
+      ModelClass &mc = s->classes[id];
       const int V = mc.rule.V;
       s->Vs.push_back(V);
       s->off[c + 1] = s->off[c] + (int64_t)V * h.Nx;
       s->cell_off[c] = (int32_t)s->total_cells;
       s->total_cells += h.Nx;
+      if (!mc.large)
+        for (int slots : {1, 2}) mc.positions[slots - 1] += (int64_t)hhlb::step_cells(slots) * step_window_count(h.Nx, slots);
       if (h.transverse_dof > 0) s->has_chi = true;
       else s->any_dt0 = true;
     }
@@ -984,11 +1016,18 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         mc.max_out = std::max(mc.max_out, m);
         i0 += m;
       }
-      if (mc.step) {
-        const size_t had = mc.fwindows.size();
-        step_windows(c, h.Nx, mc.fwindows);
-        mc.whole = mc.whole && mc.fwindows.size() == had + 1;
+    }
+    for (auto &mc : s->classes)
+      if (!mc.large) {
+        mc.slots = slots_of(mc);
+        mc.step = mc.step_of[mc.slots - 1];
       }
+    for (int c = 0; c < n_ch; ++c) {
+      ModelClass &mc = s->classes[s->ch_class[c]];
+      if (mc.large) continue;
+      const size_t had = mc.fwindows.size();
+      step_windows(c, channels[c].Nx, mc.slots, mc.fwindows);
+      mc.whole = mc.whole && mc.fwindows.size() == had + 1;
     }
     // classes that can share a launch: FP64 half-range classes of the step
     // kernel, grouped by functions and scheme
@@ -1013,7 +1052,7 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
         for (size_t ci : kv.second) {
           const ModelClass &mc = s->classes[ci];
           for (const auto &w : mc.fwindows)
-            g.wins.push_back({w.ch, w.i0, w.c0, w.nout, (int32_t)ci, (int32_t)mc.Q, {0, 0}});
+            g.wins.push_back({w.ch, w.i0, w.c0, w.nout, (int32_t)ci, (int32_t)mc.Q, mc.slots, 0});
           s->class_group[ci] = (int)s->groups.size();
         }
         s->groups.push_back(std::move(g));

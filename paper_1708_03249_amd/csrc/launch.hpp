@@ -12,8 +12,8 @@ namespace hhlb {
 
 using Launcher = void (*)(const StageArgs &, hipStream_t);
 // (quadrature kind, Q, functions (1 = f, 2 = f and chi), advection, precision,
-//  shape: 1 = one class, 3 = across classes (FP64), keyed by the largest order
-//  it holds)
+//  shape: 1 and 2 = one class, windows of one or two cells per lane; 3 = across
+//  classes (FP64), keyed by the largest order it holds)
 using LaunchKey = std::tuple<int, int, int, int, int, int>;
 using LaunchMap = std::map<LaunchKey, Launcher>;
 

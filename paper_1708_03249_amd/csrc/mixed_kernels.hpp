@@ -23,9 +23,9 @@
 // at Q = 16, BF16 or FP16 MFMA (16 x 16 x 16, FP32 accumulation) for those
 // forms at every Q (zero-padded to 16), and FP32 VALU otherwise.
 //
-// Mapping, window geometry and the split of the equilibrium between the waves
-// are those of the FP64 step kernel: (hi, lo) and the increment of a 128-cell
-// window stay in registers through the three stages, and a step reads and
+// Mapping, window geometry (two cells or one per lane) and the split of the
+// equilibrium between the waves are those of the FP64 step kernel: (hi, lo) and
+// the increment of a window stay in registers through the three stages, and a step reads and
 // writes 6 bytes per population where a stage per launch moved 52 per step.
 #pragma once
 #include "fused_kernels.hpp"
@@ -107,6 +107,21 @@ __device__ __forceinline__ void devs_down2(float ya, float yb, bool usedA, bool 
   } else {
     fa = fmaf(1.0f / 3.0f, da, (1.0f / 6.0f) * dm);
     fb = fmaf(1.0f / 3.0f, db, (1.0f / 6.0f) * da);
+  }
+}
+
+// The same for one cell per lane.
+template <int ADV>
+__device__ __forceinline__ void dev_down1(float y, bool used, float &dm, float &f) {
+  const float dp = dpp_shl1f(y) - y;
+  dm = dpp_shr1f(dp);
+  if constexpr (ADV == 0) {
+    const float D = (float)kSq1312 * (dp - dm), Dl = dpp_shr1f(D), Dr = dpp_shl1f(D);
+    WenoWeightsF w(dm, dp, Dl, D, Dr, Dl * Dl, D * D, Dr * Dr);
+    if (!w.regular() && used) w.limit();
+    f = w.dev(dm, dp, Dl - D, D - Dr);
+  } else {
+    f = fmaf(1.0f / 3.0f, dp, (1.0f / 6.0f) * dm);
   }
 }
 
@@ -323,45 +338,43 @@ __device__ __forceinline__ void mfma_force(const ForceA<PREC> &aM, const ForceDe
 }
 
 // waves per SIMD the registers are fitted to: y^n, its correction word, the
-// increment and the sources take 7 H registers per lane
-#ifndef HHLB_MIXED_WAVES
-#define HHLB_MIXED_WAVES(H) ((H) <= 8 ? 4 : 3)
-#endif
-constexpr int mixed_waves(int H) { return HHLB_MIXED_WAVES(H); }
+// increment and the sources take 7 H registers per lane with two slots, 4 H
+// with one
+constexpr int mixed_waves(int H, int slots) { return H <= 8 ? 4 : 3; }
 
 template <int Q, int PREC>
 constexpr bool mixed_mfma() { return PREC != kPrecF32 || Q == 16; }
 
 // LDS of a window (bytes): the moment partials, the equilibrium populations,
 // a tile per wave for the force block.  At H = 16, and for f alone, the tiles
-// lie in the memory of the partials: 48 KB, three blocks per CU, where 60 KB
+// lie in the memory of the partials (two slots): 48 KB, three blocks per CU, where 60 KB
 // would leave two (f alone, Q = 6: 20 KB, seven blocks of two waves, not five).
-constexpr int mixed_part(int nfun) { return 2 * step_sums(nfun) * kStepCells * 8; }
-constexpr int kMixedTile = 64 * 16 * 4;
-template <int Q, int NFUN, int PREC>
-constexpr bool mixed_alias() { return mixed_mfma<Q, PREC>() && (Q > 12 || NFUN == 1); }
-template <int Q, int NFUN, int PREC>
-constexpr int mixed_tile_offset() { return mixed_alias<Q, NFUN, PREC>() ? 0 : mixed_part(NFUN); }
-template <int Q, int NFUN, int PREC>
-constexpr int mixed_geq_offset() {
-  constexpr int tiles = mixed_mfma<Q, PREC>() ? 2 * NFUN * kMixedTile : 0;
-  return mixed_alias<Q, NFUN, PREC>() ? (tiles > mixed_part(NFUN) ? tiles : mixed_part(NFUN)) : mixed_part(NFUN) + tiles;
-}
-template <int Q, int NFUN, int PREC>
-constexpr int mixed_lds_bytes() { return mixed_geq_offset<Q, NFUN, PREC>() + 2 * 2 * Q * 64 * 8 + 2 * 8; }
+template <int Q, int NFUN, int PREC, int SLOTS>
+struct MixedLds {
+  static constexpr bool kMfma = mixed_mfma<Q, PREC>();
+  static constexpr bool kAlias = kMfma && (Q > 12 || NFUN == 1);
+  static constexpr int kTile = 64 * 16 * 4;
+  static constexpr int part = 2 * step_sums(NFUN) * 64 * SLOTS * 8;
+  static constexpr int tiles = kMfma ? 2 * NFUN * kTile : 0;
+  static constexpr int tile_at = kAlias ? 0 : part;
+  static constexpr int geq_at = kAlias ? (tiles > part ? tiles : part) : part + tiles;
+  static constexpr int nw_at = geq_at + 2 * SLOTS * Q * 64 * 8;
+  static constexpr int bytes = nw_at + 2 * 8;
+};
 
 // nsteps steps of nst stages of one window, run by a block of 2 NFUN waves
 // (3; or 1: one forward-Euler stage, whose increment goes to the output, for
 // the residual).
-template <int Q, int NFUN, int ADV, int PREC>
-__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(mixed_waves(Q)))) void
+template <int Q, int NFUN, int ADV, int PREC, int SLOTS>
+__global__ __launch_bounds__(128 * NFUN) __attribute__((amdgpu_waves_per_eu(mixed_waves(Q, SLOTS)))) void
 step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChannel *__restrict__ chans,
                   const DevFusedWindow *__restrict__ wins, const double *__restrict__ inv_dx,
                   const double *__restrict__ gw, const float *__restrict__ in_f, const float *__restrict__ in_c) {
-  constexpr int H = Q, SLOTS = 2;
+  using L = MixedLds<Q, NFUN, PREC, SLOTS>;
+  constexpr int H = Q, P = step_cells(SLOTS);
   constexpr bool kMfmaEq = step_mfma<0, Q>();
-  constexpr bool kMfmaK = mixed_mfma<Q, PREC>();
-  __shared__ __align__(16) char s_lds[mixed_lds_bytes<Q, NFUN, PREC>()];
+  constexpr bool kMfmaK = L::kMfma, kAlias = L::kAlias;
+  __shared__ __align__(16) char s_lds[L::bytes];
   const DevFusedWindow win = wins[A.xcd_map ? xcd_window(blockIdx.x, A.nwin) : (int)blockIdx.x];
   ConstTables tp = (ConstTables)tb;
   ConstChannel cp = (ConstChannel)(chans + win.ch);
@@ -372,17 +385,17 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
   const int Nx = cp->Nx, c0 = win.c0;
   const double sg = hw ? -1.0 : 1.0;
   double *s_part = (double *)s_lds;
-  float *s_tile = (float *)(s_lds + mixed_tile_offset<Q, NFUN, PREC>() + wv * kMixedTile);
-  double *s_geq = (double *)(s_lds + mixed_geq_offset<Q, NFUN, PREC>());
-  double *s_nw = s_geq + 2 * 2 * H * 64;
-  // plane (parity of the position) and cell of each slot
-  const int plane[SLOTS] = {hw, 1 - hw};
-  const int i[SLOTS] = {hw ? c0 + 127 - 2 * lane : c0 + 2 * lane, hw ? c0 + 126 - 2 * lane : c0 + 2 * lane + 1};
+  float *s_tile = (float *)(s_lds + L::tile_at + wv * L::kTile);
+  double *s_geq = (double *)(s_lds + L::geq_at), *s_nw = (double *)(s_lds + L::nw_at);
+  // plane (position modulo the slots) and cell of each slot (the first, of one)
+  const int plane[2] = {SLOTS == 1 ? 0 : hw, 1 - hw};
+  const int i[2] = {hw ? c0 + (P - 1) - SLOTS * lane : c0 + SLOTS * lane,
+                    hw ? c0 + (P - 2) - SLOTS * lane : c0 + SLOTS * lane + 1};
   const int first = win.i0 - c0, last = first + win.nout - 1;   // output positions
-  const bool needL = c0 < 0, needR = Nx - 1 - c0 <= kStepCells - 1 - kStepGhosts;
+  const bool needL = c0 < 0, needR = Nx - 1 - c0 <= P - 1 - kStepGhosts;
   const bool down = hw ? needL : needR, up = hw ? needR : needL;
 
-  const int w0 = c0 < 0 ? 0 : c0, w1 = c0 + kStepCells < Nx ? c0 + kStepCells : Nx;
+  const int w0 = c0 < 0 ? 0 : c0, w1 = c0 + P < Nx ? c0 + P : Nx;
   const uint32_t wcells = (uint32_t)(w1 - w0);
   uint32_t cell[SLOTS];   // index in the window's rows; huge where the position has no cell
   bool inside[SLOTS];
@@ -413,9 +426,9 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
         hi[j][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, cell[s] * 4u, 0, 0));
         d[j][s] = 0.0f;
       }
-      const unsigned l0 = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, cell[0] * 2u, 0, 0);
-      const unsigned l1 = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, cell[1] * 2u, 0, 0);
-      lo[j] = l0 | (l1 << 16);
+      lo[j] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, cell[0] * 2u, 0, 0);
+      if constexpr (SLOTS == 2)
+        lo[j] |= (unsigned)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, cell[1] * 2u, 0, 0) << 16;
     }
   }
 
@@ -426,7 +439,7 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     const double b_s = st == 0 ? 1.0 : (st == 1 ? 0.25 : 2.0 / 3.0);   // 1 - a_s
     // positions whose result is still exact after this stage
     const int left = 3 * (A.nst - 1 - st);
-    const int lo_q = needL ? 0 : first - left, hi_q = needR ? kStepCells - 1 : last + left;
+    const int lo_q = needL ? 0 : first - left, hi_q = needR ? P - 1 : last + left;
 
     // ---- closure, part 1: ghosts of the nodes flowing into a wall are
     // extrapolated quadratically from the three nearest cells (Sec. IV.C.3);
@@ -435,14 +448,14 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     if (down) {
       int ln = lane;   // what the closure needs of the lane is formed anew, not kept through the steps
       asm volatile("" : "+v"(ln));
-      const int pd = hw ? kStepCells - 1 + c0 : Nx - 1 - c0;   // wind position of the wall cell
-      const int lp = pd >> 1;
+      const int pd = hw ? P - 1 + c0 : Nx - 1 - c0;   // wind position of the wall cell
+      const int lp = SLOTS == 2 ? pd >> 1 : pd;
       const bool odd = pd & 1;
       float c_[3][SLOTS];
       bool ghost[SLOTS];
 #pragma unroll
       for (int s = 0; s < SLOTS; ++s) {
-        const int gi = 2 * ln + s - pd;   // ghost order 1, 2 (else <= 0)
+        const int gi = SLOTS * ln + s - pd;   // ghost order 1, 2 (else <= 0)
         ghost[s] = gi == 1 || gi == 2;
         c_[0][s] = gi == 1 ? 3.0f : 6.0f;
         c_[1][s] = gi == 1 ? -3.0f : -8.0f;
@@ -451,11 +464,24 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
       float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        const float ye = hi[j][0] + d[j][0], yo = hi[j][1] + d[j][1];
-        const float e0 = readlane_f(ye, lp), o0 = readlane_f(yo, odd ? lp : lp - 1), e1 = readlane_f(ye, lp - 1),
-                    o1 = readlane_f(yo, lp - 1);
-        const float y0 = odd ? o0 : e0, y1 = odd ? e0 : o0, y2 = odd ? o1 : e1;
+        float y0, y1, y2;
+        const float ye = hi[j][0] + d[j][0];
+        if constexpr (SLOTS == 1) {
+          y0 = readlane_f(ye, lp);
+          y1 = readlane_f(ye, lp - 1);
+          y2 = readlane_f(ye, lp - 2);
+        } else {
+          const float yo = hi[j][1] + d[j][1];
+          const float e0 = readlane_f(ye, lp), o0 = readlane_f(yo, odd ? lp : lp - 1), e1 = readlane_f(ye, lp - 1),
+                      o1 = readlane_f(yo, lp - 1);
+          y0 = odd ? o0 : e0;
+          y1 = odd ? e0 : o0;
+          y2 = odd ? o1 : e1;
+        }
         if (ln == j) { a0 = y0; a1 = y1; a2 = y2; }
+        // taken here: sunk to where the f wave uses them, every node's values
+        // would stay in scalar registers (Q = 16: 100 of them spilled)
+        if constexpr (H > 12) asm volatile("" : "+v"(a0), "+v"(a1), "+v"(a2));
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
           if (ghost[s]) d[j][s] = fmaf(c_[2][s], y2, fmaf(c_[1][s], y1, c_[0][s] * y0));
@@ -474,12 +500,12 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     // ---- partial moments of this half (FP64) and the rank-1 force projections ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     auto part = [&](int h, int q, int s) -> double & {
-      return s_part[((h * step_sums(NFUN) + q) * 2 + plane[s]) * 64 + pl];
+      return s_part[((h * step_sums(NFUN) + q) * SLOTS + plane[s]) * 64 + pl];
     };
     {
-      double m0[SLOTS] = {0.0, 0.0}, mb[SLOTS] = {0.0, 0.0};
+      double m0[SLOTS] = {}, mb[SLOTS] = {};
       if (fn == 0) {   // uniform over the wave
-        double m1[SLOTS] = {0.0, 0.0}, m2[SLOTS] = {0.0, 0.0};
+        double m1[SLOTS] = {}, m2[SLOTS] = {};
 #pragma unroll
         for (int j = 0; j < H; ++j)
 #pragma unroll
@@ -523,7 +549,9 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
       typedef const __attribute__((address_space(4))) double *ConstDoubles;
       ConstDoubles gww = (ConstDoubles)gw + cp->gw_off + (hw ? 3 * H : 0);
       asm volatile("" : "+s"(gww));
-      const bool gh[SLOTS] = {hw ? i[0] >= Nx : i[0] < 0, hw ? i[1] >= Nx : i[1] < 0};
+      bool gh[SLOTS];
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) gh[s] = hw ? i[s] >= Nx : i[s] < 0;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
         const float ghost = (float)(sc * gww[j] * tp->iwq[j]);
@@ -553,18 +581,19 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     }
 
     // ---- equilibrium populations phi^eq_k / n of this half (FP64): with f
-    // and chi, each of the half's two waves takes one slot ----
+    // and chi, each of the half's two waves takes one slot (of one slot, the f
+    // wave) ----
     asm volatile("" : "+s"(tp), "+s"(cp));
     const bool collide = cp->inv_Kn != 0.0;
     if (collide) {
 #pragma unroll 1
-      for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 ? fn + 1 : SLOTS); ++e) {
+      for (int e = NFUN > 1 ? fn : 0; e < (NFUN > 1 && (SLOTS == 2 || fn == 0) ? fn + 1 : SLOTS); ++e) {
         double G[Q];
-        const int qp = (e == 0 ? plane[0] : plane[1]) + 2 * pl;   // position
-        half_range_coeffs<Q>(tp, e == 0 ? u[0] : u[1], e == 0 ? T[0] : T[1], sg, lane, lad,
-                             (e == 0 ? inside[0] : inside[1]) && qp >= lo_q && qp <= hi_q, wide, G);
+        const int qp = (e == 0 ? plane[0] : plane[SLOTS - 1]) + SLOTS * pl;   // position
+        half_range_coeffs<Q>(tp, e == 0 ? u[0] : u[SLOTS - 1], e == 0 ? T[0] : T[SLOTS - 1], sg, lane, lad,
+                             (e == 0 ? inside[0] : inside[SLOTS - 1]) && qp >= lo_q && qp <= hi_q, wide, G);
         asm volatile("" : "+s"(tp));
-        double *ge = s_geq + (hw * 2 + e) * H * 64;
+        double *ge = s_geq + (hw * SLOTS + e) * H * 64;
         if constexpr (kMfmaEq) {
           double aH[H / 4];
           mfma_operand<H>(tb->HWss, lane, aH);
@@ -605,14 +634,16 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < H; ++j) src[j][0] = src[j][1] = 0.0f;
+      for (int j = 0; j < H; ++j)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) src[j][s] = 0.0f;
 #pragma unroll
       for (int jj = 0; jj < H; ++jj) {
-        const float y0 = hi[jj][0] + d[jj][0], y1 = hi[jj][1] + d[jj][1];
+        const float y0 = hi[jj][0] + d[jj][0], y1 = hi[jj][SLOTS - 1] + d[jj][SLOTS - 1];
 #pragma unroll
         for (int j = 0; j < H; ++j) {
           src[j][0] = fmaf(tp->Ks[j * H + jj], y0, src[j][0]);
-          src[j][1] = fmaf(tp->Ks[j * H + jj], y1, src[j][1]);
+          if constexpr (SLOTS == 2) src[j][1] = fmaf(tp->Ks[j * H + jj], y1, src[j][1]);
         }
       }
 #pragma unroll
@@ -637,7 +668,7 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           const double y = hi[j][s] + d[j][s];
-          const float v = (float)fma(nT[s], s_geq[((hw * 2 + s) * H + j) * 64 + lane], -(cT[s] * y));
+          const float v = (float)fma(nT[s], s_geq[((hw * SLOTS + s) * H + j) * 64 + lane], -(cT[s] * y));
           src[j][s] = fmaf(b_f, d[j][s], src[j][s] + v);
         }
     } else {
@@ -648,35 +679,47 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
     }
     // keep the finished sources in registers
 #pragma unroll
-    for (int j = 0; j < H; ++j) asm volatile("" : "+v"(src[j][0]), "+v"(src[j][1]));
+    for (int j = 0; j < H; ++j)
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) asm volatile("" : "+v"(src[j][s]));
 
     // ---- pass 2: advection (Sec. IV.C.2): the flux difference of a cell from
     // its faces' deviations, v (y_i - y_{i-1}) + (v dev_i - v dev_{i-1}) with
     // i - 1 upwind; a wall's emergent face is the ghost itself (deviation 0) ----
-    const int q0 = plane[0] + 2 * pl, q1 = plane[1] + 2 * pl;
-    const bool use0 = inside[0] && q0 >= lo_q - 1 && q0 <= hi_q + 1, use1 = inside[1] && q1 >= lo_q - 1 && q1 <= hi_q + 1;
-    const bool wf0 = hw ? i[0] == Nx : i[0] == -1, wf1 = hw ? i[1] == Nx : i[1] == -1;
-    const float sdx0 = (float)(-dxi[0] * bdt), sdx1 = (float)(-dxi[1] * bdt);
+    bool use[SLOTS], wf[SLOTS];
+    float sdx[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      const int q = plane[s] + SLOTS * pl;
+      use[s] = inside[s] && q >= lo_q - 1 && q <= hi_q + 1;
+      wf[s] = hw ? i[s] == Nx : i[s] == -1;
+      sdx[s] = (float)(-dxi[s] * bdt);
+    }
     asm volatile("" : "+s"(tp));
 #pragma unroll
     for (int j = 0; j < H; ++j) {
       const float v = fabsf(tp->pf[j]);
       float dm, da, fa, fb;
-      devs_down2<ADV>(hi[j][0] + d[j][0], hi[j][1] + d[j][1], use0, use1, dm, da, fa, fb);
+      if constexpr (SLOTS == 2)
+        devs_down2<ADV>(hi[j][0] + d[j][0], hi[j][1] + d[j][1], use[0], use[1], dm, da, fa, fb);
+      else
+        dev_down1<ADV>(hi[j][0] + d[j][0], use[0], dm, fa);
       if (up) {
         asm volatile("");
-        if (wf0) fa = 0.0f;
-        if (wf1) fb = 0.0f;
+        if (wf[0]) fa = 0.0f;
+        if constexpr (SLOTS == 2)
+          if (wf[1]) fb = 0.0f;
       }
       fa *= v;
-      fb *= v;
-      const float fu = dpp_shr1f(fb);
-      d[j][0] = fmaf(sdx0, fmaf(v, dm, fa - fu), src[j][0]);
-      d[j][1] = fmaf(sdx1, fmaf(v, da, fb - fa), src[j][1]);
-      asm volatile("" : "+v"(d[j][0]), "+v"(d[j][1]));
+      if constexpr (SLOTS == 2) fb *= v;
+      const float fu = dpp_shr1f(SLOTS == 2 ? fb : fa);
+      d[j][0] = fmaf(sdx[0], fmaf(v, dm, fa - fu), src[j][0]);
+      if constexpr (SLOTS == 2) d[j][1] = fmaf(sdx[1], fmaf(v, da, fb - fa), src[j][1]);
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) asm volatile("" : "+v"(d[j][s]));
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (mixed_alias<Q, NFUN, PREC>()) __syncthreads();   // the next partials overwrite the tiles
+    if constexpr (kAlias) __syncthreads();   // the next partials overwrite the tiles
     if (st == 2) {
 #pragma unroll
       for (int j = 0; j < H; ++j) {
@@ -691,7 +734,8 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
           l2 |= (unsigned)(uint16_t)ln << (16 * s);
         }
         lo[j] = l2;
-        asm volatile("" : "+v"(hi[j][0]), "+v"(hi[j][1]), "+v"(lo[j]));
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) asm volatile("" : "+v"(hi[j][s]), "+v"(lo[j]));
         __builtin_amdgcn_sched_barrier(0);
       }
     }

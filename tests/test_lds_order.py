@@ -49,7 +49,7 @@ def resolve(text, env):
             pos = end + 1
             continue
         expr = re.sub(r"\w+<[^<>]*>\(\)", lambda c: c.group().split("<")[0], cond)
-        expr = expr.replace("&&", " and ").replace("||", " or ").replace("PREC", "'PREC'")
+        expr = re.sub(r"!(?!=)", " not ", expr).replace("&&", " and ").replace("||", " or ").replace("PREC", "'PREC'")
         taken = bool(eval(expr, {}, env))
         yes_end = statement(text, end + 1)
         out.append(text[pos:m.start()])
@@ -127,24 +127,32 @@ def stage_loop(name):
     return text[i:closing(text, i) + 1]
 
 
+def fp64_env(quad, mfma, nfun, slots, collide):
+    own = mfma and nfun == 1 and slots == 1
+    return dict(H=16 if mfma else 8, QUAD=quad, kMfma=mfma, NFUN=nfun, SLOTS=slots, collide=collide, kOwnEq=own, kAlias=mfma and not own,
+                kDefer=mfma and slots == 2)
+
+
 @pytest.mark.parametrize("collide", [True, False])
+@pytest.mark.parametrize("slots", [1, 2])
 @pytest.mark.parametrize("nfun", [1, 2])
 @pytest.mark.parametrize("quad,mfma", [(0, False), (0, True), (1, False)])
-def test_fp64_step_kernel(quad, mfma, nfun, collide):
-    env = dict(QUAD=quad, kMfma=mfma, NFUN=nfun, collide=collide)
-    assert not conflicts(resolve(stage_loop("fused_kernels.hpp"), env), mfma, collide)
+def test_fp64_step_kernel(quad, mfma, nfun, slots, collide):
+    env = fp64_env(quad, mfma, nfun, slots, collide)
+    assert not conflicts(resolve(stage_loop("fused_kernels.hpp"), env), env["kAlias"], collide)
 
 
 @pytest.mark.parametrize("collide", [True, False])
+@pytest.mark.parametrize("slots", [1, 2])
 @pytest.mark.parametrize("nfun", [1, 2])
 @pytest.mark.parametrize("mfma_k,alias", [(False, False), (True, False), (True, True)])
-def test_mixed_step_kernel(mfma_k, alias, nfun, collide):
-    env = dict(NFUN=nfun, kMfmaEq=False, kMfmaK=mfma_k, mixed_alias=alias, collide=collide)
+def test_mixed_step_kernel(mfma_k, alias, nfun, slots, collide):
+    env = dict(H=16 if alias else 8, NFUN=nfun, SLOTS=slots, kMfmaEq=False, kMfmaK=mfma_k, kAlias=alias, collide=collide)
     assert not conflicts(resolve(stage_loop("mixed_kernels.hpp"), env), alias, collide)
 
 
 def test_a_removed_barrier_is_found():
-    env = dict(QUAD=1, kMfma=False, NFUN=2, collide=True)
+    env = fp64_env(1, False, 2, 2, True)
     loop = resolve(stage_loop("fused_kernels.hpp"), env)
     for m in re.finditer(r"__syncthreads\(\);", loop):
         assert conflicts(loop[:m.start()] + loop[m.end():], False, True), loop[m.start() - 200:m.end()]
