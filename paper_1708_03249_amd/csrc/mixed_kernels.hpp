@@ -21,7 +21,7 @@
 // y_s = hi + d_in, a_s = 0, 3/4, 1/3 the weights of y^n in Eq. (rk3).  The
 // force block -F (K y) is contracted on the matrix cores: FP32 MFMA (16 x 16 x 4) for the FP32 form
 // at Q = 16, BF16 or FP16 MFMA (16 x 16 x 16, FP32 accumulation) for those
-// forms at every Q (zero-padded to 16), and FP32 VALU otherwise.
+// forms above Q = 4 (zero-padded to 16), and FP32 VALU otherwise.
 //
 // Mapping, window geometry (two cells or one per lane) and the split of the
 // equilibrium between the waves are those of the FP64 step kernel: (hi, lo) and
@@ -342,8 +342,13 @@ __device__ __forceinline__ void mfma_force(const ForceA<PREC> &aM, const ForceDe
 // with one
 constexpr int mixed_waves(int H, int slots) { return H <= 8 ? 4 : 3; }
 
+// The force block on the matrix cores: FP32 at Q = 16 (below, the vector ALU does
+// without the padding to 16), the other forms above four nodes: a block of 2 x 2
+// or 4 x 4 is 16 to 64 times padding there, and takes FP32 vector arithmetic in
+// every form (64 channels of 16384 cells, BF16: Q = 2 193 -> 105, Q = 4 245 -> 166
+// us a step).
 template <int Q, int PREC>
-constexpr bool mixed_mfma() { return PREC != kPrecF32 || Q == 16; }
+constexpr bool mixed_mfma() { return PREC == kPrecF32 ? Q == 16 : Q > 4; }
 
 // LDS of a window (bytes): the moment partials, the equilibrium populations,
 // a tile per wave for the force block.  At H = 16, and for f alone, the tiles
