@@ -425,7 +425,8 @@ step_kernel_mixed(StageArgs A, const DevTables *__restrict__ tb, const DevChanne
 #pragma unroll
     for (int j = 0; j < H; ++j) {
       const __amdgpu_buffer_rsrc_t r = w.take((int64_t)Nx * 4, wcells * 4u);
-      const __amdgpu_buffer_rsrc_t rl = wl.take((int64_t)Nx * 2, wcells * 2u);
+      // the one stage for the residual reads no correction words
+      const __amdgpu_buffer_rsrc_t rl = wl.take((int64_t)Nx * 2, A.nst == 1 ? 0u : wcells * 2u);
 #pragma unroll
       for (int s = 0; s < SLOTS; ++s) {
         hi[j][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, cell[s] * 4u, 0, 0));
