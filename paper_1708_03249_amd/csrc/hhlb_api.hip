@@ -1899,11 +1899,16 @@ hhlb_status multi_launch_checks(const MultiSet &ms, const void *f, int64_t npts,
 
 // Launch the whole-step kernel if the set has one: the y and z velocities of a
 // point fit the lanes of a wave, V_x has an instance, and the block's LDS stays
-// within 64 KB.  The others run one launch per stage.
+// within 64 KB.  The others run one launch per stage, and so does a right-hand
+// side alone at few points where an axis' order exceeds 7: it waits for one stage
+// of one wave, whose orders stop at the axis' own in the stage kernel and at 20
+// here (HH(10) x H(4), 100 and 3000 points: 40 and 40 against 52 and 46 us).
 bool multi_whole(const MultiSet &ms, const hhlb::MultiArgs &a, hipStream_t s) {
   const int P = ms.V / ms.shape.Va[0];
   if (P > 64) return false;
   if (a.npts <= 0) return true;
+  constexpr int kFewBlocks = 64;
+  if (a.rhs_only && ms.nmax > 7 && a.npts <= (int64_t)kFewBlocks * hhlb::kMultiWaves * (64 / P)) return false;
   return ms.nmax <= 3 ? hhlb::launch_multi_n3(a, ms.shape, s)
                       : (ms.nmax <= 7 ? hhlb::launch_multi_n7(a, ms.shape, s) : hhlb::launch_multi_n20(a, ms.shape, s));
 }
