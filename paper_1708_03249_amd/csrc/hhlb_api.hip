@@ -319,15 +319,15 @@ struct ModelClass {
   Launcher step = nullptr, step_of[2] = {nullptr, nullptr};
   int slots = 2;
   int64_t positions[2] = {0, 0};   // of its windows with either number of slots
-  std::vector<hhlb::DevWindow> windows;
-  int max_out = 0;     // the longest of them
-  size_t win_off = 0;  // byte offset in workspace
-  std::vector<hhlb::DevFusedWindow> fwindows;   // the step kernel's windows (9-cell halos)
-  size_t fwin_off = 0;
+  std::vector<hhlb::DevFusedWindow> fwindows;   // its windows (9-cell halos)
+  size_t fwin_off = 0;  // byte offset in workspace
   bool whole = true;   // every channel fits one window of the step kernel
   // Q > 16 (half-range Hermite, FP64): the node-parallel stage, whose tables
   // (DevLarge, then KinT and HWs) live in their own workspace block
   bool large = false;
+  std::vector<hhlb::DevWindow> windows;
+  int max_out = 0;     // the longest of them
+  size_t win_off = 0;
   int tiles = 0;       // of 16 nodes, over both halves
   int32_t cells = 0;   // of its channels
   size_t sums_at = 0;  // its partial sums (doubles) in either buffer
@@ -570,26 +570,17 @@ void add_composite_entries(T &d, int o, double ytop, long double inv_s2pi) {
 hhlb_status make_tables(const hhlb_channel &h, int N, int precision, const hhlb::Rule &r, hhlb::DevTables &d) {
   std::memset(&d, 0, sizeof(d));
   for (int k = 0; k < r.V; ++k) d.p[k] = r.p[k];
-  for (int k = 0; k < r.H; ++k) { d.z[k] = (double)r.z[k]; d.w[k] = (double)r.w[k]; d.vv[k] = r.p[k] * r.p[k]; }
+  for (int k = 0; k < r.H; ++k) { d.w[k] = (double)r.w[k]; d.vv[k] = r.p[k] * r.p[k]; }
   for (int l = 0; l < h.Q + 1 && l < (int)r.a.size(); ++l) d.a[l] = (double)r.a[l];
-  for (int l = 0; l < h.Q + 2 && l < (int)r.b.size(); ++l) {
-    d.sb[l] = (double)sqrtl(r.b[l]);
-    d.isb[l] = (double)(1.0L / sqrtl(r.b[l]));
-  }
   if (hhlb::half_range(h.quad)) {
     for (int j = 0; j < r.H * r.H; ++j) d.Kin[j] = r.Kin[j];
     for (int k = 0; k < r.H; ++k) { d.ka[k] = r.ka[k]; d.kb[k] = r.kb[k]; }
-    for (int k = 0; k < r.H; ++k)
-      for (int l = 0; l < h.Q; ++l) d.HW[k * h.Q + l] = l <= N ? r.HW[(size_t)k * h.Q + l] : 0.0;
   } else {
     for (int j = 0; j < r.V * r.V; ++j) d.Kin[j] = r.K[j];
     for (int k = 0; k < r.V; ++k)
       for (int l = 0; l < h.Q; ++l) d.HW[k * h.Q + l] = l <= N ? r.HW[(size_t)k * h.Q + l] : 0.0;
   }
-  std::vector<long double> tau, lam;
-  hhlb::gauss_legendre01(hhlb::kNc, tau, lam);
   const long double inv_s2pi = 1.0L / sqrtl(2 * 3.141592653589793238462643383279502884L);
-  for (int j = 0; j < hhlb::kNc; ++j) { d.tau[j] = (double)tau[j]; d.lamw[j] = (double)(lam[j] * inv_s2pi); }
   d.inv_p0 = 1.0 / h.p0;
   // monic recurrence and the normalisation folded into the contraction
   std::vector<long double> HWs((size_t)r.H * h.Q, 0.0L);
@@ -1013,6 +1004,7 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
       d.half_Dt = 0.5 * h.transverse_dof;
       d.inv_1pDt = 1.0 / (1.0 + h.transverse_dof);
       s->dch.push_back(d);
+      if (!mc.large) continue;
       // windows of at most kWin cells and nearly equal length, so that a wall's
       // three nearest cells lie in one
       const int nw = (h.Nx + hhlb::kWin - 1) / hhlb::kWin;
@@ -1072,8 +1064,8 @@ hhlb_status hhlb_create(const hhlb_channel *channels, int32_t n_ch, int32_t prec
     s->o_chclass = take(sizeof(int32_t) * n_ch);
     s->o_V = take(sizeof(int32_t) * n_ch);
     for (auto &mc : s->classes) {
-      mc.win_off = take(sizeof(hhlb::DevWindow) * mc.windows.size());
-      mc.fwin_off = take(sizeof(hhlb::DevFusedWindow) * mc.fwindows.size());
+      if (mc.large) mc.win_off = take(sizeof(hhlb::DevWindow) * mc.windows.size());
+      else mc.fwin_off = take(sizeof(hhlb::DevFusedWindow) * mc.fwindows.size());
     }
     for (auto &g : s->groups) g.win_off = take(sizeof(hhlb::DevFusedClassWindow) * g.wins.size());
     s->o_dx = take(sizeof(double) * s->total_cells);
@@ -1141,9 +1133,10 @@ hhlb_status hhlb_bind_workspace(hhlb_solver *s, void *dev_ptr) {
   HIP_TRY(hipMemcpyAsync(ws + s->o_V, s->Vs.data(), sizeof(int32_t) * n_ch, hipMemcpyHostToDevice,
                          s->stream));
   for (auto &mc : s->classes) {
-    HIP_TRY(hipMemcpyAsync(ws + mc.win_off, mc.windows.data(), sizeof(hhlb::DevWindow) * mc.windows.size(),
-                           hipMemcpyHostToDevice, s->stream));
-    if (!mc.fwindows.empty())
+    if (mc.large)
+      HIP_TRY(hipMemcpyAsync(ws + mc.win_off, mc.windows.data(), sizeof(hhlb::DevWindow) * mc.windows.size(),
+                             hipMemcpyHostToDevice, s->stream));
+    else
       HIP_TRY(hipMemcpyAsync(ws + mc.fwin_off, mc.fwindows.data(),
                              sizeof(hhlb::DevFusedWindow) * mc.fwindows.size(), hipMemcpyHostToDevice, s->stream));
     if (mc.large)
@@ -1743,7 +1736,7 @@ hhlb_status hhlb_launch_info(const hhlb_solver *s, int32_t *launches_per_stage, 
   }
   if (windows_total) {
     int64_t t = 0;
-    for (auto &mc : s->classes) t += (int64_t)mc.windows.size();
+    for (auto &mc : s->classes) t += (int64_t)(mc.large ? mc.windows.size() : mc.fwindows.size());
     *windows_total = t;
   }
   return HHLB_OK;

@@ -9,7 +9,6 @@
 namespace hhlb {
 
 constexpr int kQmaxDev = 16;   // largest per-half order with a kernel
-constexpr int kNc = 8;         // Gauss-Legendre points of the full-range kernel's correction
 constexpr int kLadder = 8;     // calibrated correction point counts the half-range kernel chooses from
 constexpr int kComposite = 6;  // beyond them: the top count on 2, 4, .., 64 panels
 constexpr int kLadderAll = kLadder + kComposite;
@@ -23,14 +22,11 @@ constexpr int kHalo = 3;
 struct DevTables {
   double p[2 * 256];                      // p_k / m (every node, also of the large-Q classes)
   double vv[kQmaxDev];                    // half: (p_k / m)^2
-  double z[kQmaxDev], w[kQmaxDev];        // positive nodes (units of p0), weights
+  double w[kQmaxDev];                     // weights of the positive nodes
   double a[kQmaxDev + 2];                 // recurrence: sqrt(b_{l+1}) h_{l+1} = (z-a_l) h_l - sqrt(b_l) h_{l-1}
-  double sb[kQmaxDev + 3];                // sqrt(b_l)
-  double isb[kQmaxDev + 3];               // 1/sqrt(b_l)
   double Kin[kQmaxDev * kQmaxDev];        // half: + half within block (H x H); full: dense V x V
   double ka[kQmaxDev], kb[kQmaxDev];      // half: rank-1 cross term
-  double HW[2 * kQmaxDev * kQmaxDev];     // half: H x Q; full: V x Q (zero beyond N)
-  double tau[kNc], lamw[kNc];             // GL nodes in (0,1), weights * 1/sqrt(2 pi)
+  double HW[kQmaxDev * kQmaxDev];         // full: V x Q (zero beyond N)
   double inv_p0;
   // half-range kernel: monic recurrence q_{l+1} = (x - a_l) q_l - b_l q_{l-1}
   double mb[kQmaxDev + 2];                // b_l
