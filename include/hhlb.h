@@ -181,11 +181,12 @@ hhlb_status hhlb_step(hhlb_solver *s, int64_t n_steps);
  *                 0 = block b handles window b.
  *  waves_per_window, step_fusion: kept for callers that set them.  Classes
  *                 with Q <= 16 run whole steps (Eq. rk3) per launch whatever
- *                 the value -- windows of 128 cells with 9-cell halos, one
- *                 wave per momentum half and function, y^n and the stage state
- *                 in registers; classes whose channels fit one window each
- *                 (Nx <= 124) up to 64 steps per launch -- and larger ones
- *                 launch their stages.
+ *                 the value -- windows of 128 cells with 9-cell halos (of 64
+ *                 where the class's channels fit those better), one wave per
+ *                 momentum half and function, y^n and the stage state in
+ *                 registers; classes whose channels fit one window each
+ *                 (Nx <= 124, or 60) up to 64 steps per launch -- and larger
+ *                 ones launch their stages.
  *  merge_classes: 0 = launches of their own for each model class; 1 = one
  *                 launch per step for all FP64 half-range classes that share
  *                 the functions (f, or f and chi) and the scheme, each block
@@ -209,14 +210,15 @@ typedef struct {
 hhlb_status hhlb_set_tuning(hhlb_solver *s, const hhlb_tuning *t);
 hhlb_status hhlb_get_tuning(const hhlb_solver *s, hhlb_tuning *t);
 
-/* Autotuner: times trial_steps steps of every candidate configuration
- * (step_fusion in {0, 1} when a class has the fused-step kernel;
- * waves_per_window in {2, 4} when a class has the four-wave kernel; direct
+/* Autotuner: times trial_steps steps of every candidate configuration (direct
  * launches with class_streams in {0, 1} -- 1 only when there are several
  * classes -- and graphs of 16 steps; each with xcd_map in {1, 0}; and
  * merge_classes in {1, 2} when some classes can share a launch) on the
  * solver's own channels and keeps the fastest; *best_out (may be NULL)
- * receives it.  The trials advance the state like hhlb_step (candidates x
+ * receives it, with step_fusion 0 and waves_per_window 2.  Configurations
+ * without merge_classes are timed twice where a class is FP64 half range and
+ * four times where such a class has chi (once per value of the two switches
+ * that select nothing).  The trials advance the state like hhlb_step (candidates x
  * (trial_steps + 1) steps) and synchronise the stream; call it in place of
  * warm-up steps. */
 hhlb_status hhlb_autotune(hhlb_solver *s, int32_t trial_steps, hhlb_tuning *best_out);
@@ -251,8 +253,8 @@ hhlb_status hhlb_moments(const hhlb_solver *s, double *n_dev, double *u_dev, dou
 hhlb_status hhlb_diagnostics(hhlb_solver *s, double *n_wall_dev, double *mass_dev, double *residual_dev,
                              int32_t *nonfinite_dev);
 
-/* Kernel launches of one RK stage (for profiling); where a launch takes a
- * whole step it counts as one. */
+/* Kernel launches of one RK stage (for profiling; where a launch takes a whole
+ * step it counts as one) and the windows they cover. */
 hhlb_status hhlb_launch_info(const hhlb_solver *s, int32_t *launches_per_stage,
                              int64_t *windows_total);
 

@@ -1625,6 +1625,10 @@ extern "C" hhlb_status hhlb_autotune(hhlb_solver *s, int32_t trial_steps, hhlb_t
     if (e != hipSuccess) st = fail(HHLB_E_HIP, std::string("autotune timing: ") + hipGetErrorString(e));
     if (st) break;
     t.ms_per_step = ms / trial_steps;
+    // these two select nothing: their candidates are further samples of the same
+    // launches (the number of trials is what callers count on)
+    t.step_fusion = 0;
+    t.waves_per_window = 2;
     if (!have || t.ms_per_step < best_ms) { best = t; best_ms = t.ms_per_step; have = true; }
   }
   (void)hipEventDestroy(e0);
