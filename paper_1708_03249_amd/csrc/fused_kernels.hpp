@@ -16,7 +16,8 @@
 // independent chains.  The waves of a half share the equilibrium: each evaluates
 // it for one of the two cells of its lanes.  The halves meet in LDS: moment
 // sums, wall densities, the equilibrium populations (and, full range, the
-// populations the dense force matrix couples), two barriers per stage.
+// populations the dense force matrix couples): two barriers per stage, a third
+// for the full range's energy or where tiles share the partials' memory.
 //
 // Classes of short channels take windows of 64 cells instead, one slot per lane
 // (the host weighs the two, see slots_of): most positions of a 128-cell window
@@ -832,9 +833,9 @@ __device__ __forceinline__ void step_window(const StageArgs &A, const DevTables 
 // one or two blocks a CU holds anyway and the faces of two nodes interleave
 // (their chains bound a lone wave: at Q = 8 the advection takes 8900 of a
 // stage's 17000 cycles, 1100 a node for some 100 instructions).  16 steps of one channel
-// of 512 cells, Q = 8: 411 -> 381 us, 64 steps of HLB(15;16) 1521 -> 1442 us, 16
-// steps of 64 channels, Q = 12: 882 -> 855 us; groups of four 378, 1434 and
-// 1066 us (beyond 256 registers).
+// of 512 cells, Q = 8: 404 -> 372 us, 64 steps of HLB(15;16) 1535 -> 1493 us, 16
+// steps of 64 channels, Q = 12: 854 -> 835 us.  Groups of four gained under 1 % on
+// the first two and cost a quarter on the third (beyond 256 registers).
 constexpr int few_group(int H) { return H % 2 == 0 ? 2 : 1; }
 // waves per SIMD that fit with FEW: 4 H doubles per slot and the faces of two
 // nodes (f alone at H = 16 holds both tables' operands besides)

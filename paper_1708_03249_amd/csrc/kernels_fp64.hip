@@ -18,7 +18,8 @@ template <int QUAD, int Q, int NF, int ADV, int SLOTS>
 void launch_step(const StageArgs &a, hipStream_t s) {
   // FEW where its waves all fit the GPU at once: beyond that the many-window
   // form's third or fourth wave per SIMD is worth more.  Up to four nodes per
-  // half it gains nothing (607 against 613 us for 64 steps of a 64-cell channel).
+  // half it gains next to nothing (576 against 579 us for 64 steps of a 64-cell
+  // channel).
   constexpr int H = QUAD == 0 ? Q : Q / 2;
   if constexpr (H > 4) {
     if ((int64_t)a.nwin * 2 * NF <= (int64_t)kSimds * few_waves(H, SLOTS, NF)) {
