@@ -69,17 +69,7 @@ def bytes_per_node_update(form="fp64", nfun=2):
     """Algorithmic HBM bytes of one RK-3 step: y^n in, y^{n+1} out, per
     function 16 bytes in FP64, 12 in the mixed forms (4 bytes of hi and 2 of
     lo each way)."""
-    return nfun * {"fp64": 16, "fp64_fused": 16}.get(form, 12)
-
-
-def form_precision(H, form):
-    """Arithmetic form of a bench form name (fp64_fused: FP64 with the
-    step_fusion switch set, which selects nothing: every step is one launch)."""
-    return H.PRECISIONS["fp64" if form == "fp64_fused" else form]
-
-
-def form_tuning(form):
-    return {"step_fusion": 1} if form == "fp64_fused" else {}
+    return nfun * (16 if form == "fp64" else 12)
 
 
 def batch_workload(n_ch=4096, seed=0):
@@ -134,21 +124,20 @@ def tune_on_sample(H, torch, np, chans, form, trial_steps=10, stride=8):
 
 def run_batch(H, torch, np, args):
     """Batched workload: every form advances all channels in one launch per
-    class and stage (or per class and step with step fusion); compared with
-    the FP64 form stepping each channel as its own solver (timed on a
-    sample of channels).  Legs: each form in the default launch
-    configuration (direct launches, classes in turn on one stream); the FP64
-    form with fused steps; the FP64 form with one launch per stage across
-    its classes (a block per window, and persistent blocks), replayed as
-    16-step HIP graphs; and each form in the configuration hhlb_autotune
-    picks on every 8th channel, replayed as HIP graphs when it chooses them."""
+    class and step; compared with the FP64 form stepping each channel as its
+    own solver (timed on a sample of channels).  Legs: each form in the
+    default launch configuration (direct launches, classes in turn on one
+    stream); the FP64 form with one launch per step across its classes (a
+    block per window, and persistent blocks), replayed as 16-step HIP graphs;
+    and each form in the configuration hhlb_autotune picks on every 8th
+    channel, replayed as HIP graphs when it chooses them."""
     chans = batch_workload(args.batch_channels)
     nu_step = sum(c.V * c.Nx for c in chans)
     out = {"workload": f"{len(chans)} channels, Nx~U{{64..1024}}, Q~U{{4,8,12}}, log10 Kn~U[-3,1], "
                        "g~U[-1,0], T_right/T_left~U[1,2] (PCG64 seed 0), uniform grid, WENO5+RK3, "
                        "f and chi, dt=min(CFL 0.5, Kn/2), smoothly modulated start",
            "node_updates_per_step": nu_step, "steps": args.batch_steps, "forms": {}}
-    legs = [("fp64", "fp64", {}), ("fp64_fused", "fp64", {"step_fusion": 1}),
+    legs = [("fp64", "fp64", {}),
             ("fp64_one_launch", "fp64", {"merge_classes": 1, "graph_steps": 16}),
             ("fp64_persistent", "fp64", {"merge_classes": 2, "graph_steps": 16}),
             ("mixed_f32", "mixed_f32", {})]
@@ -180,12 +169,11 @@ def run_batch(H, torch, np, args):
         assert int(bad.item()) == 0, f"batch {name}: non-finite populations"
         used.pop("ms_per_step", None)
         # algorithmic HBM bytes of a step over its time (every class together)
-        bform = "fp64_fused" if tuning.get("step_fusion") else form
-        gbs = bytes_per_node_update(bform) * nu_step / (ms / args.batch_steps / 1e3) / 1e9
+        gbs = bytes_per_node_update(form) * nu_step / (ms / args.batch_steps / 1e3) / 1e9
         rec = {"value": nu_step * args.batch_steps / (ms / 1e3), "unit": "node-updates/s",
                "ms_per_step": ms / args.batch_steps, "tuning": used,
                "launches_per_stage": s.launch_info()[0],
-               "hbm": {"algorithmic_bytes_per_node_update": bytes_per_node_update(bform),
+               "hbm": {"algorithmic_bytes_per_node_update": bytes_per_node_update(form),
                        "achieved_GBps": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4)},
                "mass_drift": float(((mass - mass0) / mass0).abs().max().item())}
         if name == "fp64":
@@ -283,18 +271,18 @@ def run_steady(H, torch, np, args):
 
 def flops_per_node_update(Q=Q, N=Q - 1, nfun=2, nc=8):
     """Floating-point operations of one node-update (both functions, three
-    stages) as the FP64 stage kernel executes them, counting an FMA as two:
-    per node and function, the lane-parallel WENO-5 face value (smoothness
-    indicators, candidates and weights of the triple decomposition: 58), flux
-    difference and RK combination (6), structured force matrix (half block
+    stages) as the FP64 step kernel executes them, counting an FMA as two:
+    per node and function, the lane-parallel WENO-5 face value (shared
+    differences 5, smoothness indicators and weights 22, value 17), flux
+    difference and RK combination (8), structured force matrix (half block
     plus rank-1 term: 2(Q+2)) and BGK (4); per cell and shared by its 2Q
     nodes, the moment sums (7 per node) and the equilibrium: the M = (N+2)//2
     main points and nc correction points of each half, N+1 recurrence levels
-    of 8 flops each, then the table contraction 2Q (N+1) x 2."""
+    of 6 flops each, then the table contraction 2Q (N+1) x 2."""
     V = 2 * Q
     M = (N + 2) // 2
-    per_node_fn = 58 + 6 + 2 * (Q + 2) + 4
-    per_cell = 7 * V + 2 * (M + nc) * (N + 1) * 8 + V * (N + 1) * 2
+    per_node_fn = 44 + 8 + 2 * (Q + 2) + 4
+    per_cell = 7 * V + 2 * (M + nc) * (N + 1) * 6 + V * (N + 1) * 2
     return 3 * (nfun * per_node_fn + per_cell / V)
 
 
@@ -318,24 +306,24 @@ def ladder_points(counts, reach, y):
 
 
 def mean_ladder_points(s, mom, np):
-    """Average correction points per half over the windows of 58 cells, from
-    the final moments: each window takes the ladder count covering its
-    largest |u|/sqrt(T)."""
+    """Average correction points per half over the step kernel's windows (110
+    cells and their halo), from the final moments: each window takes the
+    ladder count covering its largest |u|/sqrt(T)."""
     n, u, T = mom
     y = (u.abs() / T.clamp_min(1e-300).sqrt()).cpu().numpy()
     counts, reach = s.equilibrium_ladder(0)
     tot, nw = 0.0, 0
     for k, ch in enumerate(s.channels):
         a, b = int(s.cells[k]), int(s.cells[k + 1])
-        for i0 in range(a, b, 58):
-            tot += ladder_points(counts, reach, float(y[max(a, i0 - 3):min(b, i0 + 61)].max()))
+        for i0 in range(a, b, 110):
+            tot += ladder_points(counts, reach, float(y[max(a, i0 - 9):min(b, i0 + 119)].max()))
             nw += 1
     return tot / max(nw, 1)
 
 
 def measured_counter(form, key):
     """A figure (e.g. the MFMA busy fraction) from the committed rocprofv3
-    counter record of the stage kernel, if it was taken on the kernel source
+    counter record of the step kernel, if it was taken on the kernel source
     built now; else None."""
     rec = _profile_record(form)
     return None if rec is None else rec.get(key)
@@ -344,7 +332,7 @@ def measured_counter(form, key):
 def _profile_record(form="fp64", name=None):
     import hashlib
     if name is None:
-        name = "stage_kernel_traffic.json" if form == "fp64" else f"stage_kernel_{form}_traffic.json"
+        name = f"step_kernel_{form}_traffic.json"
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
@@ -362,7 +350,7 @@ def _profile_record(form="fp64", name=None):
 
 
 def measured_traffic(form="fp64", name=None):
-    """HBM bytes per stage launch from the committed rocprofv3 FETCH_SIZE /
+    """HBM bytes per launch from the committed rocprofv3 FETCH_SIZE /
     WRITE_SIZE passes, if they were taken on the kernel source (the kernel's
     sources and the build flags) built now.  `name` picks another record."""
     rec = _profile_record(form, name)
@@ -428,8 +416,7 @@ def cpu_baseline(H, torch, np, forms, steps, n_parity=4, max_threads=16):
     starts = [start(c) for c in range(n_parity)]
     errs = {}
     for form in forms:
-        s = H.Solver(chans[:n_parity], precision=form_precision(H, form))
-        s.set_tuning(**form_tuning(form))
+        s = H.Solver(chans[:n_parity], precision=H.PRECISIONS[form])
         for k, (oc, _, _) in enumerate(starts):
             assert abs(s.dt[k] - oc.dt) <= 4.5e-16 * oc.dt, (form, k, s.dt[k], oc.dt)
         f = torch.from_numpy(np.concatenate([st[1].ravel() for st in starts])).cuda()
@@ -456,7 +443,7 @@ def cpu_baseline(H, torch, np, forms, steps, n_parity=4, max_threads=16):
 def copy_bandwidth(torch, mib=1024, reps=5):
     """Bandwidth a plain device copy of mib MiB reaches on this GPU (read +
     write bytes over the copy time, best of reps): the practical ceiling the
-    stage kernels' HBM fraction is also quoted against."""
+    step kernels' HBM fraction is also quoted against."""
     n = mib * 2**20 // 8
     src = torch.ones(n, dtype=torch.float64, device="cuda")
     dst = torch.empty_like(src)
@@ -478,8 +465,7 @@ def copy_bandwidth(torch, mib=1024, reps=5):
 def run_form(H, torch, np, chans, form, args):
     """Warm up, time args.steps steps of one arithmetic form; return its
     record and the final moments (device tensors)."""
-    s = H.Solver(chans, precision=form_precision(H, form))
-    s.set_tuning(waves_per_window=args.waves_per_window, **form_tuning(form))
+    s = H.Solver(chans, precision=H.PRECISIONS[form])
     mass0 = init_developed(s, torch, np)
     print(f"[bench] {form}: {len(chans)} channels x Nx={NX}, V={2 * Q}; workspace "
           f"{s.ws_bytes / 2**30:.2f} GiB; warmup {args.warmup}", file=sys.stderr, flush=True)
@@ -518,9 +504,8 @@ def run_form(H, torch, np, chans, form, args):
     # the scope's roof for this streaming stencil is HBM (32 B per
     # node-update in FP64, 24 in the mixed forms); the vector-ALU fraction of
     # the executed flop count rides along
-    fp64 = form in ("fp64", "fp64_fused")
-    kname = ("hhlb::step_kernel<0,16,2,0> (one RK-3 step, FP64)" if fp64 else
-             f"hhlb::step_kernel_mixed<16,2,0,{form_precision(H, form)}> (one RK-3 step, {form})")
+    kname = ("hhlb::step_kernel<0,16,2,0,false,2> (one RK-3 step, FP64)" if form == "fp64" else
+             f"hhlb::step_kernel_mixed<16,2,0,{H.PRECISIONS[form]},2> (one RK-3 step, {form})")
     roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(form),
             "kernel": kname, "algorithmic_bytes_per_node_update": bytes_per_node_update(form),
@@ -576,30 +561,28 @@ def run_ballistic(H, torch, np, nx=24, steps=2000, warmup=32):
 def run_small(H, torch, np, steps=20000, warmup=64):
     """The small channel of the parity tests, HHLB(3;4), Nx = 64, third-order
     upwind, f and chi, Kn = 0.1, g = -0.1, equal walls, dt = 5e-4, from the
-    equilibrium: 20 000 steps (t = 10) as 64-step HIP graphs, per-stage
-    launches and fused steps.  One channel of two windows is launch-bound:
-    this is the latency of a step.  HIP events on the solver's stream."""
+    equilibrium: 20 000 steps (t = 10) as 64-step HIP graphs, each one launch.
+    One channel of one window runs on four waves: this is the latency of a
+    step's chain.  HIP events on the solver's stream."""
     ch = H.Channel(quad=H.HALF_HERMITE, Q=4, N=3, Nx=64, adv=H.UPWIND3, transverse_dof=2, Kn=0.1,
                    g=-0.1, dt=5e-4)
     rec = {"workload": "HHLB(3;4) V=8, one channel, Nx=64 uniform, upwind-3+RK3, f and chi, Kn=0.1, "
                        "g=-0.1, equal walls, dt=5e-4, 64-step HIP graphs", "steps": steps}
-    for name, fusion in (("per_stage", 0), ("fused", 1)):
-        s = H.Solver([ch])
-        s.set_tuning(graph_steps=64, step_fusion=fusion)
-        s.init_equilibrium()
-        s.step(warmup)
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        torch.cuda.synchronize()
-        e0.record(s.stream)
-        s.step(steps)
-        e1.record(s.stream)
-        torch.cuda.synchronize()
-        ms = e0.elapsed_time(e1)
-        _, _, bad = s.diagnostics()
-        assert int(bad.item()) == 0, "small channel: non-finite populations"
-        s.close()
-        rec[name] = {"value": ch.V * ch.Nx * steps / (ms / 1e3), "unit": "node-updates/s",
-                     "us_per_step": 1e3 * ms / steps}
+    s = H.Solver([ch])
+    s.set_tuning(graph_steps=64)
+    s.init_equilibrium()
+    s.step(warmup)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda.synchronize()
+    e0.record(s.stream)
+    s.step(steps)
+    e1.record(s.stream)
+    torch.cuda.synchronize()
+    ms = e0.elapsed_time(e1)
+    _, _, bad = s.diagnostics()
+    assert int(bad.item()) == 0, "small channel: non-finite populations"
+    s.close()
+    rec.update(value=ch.V * ch.Nx * steps / (ms / 1e3), unit="node-updates/s", us_per_step=1e3 * ms / steps)
     return rec
 
 
@@ -608,9 +591,13 @@ def run_multi(H, torch, np, npts=1_000_000, steps=10, warmup=2):
     3-D product set HH(4) x H(4) x H(4) (V = 8 x 4 x 4 = 128, N = 3 per
     axis), npts points started at the discrete Maxwellian w_v modulated by a
     seeded smooth factor, F = (0.3, -0.2, 0.5), Kn = 0.1, dt = 1e-3.  HIP
-    events on the stream the steps run on.  Algorithmic HBM bytes per
-    node-update per RK-3 step: 64 (reads of y_s and y^n, writes of the next
-    stage; 8-byte values)."""
+    events on the stream the steps run on.  The steps (up to 64) are one
+    launch, which reads and writes each population once: 16 bytes a
+    node and launch.  The vector ALU bounds it, by the operations the method
+    needs per point and stage: per velocity the rows of three force matrices,
+    a product of three equilibrium factors, moments, relaxation and the RK-3
+    combination; per axis the coefficients at the points of the exact rule
+    (half range) or in closed form (full range) and their contraction."""
     axes = [H.Axis(H.HALF_HERMITE, 4, 3), H.Axis(H.FULL_HERMITE, 4, 3), H.Axis(H.FULL_HERMITE, 4, 3)]
     p, w = H.multi_nodes(axes)
     V = w.size
@@ -629,18 +616,24 @@ def run_multi(H, torch, np, npts=1_000_000, steps=10, warmup=2):
     ms = e0.elapsed_time(e1) / steps
     assert bool(torch.isfinite(f).all()), "multi: non-finite populations"
     nu = npts * V
-    gbs = 64.0 * nu / (ms / 1e3) / 1e9
+    launches = -(-steps // 64)
+    gbs = 16.0 * nu * launches / (steps * ms / 1e3) / 1e9
+    coeff = sum(6.0 * a.N if a.quad == H.FULL_HERMITE else 2 * 7.0 * (a.N + 1) * ((a.N + 2) // 2) for a in axes)
+    Va = [a.Q if a.quad == H.FULL_HERMITE else 2 * a.Q for a in axes]
+    stage = V * (2 * sum(Va) + 4 * len(axes) + 15) + coeff + sum(2 * v * (a.N + 1) for v, a in zip(Va, axes))
+    tfs = 3 * stage * npts / (ms / 1e3) / 1e12
     out = {"workload": f"App. A mixed quadrature, homogeneous gas: HH(4) x H(4) x H(4) (V = {V}, N = 3 per "
                        f"axis), {npts} points, F = (0.3, -0.2, 0.5), Kn = 0.1, dt = 1e-3, FP64",
            "value": nu / (ms / 1e3), "unit": "node-updates/s", "ms_per_step": ms, "steps": steps,
-           "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": round(gbs / HBM_PEAK_GBS, 4),
-                        "traffic": measured_traffic(name="multi_kernel_traffic.json"),
-                        "kernel": "hhlb::multi_kernel (one RK-3 stage)",
-                        "algorithmic_bytes_per_node_update_per_step": 64,
-                        "algorithmic_bytes_per_launch": 64.0 * nu / 3,
-                        "traffic_unit": "HBM bytes per launch, average over the three stages "
-                                        "(rocprofv3 FETCH_SIZE+WRITE_SIZE, copy-calibrated)"}}
+           "roofline": {"bound": "vector_alu", "achieved": round(tfs, 2), "peak": FP64_VECTOR_PEAK_TFLOPS,
+                        "unit": "TFLOP/s", "frac": round(tfs / FP64_VECTOR_PEAK_TFLOPS, 4),
+                        "flops_per_node_update": round(3 * stage / V, 1),
+                        "kernel": "hhlb::multi_steps_kernel<8,3,true> (all RK-3 steps of a call, up to 64)",
+                        "hbm": {"achieved_GBps": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
+                                "algorithmic_bytes_per_launch": 16.0 * nu,
+                                "traffic": measured_traffic(name="multi_steps_kernel_traffic.json"),
+                                "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE+WRITE_SIZE, "
+                                                "copy-calibrated)"}}}
     del f
     torch.cuda.empty_cache()
     return out
@@ -661,10 +654,10 @@ def main():
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--no-cpu-baseline", action="store_true")
-    ap.add_argument("--forms", default="fp64,mixed_f32,mixed_bf16,mixed_f16,fp64_fused",
+    ap.add_argument("--forms", default="fp64,mixed_f32,mixed_bf16,mixed_f16",
                     help="arithmetic forms to time; the first is the primary line")
     ap.add_argument("--waves-per-window", type=int, default=2, choices=(2, 4),
-                    help="stage-kernel shape for the large workload (4: FP64 four-wave kernel)")
+                    help="accepted, selects nothing")
     ap.add_argument("--batch-channels", type=int, default=4096,
                     help="channels of the batched uneven workload (0 skips it)")
     ap.add_argument("--batch-steps", type=int, default=1000)
